@@ -887,6 +887,9 @@ struct DecodePlan {
   std::vector<DevDecodeWork> work;
   std::vector<int32_t> tok_req;
   int max_split = 1;
+  // 16-row blocks of one workgroup: 2 when a request has more than 16 packed
+  // rows, so that those share one pass over the request's K and V.
+  int row_blocks = 1;
   size_t off_work = 0, off_pages = 0, off_tokreq = 0, off_plse = 0, off_po = 0, bytes = 0;
 };
 
@@ -929,10 +932,13 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
   // Split planning: workgroups of at least 8 tiles (two per wave), about as
   // many as the compute units hold at once (two each), so the whole step
   // runs in one round of workgroups when the requests allow it.
+  for (int b = 0; b < B; ++b)
+    if ((int64_t)(p->q_offsets[b + 1] - p->q_offsets[b]) * g > kDecRows) dp.row_blocks = 2;
+  const int rows_per_wg = kDecRows * dp.row_blocks;
   int64_t total = 0;
   for (int b = 0; b < B; ++b) {
     const int64_t n = p->q_offsets[b + 1] - p->q_offsets[b];
-    total += ceil_div(p->kv_lens[b], kDecTile) * Hkv * ceil_div(n * g, kDecRows);
+    total += ceil_div(p->kv_lens[b], kDecTile) * Hkv * ceil_div(n * g, rows_per_wg);
   }
   const int64_t per_wg = std::max<int64_t>(8, ceil_div(total, 2 * (int64_t)device_topology().cus));
   dp.reqs.resize(B);
@@ -955,7 +961,7 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
     dp.max_split = std::max(dp.max_split, ns);
     for (int t = 0; t < n; ++t) dp.tok_req[r.q0 + t] = b;
     for (int kvh = 0; kvh < Hkv; ++kvh)
-      for (int row0 = 0; row0 < n * g; row0 += kDecRows)
+      for (int row0 = 0; row0 < n * g; row0 += rows_per_wg)
         for (int s = 0; s < ns; ++s) {
           DevDecodeWork d{};
           d.b = b;
@@ -1222,7 +1228,7 @@ cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, 
   kp.page_size = p->page_size;
   kp.Tq = dp.Tq;
   kp.scale_log2 = p->softmax_scale * 1.4426950408889634f;
-  hipError_t e = timed("decode", stream, [&] { return launch_decode_bf16(kp, p->head_dim, (int)dp.work.size(), stream); });
+  hipError_t e = timed("decode", stream, [&] { return launch_decode_bf16(kp, p->head_dim, (int)dp.work.size(), dp.row_blocks, stream); });
   if (e != hipSuccess) return hip_fail("decode launch", e);
   if (dp.max_split > 1) {
     e = timed("decode_merge", stream, [&] { return launch_decode_merge_bf16(kp, p->head_dim, stream); });

@@ -6,20 +6,30 @@
 //
 // A decode step has very few query rows per (request, KV head) (n * g, e.g.
 // 4) against thousands of keys, so the work is streaming K and V out of HBM.
-// One workgroup takes a block of up to 16 packed rows of one (request, KV
-// head) and a range of 32-key tiles (the host splits a request's key axis
-// so that every compute unit holds two workgroups; partials are merged by
-// their LSE). Its four waves work independently on every fourth tile of the
-// range, so no wave ever waits on another until the end, where the four
-// partial softmax states are combined through LDS. The products use
-// v_mfma_f32_16x16x32_bf16, whose 16 columns fit the few rows of a decode
-// step. K and V go from memory straight into registers, one tile ahead of
-// their use: K already in the MFMA operand layout (each lane loads 16 bytes
-// of one key row per step), V in whole rows, written into the wave's LDS
-// tile just before its transposed reads for the PV product. Page addresses
-// come from the page table (scalar loads, a tile ahead of the loads that
-// use them). Per tile and wave: S^T = K Q^T, an online-softmax update, and
-// O^T += V^T P^T with P^T straight from the score registers.
+// One workgroup takes a block of up to 16 (NB = 1) or 32 (NB = 2) packed rows
+// of one (request, KV head) and a range of 32-key tiles (the host splits a
+// request's key axis so that every compute unit holds two workgroups;
+// partials are merged by their LSE). Its four waves work independently on
+// every fourth tile of the range, so no wave ever waits on another until the
+// end, where the four partial softmax states are combined through LDS. The
+// products use v_mfma_f32_16x16x32_bf16, whose 16 columns fit the few rows of
+// a decode step; with NB = 2 each K and V fragment feeds two of them, so 17 to
+// 32 rows stream the request's keys once instead of twice. K and V go from
+// memory straight into registers, one tile ahead of their use: K already in
+// the MFMA operand layout (each lane loads 16 bytes of one key row per step)
+// into the other of two register sets, V in whole rows into the registers
+// that its write into the wave's LDS tile (read transposed for the PV
+// product) has just freed: one V set instead of two is what leaves room for a
+// second row block without spills. Loads go through buffer resources whose
+// scalar base is the tile's page, so lane offsets are loop constants. Page
+// addresses come from the page table (scalar loads, a tile ahead of the loads
+// that use them). Per tile and wave: S^T = K Q^T, an online-softmax update,
+// and O^T += V^T P^T with P^T straight from the score registers.
+//
+// Bound by HBM. Per call, before and after the second row block and the
+// single V set: 16 requests x 8 new tokens x 4 heads per group over ~4,250
+// keys 101.6 -> 72.2 us; 64 requests x 1 new token over 4,161 keys 177.9 ->
+// 175.2 us (1.09 GB of K and V).
 #include "cas_device.h"
 
 namespace cas {
@@ -34,7 +44,8 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
 
-template <int D>
+// NB: 16-row blocks of one workgroup (1 or 2).
+template <int D, int NB>
 __global__ __launch_bounds__(kDecWaves * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void decode_bf16_kernel(DecodeParams p) {
   static_assert(kDecRows == 16, "one 16-column MFMA block of rows");
@@ -44,12 +55,12 @@ void decode_bf16_kernel(DecodeParams p) {
   constexpr int CPR = D / 8;                  // 16-byte chunks per key row
   constexpr int RPI = 64 / CPR;               // key rows per V load instruction
   constexpr int NI = kDecTile / RPI;          // V load instructions per tile
-  constexpr int OS = NDB * 4 * 64;            // floats of one wave's O^T in the closing combine
-  static_assert(OS * 4 == TB, "a wave's O^T fills its V tile");
-  // Each wave's V tile (the closing combine reuses it for the wave's O^T);
-  // m and l of every wave.
+  constexpr int OS = NDB * 4 * 64;            // floats of one wave's O^T of a row block in the closing combine
+  static_assert(OS * 4 == TB, "a wave's O^T of one row block fills its V tile");
+  // Each wave's V tile (the closing combine reuses it for the wave's O^T, one
+  // row block after the other); m and l of every wave and row block.
   __shared__ __attribute__((aligned(1024))) char vs[kDecWaves * TB];
-  __shared__ __attribute__((aligned(16))) float ml[kDecWaves * 128];
+  __shared__ __attribute__((aligned(16))) float ml[kDecWaves * NB * 128];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, bq = lane >> 4;    // MFMA column (row of the block) and k-group
@@ -59,24 +70,33 @@ void decode_bf16_kernel(DecodeParams p) {
   const int kvh = __builtin_amdgcn_readfirstlane(w.kvh);
   const int kv_len = __builtin_amdgcn_readfirstlane(rq.kv_len);
   const int nrows = rq.n * g;
-  const int my_row = w.row0 + j;
-  const bool row_ok = my_row < nrows;
-  const int my_i = my_row / g;                            // query index within the request
-  const int my_h = kvh * g + (my_row - my_i * g);
-  // Last key this row sees (rows past the block's end see every key: their
+  // Row block rb of lane (j, bq): row row0 + 16 rb + j.
+  bool row_ok[NB];
+  int my_i[NB], my_h[NB];                                 // query index within the request, query head
+  // Last key each row sees (rows past the block's end see every key: their
   // Q is zero and nothing of theirs is stored).
-  const int my_lim = row_ok ? kv_len - rq.n + my_i : kv_len - 1;
+  int my_lim[NB];
+#pragma unroll
+  for (int rb = 0; rb < NB; ++rb) {
+    const int r = w.row0 + 16 * rb + j;
+    row_ok[rb] = r < nrows;
+    my_i[rb] = r / g;
+    my_h[rb] = kvh * g + (r - my_i[rb] * g);
+    my_lim[rb] = row_ok[rb] ? kv_len - rq.n + my_i[rb] : kv_len - 1;
+  }
   const float c = p.scale_log2;
   char *const vt = vs + wave * TB;
 
   // Q as the B operand: step st of lane (j, bq) is channels 32 st + 8 bq ..
   // + 7 of row j.
-  bf16x8 qf[NQ];
-  {
-    const __bf16 *qp = (const __bf16 *)p.q + ((int64_t)(rq.q0 + (row_ok ? my_i : 0)) * Hq + my_h) * D + 8 * bq;
+  bf16x8 qf[NB][NQ];
+#pragma unroll
+  for (int rb = 0; rb < NB; ++rb) {
+    const __bf16 *qp = (const __bf16 *)p.q +
+                       ((int64_t)(rq.q0 + (row_ok[rb] ? my_i[rb] : 0)) * Hq + (row_ok[rb] ? my_h[rb] : kvh * g)) * D + 8 * bq;
 #pragma unroll
     for (int st = 0; st < NQ; ++st)
-      qf[st] = row_ok ? *reinterpret_cast<const bf16x8 *>(qp + 32 * st) : Mma<__bf16>::zero();
+      qf[rb][st] = row_ok[rb] ? *reinterpret_cast<const bf16x8 *>(qp + 32 * st) : Mma<__bf16>::zero();
   }
 
   // The pages of a tile's keys 0..15 (a) and 16..31 (b): one page when pages
@@ -93,194 +113,225 @@ void decode_bf16_kernel(DecodeParams p) {
     }
     return tp;
   };
-  // Element offset of key k0 + r (r < 32) of a tile in the pool; keys past
-  // kv_len stand in for the tile's first key.
-  auto key_off = [&](int k0, int r, const TilePages &tp) __attribute__((always_inline)) {
-    const int rr = k0 + r < kv_len ? r : 0;
-    const int page = rr < 16 ? tp.a : tp.b;
-    return (((int64_t)page * P + ((k0 + rr) & (P - 1))) * Hkv + kvh) * D;
+  // K and V of a tile come in two halves of 16 keys, each inside one page:
+  // buffer resources over the half's valid rows of this KV head (scalar base
+  // address; rows at or past kv_len read as zero), so the lane offsets are
+  // the same for every tile.
+  const int row_bytes = Hkv * D * 2;
+  struct HalfRsrc {
+    BufRsrc h[2];
+  };
+  auto half_rsrc = [&](const void *pool, int tile, const TilePages &tp) __attribute__((always_inline)) {
+    HalfRsrc r;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k0 = tile * kDecTile + 16 * h;
+      const int valid = min(16, kv_len - k0);
+      const int64_t off = (((int64_t)(h ? tp.b : tp.a) * P + (k0 & (P - 1))) * Hkv + kvh) * D;
+      r.h[h] = make_rsrc((const __bf16 *)pool + off, valid > 0 ? (valid - 1) * row_bytes + D * 2 : 0);
+    }
+    return r;
+  };
+  auto load16 = [&](BufRsrc rs, int off) __attribute__((always_inline)) {
+    return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
   };
   // K of a tile as the A operand: fragment kb * NQ + st of lane (j, bq) is
   // channels 32 st + 8 bq .. + 7 of key 16 kb + j.
+  const int koff = j * row_bytes + 16 * bq;
   auto load_k = [&](int tile, const TilePages &tp, bf16x8 (&kr)[2 * NQ]) __attribute__((always_inline)) {
-    const int k0 = tile * kDecTile;
+    const HalfRsrc r = half_rsrc(p.k_pages, tile, tp);
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      const __bf16 *src = (const __bf16 *)p.k_pages + key_off(k0, 16 * kb + j, tp) + 8 * bq;
+    for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int st = 0; st < NQ; ++st) kr[kb * NQ + st] = *reinterpret_cast<const bf16x8 *>(src + 32 * st);
-    }
+      for (int st = 0; st < NQ; ++st) kr[kb * NQ + st] = load16(r.h[kb], koff + 64 * st);
   };
   // V of a tile in whole rows: load i of a lane is chunk lane % CPR of key
   // row RPI * i + lane / CPR.
+  const int voff = (lane / CPR) * row_bytes + (lane % CPR) * 16;
   auto load_v = [&](int tile, const TilePages &tp, bf16x8 (&vr)[NI]) __attribute__((always_inline)) {
-    const int k0 = tile * kDecTile;
+    const HalfRsrc r = half_rsrc(p.v_pages, tile, tp);
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const __bf16 *src = (const __bf16 *)p.v_pages + key_off(k0, RPI * i + lane / CPR, tp) + (lane % CPR) * 8;
-      vr[i] = *reinterpret_cast<const bf16x8 *>(src);
-    }
+    for (int i = 0; i < NI; ++i) vr[i] = load16(r.h[2 * i / NI], voff + (i % (NI / 2)) * RPI * row_bytes);
   };
-  // V rows into the wave's LDS tile (16-byte chunks XOR-swizzled by row);
-  // rows past kv_len are written as zeros.
-  auto write_v = [&](int tile, const bf16x8 (&vr)[NI]) __attribute__((always_inline)) {
-    const int k0 = tile * kDecTile;
+  // V rows into the wave's LDS tile (16-byte chunks XOR-swizzled by row). Row
+  // RPI i + lane / CPR of load i differs from row lane / CPR by a constant in
+  // the address and one in the swizzle. (The asm keeps the compiler from
+  // holding every address in a register of its own.)
+  const int wbase = (lane / CPR) * (D * 2) + (((lane % CPR) ^ swz<D>(lane / CPR)) << 4);
+  auto write_v = [&](const bf16x8 (&vr)[NI]) __attribute__((always_inline)) {
+    int w0 = wbase;
+    asm volatile("" : "+v"(w0));
 #pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int r = RPI * i + lane / CPR;
-      const bf16x8 v = k0 + r < kv_len ? vr[i] : Mma<__bf16>::zero();
-      *reinterpret_cast<bf16x8 *>(vt + r * (D * 2) + (((lane % CPR) ^ swz<D>(r)) << 4)) = v;
-    }
+    for (int i = 0; i < NI; ++i)
+      *reinterpret_cast<bf16x8 *>(vt + (w0 ^ (swz<D>(RPI * i) << 4)) + RPI * i * (D * 2)) = vr[i];
   };
   // V^T as the A operand of the PV product for channel block db: lane (j, bq)
   // holds channel 16 db + j of keys 4 bq .. 4 bq + 3 and 16 + 4 bq .. + 3, the
   // keys its P^T registers hold. Each transposed read of a 16-lane group
   // covers 4 key rows x 16 channels; lane j addresses row j / 4, channels
-  // 4 (j % 4) .. + 3 of it and receives channel j of all four rows.
-  auto vt_frag = [&](int db) __attribute__((always_inline)) {
-    const lds_char_t *base = (const lds_char_t *)vt;
-    i16x4 part[2];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int row = 16 * h + 4 * bq + (j >> 2);
-      const int col = 16 * db + 4 * (j & 3);
-      const int off = row * (D * 2) + (((col >> 3) ^ swz<D>(row)) << 4) + ((col >> 2) & 1) * 8;
-      part[h] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)(base + off));
-    }
+  // 4 (j % 4) .. + 3 of it and receives channel j of all four rows. Channel
+  // block db moves the chunk index by an XOR with 2 db, and rows 16 apart
+  // share their swizzle.
+  const int vrow = 4 * bq + (j >> 2);
+  const int tbase = vrow * (D * 2) + ((((j & 3) >> 1) ^ swz<D>(vrow)) << 4) + (j & 1) * 8;
+  auto vt_frag = [&](int t0, int db) __attribute__((always_inline)) {
+    const lds_char_t *base = (const lds_char_t *)vt + (t0 ^ (db << 5));
+    const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)base);
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4_t *)(base + 16 * D * 2));
     typedef short i16x8 __attribute__((ext_vector_type(8)));
-    return __builtin_bit_cast(bf16x8, (i16x8)__builtin_shufflevector(part[0], part[1], 0, 1, 2, 3, 4, 5, 6, 7));
+    return __builtin_bit_cast(bf16x8, (i16x8)__builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
   };
 
-  float m_run = -INFINITY, l_run = 0.0f;
-  f32x4 oacc[NDB];
+  float m_run[NB], l_run[NB];
+  f32x4 oacc[NB][NDB];
 #pragma unroll
-  for (int db = 0; db < NDB; ++db) oacc[db] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  for (int rb = 0; rb < NB; ++rb) {
+    m_run[rb] = -INFINITY;
+    l_run[rb] = 0.0f;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) oacc[rb][db] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  }
 
   auto compute = [&](int tile, const bf16x8 (&kr)[2 * NQ]) __attribute__((always_inline)) {
     const int key0 = tile * kDecTile;
-    // S^T: register e of score block kb of lane (j, bq) is key 16 kb + 4 bq + e, row j.
-    f32x4 s[2];
+    bf16x8 pf[NB];
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-      s[kb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int rb = 0; rb < NB; ++rb) {
+      // S^T: register e of score block kb of lane (j, bq) is key 16 kb + 4 bq + e, row j.
+      f32x4 s[2];
 #pragma unroll
-      for (int st = 0; st < NQ; ++st) s[kb] = mfma16(kr[kb * NQ + st], qf[st], s[kb]);
-    }
-    if (key0 + kDecTile - 1 > kv_len - rq.n) {
-      const int lim = my_lim - key0 - 4 * bq;
+      for (int kb = 0; kb < 2; ++kb) {
+        s[kb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int st = 0; st < NQ; ++st) s[kb] = mfma16(kr[kb * NQ + st], qf[rb][st], s[kb]);
+      }
+      if (key0 + kDecTile - 1 > kv_len - rq.n) {
+        const int lim = my_lim[rb] - key0 - 4 * bq;
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) s[kb][e] = 16 * kb + e <= lim ? s[kb][e] : -INFINITY;
+      }
+      float mx = -INFINITY;
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) s[kb][e] = 16 * kb + e <= lim ? s[kb][e] : -INFINITY;
+        for (int e = 0; e < 4; ++e) mx = fmaxf(mx, s[kb][e]);
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c;
+      const float m_new = fmaxf(m_run[rb], mx);
+      const float mu = m_new == -INFINITY ? 0.0f : m_new;
+      const float alpha = fast_exp2(m_run[rb] - mu);
+      float ls = 0.0f;
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float pv = fast_exp2(fmaf(s[kb][e], c, -mu));
+          ls += pv;
+          pf[rb][4 * kb + e] = (__bf16)pv;
+        }
+      l_run[rb] = l_run[rb] * alpha + ls;
+      m_run[rb] = m_new;
+#pragma unroll
+      for (int db = 0; db < NDB; ++db) oacc[rb][db] *= alpha;
     }
-    float mx = -INFINITY;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) mx = fmaxf(mx, s[kb][e]);
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64)) * c;
-    const float m_new = fmaxf(m_run, mx);
-    const float mu = m_new == -INFINITY ? 0.0f : m_new;
-    const float alpha = fast_exp2(m_run - mu);
-    float ls = 0.0f;
-    bf16x8 pf;
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const float pv = fast_exp2(fmaf(s[kb][e], c, -mu));
-        ls += pv;
-        pf[4 * kb + e] = (__bf16)pv;
-      }
-    l_run = l_run * alpha + ls;
-    m_run = m_new;
+    int t0 = tbase;
+    asm volatile("" : "+v"(t0));
 #pragma unroll
     for (int db = 0; db < NDB; ++db) {
-      oacc[db] *= alpha;
-      oacc[db] = mfma16(vt_frag(db), pf, oacc[db]);
+      const bf16x8 vf = vt_frag(t0, db);
+#pragma unroll
+      for (int rb = 0; rb < NB; ++rb) oacc[rb][db] = mfma16(vf, pf[rb], oacc[rb][db]);
     }
   };
 
-  // Tiles tile0 + wave, + 4, ...: the K and V loads of the wave's next tile
-  // go out before this tile's V is written to LDS and its products run;
-  // the page ids come one tile earlier still.
-  bf16x8 kra[2 * NQ], krb[2 * NQ], vra[NI], vrb[NI];
+  // Tiles tile0 + wave, + 4, ...: the K loads of the wave's next tile go out
+  // before this tile's V is written to LDS, its V loads right after (into the
+  // registers that the write has just read), and both are in flight while
+  // this tile's products run; the page ids come one tile earlier still.
+  bf16x8 kra[2 * NQ], krb[2 * NQ], vr[NI];
   int t = w.tile0 + wave;
   TilePages next{};
   if (t < w.tile1) {
     const TilePages tp = tile_pages(t);
     load_k(t, tp, kra);
-    load_v(t, tp, vra);
+    load_v(t, tp, vr);
     next = tile_pages(t + kDecWaves);
   }
-  auto step = [&](int tile, bf16x8 (&kc)[2 * NQ], bf16x8 (&vc)[NI], bf16x8 (&kn)[2 * NQ], bf16x8 (&vn)[NI])
-                  __attribute__((always_inline)) {
+  auto step = [&](int tile, bf16x8 (&kc)[2 * NQ], bf16x8 (&kn)[2 * NQ]) __attribute__((always_inline)) {
     const int tn = tile + kDecWaves;
-    if (tn < w.tile1) {
-      const TilePages pn = next;
-      load_k(tn, pn, kn);
-      load_v(tn, pn, vn);
+    const bool more = tn < w.tile1;
+    const TilePages pn = next;
+    if (more) load_k(tn, pn, kn);
+    write_v(vr);
+    if (more) {
+      load_v(tn, pn, vr);
       next = tile_pages(tn + kDecWaves);
     }
-    write_v(tile, vc);
     compute(tile, kc);
   };
   for (; t < w.tile1; t += 2 * kDecWaves) {
-    step(t, kra, vra, krb, vrb);
+    step(t, kra, krb);
     if (t + kDecWaves >= w.tile1) break;
-    step(t + kDecWaves, krb, vrb, kra, vra);
+    step(t + kDecWaves, krb, kra);
   }
 
-  // Combine the four waves' partial softmax states. Per wave: O^T
-  // [db][e][lane] in its V tile, m and the row sum of l per lane in ml.
-  const float l_row = l_run + __shfl_xor(l_run, 16, 64);
-  const float l_all = l_row + __shfl_xor(l_row, 32, 64);
-  __syncthreads();   // every wave is done with its V tile
-  float *const mine = reinterpret_cast<float *>(vt);
+  // Combine the four waves' partial softmax states, one row block after the
+  // other. Per wave: O^T [db][e][lane] in its V tile, m and the row sum of l
+  // per lane in ml.
 #pragma unroll
-  for (int db = 0; db < NDB; ++db)
+  for (int rb = 0; rb < NB; ++rb) {
+    const float l_row = l_run[rb] + __shfl_xor(l_run[rb], 16, 64);
+    const float l_all = l_row + __shfl_xor(l_row, 32, 64);
+    __syncthreads();   // every wave is done with its V tile (or the block before)
+    float *const mine = reinterpret_cast<float *>(vt);
+    float *const mlb = ml + rb * kDecWaves * 128;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) mine[(db * 4 + e) * 64 + lane] = oacc[db][e];
-  ml[wave * 128 + lane] = m_run;
-  ml[wave * 128 + 64 + lane] = l_all;
-  __syncthreads();
-  if (!row_ok) return;
-  float M = -INFINITY;
+    for (int db = 0; db < NDB; ++db)
 #pragma unroll
-  for (int v = 0; v < kDecWaves; ++v) M = fmaxf(M, ml[v * 128 + lane]);
-  float wv[kDecWaves];
-  float L = 0.0f;
-#pragma unroll
-  for (int v = 0; v < kDecWaves; ++v) {
-    const float mv = ml[v * 128 + lane];
-    wv[v] = (M == -INFINITY || mv == -INFINITY) ? 0.0f : fast_exp2(mv - M);
-    L += wv[v] * ml[v * 128 + 64 + lane];
-  }
-  const int64_t R = (int64_t)(rq.q0 + my_i) * Hq + my_h;   // row of q, o and the partial planes
-  const float inv = L > 0.0f ? 1.0f / L : 0.0f;
-  // Wave v stores channel blocks v, v + 4, ...: lane (j, bq) channels
-  // 16 db + 4 bq .. + 3 of row j.
-  for (int db = wave; db < NDB; db += kDecWaves) {
-    f32x4 o = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int v = 0; v < kDecWaves; ++v) {
-      const float *ov = reinterpret_cast<const float *>(vs + v * TB);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) o[e] += wv[v] * ov[(db * 4 + e) * 64 + lane];
-    }
-    const int ch = 16 * db + 4 * bq;
-    if (w.split < 0)
-      store4((__bf16 *)p.o + R * D + ch, o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
-    else
-      store4(p.part_o + (w.split * p.plane + R) * D + ch, o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
-  }
-  if (wave == 0 && bq == 0) {
-    const float lse = L > 0.0f ? (M + log2f(L)) * kLn2 : -INFINITY;
-    if (w.split < 0) {
-      if (p.lse != nullptr) p.lse[(int64_t)my_h * p.Tq + rq.q0 + my_i] = lse;
-    } else {
-      p.part_lse[w.split * p.plane + R] = lse;
+      for (int e = 0; e < 4; ++e) mine[(db * 4 + e) * 64 + lane] = oacc[rb][db][e];
+    mlb[wave * 128 + lane] = m_run[rb];
+    mlb[wave * 128 + 64 + lane] = l_all;
+    __syncthreads();
+    if (row_ok[rb]) {
+      float M = -INFINITY;
+  #pragma unroll
+      for (int v = 0; v < kDecWaves; ++v) M = fmaxf(M, mlb[v * 128 + lane]);
+      float wv[kDecWaves];
+      float L = 0.0f;
+  #pragma unroll
+      for (int v = 0; v < kDecWaves; ++v) {
+        const float mv = mlb[v * 128 + lane];
+        wv[v] = (M == -INFINITY || mv == -INFINITY) ? 0.0f : fast_exp2(mv - M);
+        L += wv[v] * mlb[v * 128 + 64 + lane];
+      }
+      const int64_t R = (int64_t)(rq.q0 + my_i[rb]) * Hq + my_h[rb];   // row of q, o and the partial planes
+      const float inv = L > 0.0f ? 1.0f / L : 0.0f;
+      // Wave v stores channel blocks v, v + 4, ...: lane (j, bq) channels
+      // 16 db + 4 bq .. + 3 of row j.
+      for (int db = wave; db < NDB; db += kDecWaves) {
+        f32x4 o = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  #pragma unroll
+        for (int v = 0; v < kDecWaves; ++v) {
+          const float *ov = reinterpret_cast<const float *>(vs + v * TB);
+  #pragma unroll
+          for (int e = 0; e < 4; ++e) o[e] += wv[v] * ov[(db * 4 + e) * 64 + lane];
+        }
+        const int ch = 16 * db + 4 * bq;
+        if (w.split < 0)
+          store4((__bf16 *)p.o + R * D + ch, o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+        else
+          store4(p.part_o + (w.split * p.plane + R) * D + ch, o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+      }
+      if (wave == 0 && bq == 0) {
+        const float lse = L > 0.0f ? (M + log2f(L)) * kLn2 : -INFINITY;
+        if (w.split < 0) {
+          if (p.lse != nullptr) p.lse[(int64_t)my_h[rb] * p.Tq + rq.q0 + my_i[rb]] = lse;
+        } else {
+          p.part_lse[w.split * p.plane + R] = lse;
+        }
+      }
     }
   }
 }
@@ -315,11 +366,15 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams p) {
 
 }  // namespace
 
-hipError_t launch_decode_bf16(const DecodeParams &p, int D, int n_work, hipStream_t s) {
-  if (D == 64)
-    hipLaunchKernelGGL(decode_bf16_kernel<64>, dim3((unsigned)n_work), dim3(kDecWaves * 64), 0, s, p);
-  else
-    hipLaunchKernelGGL(decode_bf16_kernel<128>, dim3((unsigned)n_work), dim3(kDecWaves * 64), 0, s, p);
+hipError_t launch_decode_bf16(const DecodeParams &p, int D, int n_work, int row_blocks, hipStream_t s) {
+  const dim3 grid((unsigned)n_work), wg(kDecWaves * 64);
+  if (D == 64) {
+    if (row_blocks == 1) hipLaunchKernelGGL((decode_bf16_kernel<64, 1>), grid, wg, 0, s, p);
+    else hipLaunchKernelGGL((decode_bf16_kernel<64, 2>), grid, wg, 0, s, p);
+  } else {
+    if (row_blocks == 1) hipLaunchKernelGGL((decode_bf16_kernel<128, 1>), grid, wg, 0, s, p);
+    else hipLaunchKernelGGL((decode_bf16_kernel<128, 2>), grid, wg, 0, s, p);
+  }
   return hipGetLastError();
 }
 

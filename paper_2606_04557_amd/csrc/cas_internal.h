@@ -238,8 +238,9 @@ struct AdamParams {
 
 // Paged decode: one request (its queries are tokens q0 .. q0+n-1; its keys
 // the pages page_ids[page0 ..] in order, kv_len of them) and one workgroup's
-// share: packed rows row0 .. row0+15 (row r = query r / g, head kvh*g + r % g)
-// over 32-key tiles [tile0, tile1) of the request's key axis.
+// share: packed rows row0 .. row0+15 (or +31, see DecodePlan; row r = query
+// r / g, head kvh*g + r % g) over 32-key tiles [tile0, tile1) of the
+// request's key axis.
 constexpr int kDecTile = 32;
 constexpr int kDecRows = 16;
 struct DevDecodeReq {
@@ -304,7 +305,7 @@ hipError_t launch_dq_bf16(const DqParams &p, int D, hipStream_t s);
 hipError_t launch_dkdv_bf16(const DkdvParams &p, int D, int n_wg, hipStream_t s);
 hipError_t launch_bwd_prologue_bf16(const PreParams &p, int D, hipStream_t s);
 hipError_t launch_adam_bf16(const AdamParams &p, int D, int n_chunks, hipStream_t s);
-hipError_t launch_decode_bf16(const DecodeParams &p, int D, int n_work, hipStream_t s);
+hipError_t launch_decode_bf16(const DecodeParams &p, int D, int n_work, int row_blocks, hipStream_t s);
 hipError_t launch_decode_merge_bf16(const DecodeParams &p, int D, hipStream_t s);
 
 }  // namespace cas

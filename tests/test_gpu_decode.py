@@ -84,6 +84,20 @@ def test_decode_small(case):
     _run(kp, vp, kl, qc, pages, c["Hkv"], c["g"], c["D"], 950 + len(c["name"]))
 
 
+@pytest.mark.parametrize("D,P,g", [(128, 16, 1), (64, 32, 1), (128, 64, 3)])
+def test_decode_row_block_edges(D, P, g):
+    """Row counts n * g around the edges of the 16- and 32-row blocks of one
+    workgroup (and key counts around the 32-key tiles), mixed in one call with
+    a one-token request; then each count alone, where the block size is chosen
+    for it."""
+    counts = [n for n in (1, 5, 6, 10, 11, 15, 16, 17, 21, 31, 32, 33, 49) if n * g <= 100]
+    reqs = [([i % 3], max(n, 1 + 31 * (i % 4)), n) for i, n in enumerate(counts)]
+    kp, vp, kl, qc, pages = _pool(1200 + D + g, 3, 4, P, 2, D, reqs, own_extra=1)
+    _run(kp, vp, kl, qc, pages, 2, g, D, 1210 + g)
+    for i in (0, 6, 7, len(counts) - 1):
+        _run(kp, vp, kl[i:i + 1], qc[i:i + 1], pages[i:i + 1], 2, g, D, 1220 + i)
+
+
 def test_decode_retrieval_mix_full_size():
     """Cartridge-RAG decode step at full size: a pool of 256 cartridges of 1,024
     tokens (16,384 pages of 16 tokens, 8 KV heads x 128); 64 requests, each over
