@@ -885,12 +885,12 @@ struct DecodePlan {
   int Tq = 0, Hq = 0;
   std::vector<DevDecodeReq> reqs;
   std::vector<DevDecodeWork> work;
-  std::vector<int32_t> tok_req;
+  std::vector<int32_t> tok_nsplit;
   int max_split = 1;
   // 16-row blocks of one workgroup: 2 when a request has more than 16 packed
   // rows, so that those share one pass over the request's K and V.
   int row_blocks = 1;
-  size_t off_work = 0, off_pages = 0, off_tokreq = 0, off_plse = 0, off_po = 0, bytes = 0;
+  size_t off_work = 0, off_pages = 0, off_toksplit = 0, off_plse = 0, off_po = 0, bytes = 0;
 };
 
 cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
@@ -942,7 +942,7 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
   }
   const int64_t per_wg = std::max<int64_t>(8, ceil_div(total, 2 * (int64_t)device_topology().cus));
   dp.reqs.resize(B);
-  dp.tok_req.resize(Tq);
+  dp.tok_nsplit.resize(Tq);
   struct W {
     int64_t tiles;
     DevDecodeWork w;
@@ -957,9 +957,8 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
     r.n = n;
     r.kv_len = p->kv_lens[b];
     r.page0 = p->page_offsets[b];
-    r.nsplit = ns;
     dp.max_split = std::max(dp.max_split, ns);
-    for (int t = 0; t < n; ++t) dp.tok_req[r.q0 + t] = b;
+    for (int t = 0; t < n; ++t) dp.tok_nsplit[r.q0 + t] = ns;
     for (int kvh = 0; kvh < Hkv; ++kvh)
       for (int row0 = 0; row0 < n * g; row0 += rows_per_wg)
         for (int s = 0; s < ns; ++s) {
@@ -983,7 +982,7 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
   off = align_up(off + dp.work.size() * sizeof(DevDecodeWork), 256);
   dp.off_pages = off;
   off = align_up(off + (size_t)p->page_offsets[B] * sizeof(int32_t), 256);
-  dp.off_tokreq = off;
+  dp.off_toksplit = off;
   off = align_up(off + (size_t)Tq * sizeof(int32_t), 256);
   const size_t table_end = off;
   if (dp.max_split > 1) {
@@ -1207,7 +1206,7 @@ cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, 
     std::memcpy(h, dp.reqs.data(), dp.reqs.size() * sizeof(DevDecodeReq));
     std::memcpy(h + dp.off_work, dp.work.data(), dp.work.size() * sizeof(DevDecodeWork));
     if (npage_ids) std::memcpy(h + dp.off_pages, p->page_ids, (size_t)npage_ids * sizeof(int32_t));
-    std::memcpy(h + dp.off_tokreq, dp.tok_req.data(), dp.tok_req.size() * sizeof(int32_t));
+    std::memcpy(h + dp.off_toksplit, dp.tok_nsplit.data(), dp.tok_nsplit.size() * sizeof(int32_t));
   });
   if (s != CAS_OK) return s;
   DecodeParams kp{};
@@ -1219,7 +1218,7 @@ cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, 
   kp.reqs = (const DevDecodeReq *)ws;
   kp.work = (const DevDecodeWork *)(ws + dp.off_work);
   kp.page_ids = (const int32_t *)(ws + dp.off_pages);
-  kp.tok_req = (const int32_t *)(ws + dp.off_tokreq);
+  kp.tok_nsplit = (const int32_t *)(ws + dp.off_toksplit);
   kp.part_lse = dp.max_split > 1 ? (float *)(ws + dp.off_plse) : nullptr;
   kp.part_o = dp.max_split > 1 ? (float *)(ws + dp.off_po) : nullptr;
   kp.plane = (int64_t)dp.Tq * dp.Hq;
@@ -1231,7 +1230,7 @@ cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, 
   hipError_t e = timed("decode", stream, [&] { return launch_decode_bf16(kp, p->head_dim, (int)dp.work.size(), dp.row_blocks, stream); });
   if (e != hipSuccess) return hip_fail("decode launch", e);
   if (dp.max_split > 1) {
-    e = timed("decode_merge", stream, [&] { return launch_decode_merge_bf16(kp, p->head_dim, stream); });
+    e = timed("decode_merge", stream, [&] { return launch_decode_merge_bf16(kp, p->head_dim, dp.max_split, stream); });
     if (e != hipSuccess) return hip_fail("decode_merge launch", e);
   }
   return CAS_OK;

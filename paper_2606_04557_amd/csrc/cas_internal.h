@@ -245,8 +245,6 @@ constexpr int kDecTile = 32;
 constexpr int kDecRows = 16;
 struct DevDecodeReq {
   int32_t q0, n, kv_len, page0;
-  int32_t nsplit;        // key-axis splits of every row block of the request
-  int32_t pad_[3];
 };
 struct DevDecodeWork {
   int32_t b, kvh, row0, split;   // split index, or -1 when the range is the whole axis
@@ -263,7 +261,7 @@ struct DecodeParams {
   const DevDecodeReq *reqs;
   const DevDecodeWork *work;
   const int32_t *page_ids;
-  const int32_t *tok_req; // [Tq] request of each query token (merge)
+  const int32_t *tok_nsplit; // [Tq] key-axis splits of each query token's request (merge)
   float *part_o;          // [split][Tq * Hq][D] when a request is split
   float *part_lse;        // [split][Tq * Hq]
   int64_t plane;          // Tq * Hq
@@ -306,6 +304,6 @@ hipError_t launch_dkdv_bf16(const DkdvParams &p, int D, int n_wg, hipStream_t s)
 hipError_t launch_bwd_prologue_bf16(const PreParams &p, int D, hipStream_t s);
 hipError_t launch_adam_bf16(const AdamParams &p, int D, int n_chunks, hipStream_t s);
 hipError_t launch_decode_bf16(const DecodeParams &p, int D, int n_work, int row_blocks, hipStream_t s);
-hipError_t launch_decode_merge_bf16(const DecodeParams &p, int D, hipStream_t s);
+hipError_t launch_decode_merge_bf16(const DecodeParams &p, int D, int max_split, hipStream_t s);
 
 }  // namespace cas

@@ -98,6 +98,17 @@ def test_decode_row_block_edges(D, P, g):
         _run(kp, vp, kl[i:i + 1], qc[i:i + 1], pages[i:i + 1], 2, g, D, 1220 + i)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("keys", [255, 257, 700, 2030, 2100, 4097, 4400])
+def test_decode_split_merge(D, keys):
+    """One request alone: the key axis in 1 to 18 splits (8 tiles of 32 keys
+    each), around the split counts at which the merge shares a row between
+    more lane groups; a second, unsplit request in the same call."""
+    reqs = [([], keys, 1), ([], 9, 1)]
+    kp, vp, kl, qc, pages = _pool(1300 + keys, 0, 0, 16, 2, D, reqs)
+    _run(kp, vp, kl, qc, pages, 2, 4, D, 1301)
+
+
 def test_decode_retrieval_mix_full_size():
     """Cartridge-RAG decode step at full size: a pool of 256 cartridges of 1,024
     tokens (16,384 pages of 16 tokens, 8 KV heads x 128); 64 requests, each over
