@@ -114,7 +114,7 @@ struct Plan {
   size_t off_segs = 0, off_rows = 0, off_tiles = 0, off_items = 0, off_carts = 0, off_uses = 0, off_order = 0,
          off_queues = 0, off_claim = 0,
          table_bytes = 0;
-  size_t off_part_o = 0, off_part_lse = 0, off_ovf = 0, ws_fwd = 0;
+  size_t off_part_o = 0, off_part_lse = 0, ws_fwd = 0;
   size_t off_nd = 0, off_lse2 = 0, off_part_dq = 0, off_qT = 0, off_doT = 0, ws_bwd = 0;
 };
 
@@ -480,11 +480,6 @@ cas_status_t build_plan(const cas_problem_t *p, bool bwd, Plan &pl, int fwd_spli
       off = align_up(off + (size_t)pl.fwd_splits * plane * D * 4, 256);
       pl.off_part_lse = off;
       off = align_up(off + (size_t)pl.fwd_splits * plane * 4, 256);
-    }
-    if (pl.dt == kBF16) {
-      // Per-workgroup flags of the exact (online-softmax) pass.
-      pl.off_ovf = off;
-      off = align_up(off + (size_t)pl.B * Hkv * pl.nqblk_fwd * pl.fwd_splits * 4, 256);
     }
     pl.ws_fwd = off;
   } else {
@@ -1042,7 +1037,7 @@ cas_status_t prefix_attn_fwd_run(const cas_problem_t *p, const void *q, const vo
     // The workspace is the fixed scratch: fewer key-axis splits (smaller
     // partials) until it fits. Only the rounding order of the merge changes.
     while (pl.ws_fwd > ws_bytes && pl.fwd_splits > 1) {
-      // Bytes per split (partials and flags) from this plan; the rebuilt
+      // Bytes per split (partials) from this plan; the rebuilt
       // plan is checked again since each region is rounded up to 256 bytes.
       const size_t per_split = (pl.ws_fwd - pl.table_bytes) / (size_t)pl.fwd_splits;
       const size_t room = ws_bytes > pl.table_bytes ? ws_bytes - pl.table_bytes : 0;
@@ -1109,7 +1104,6 @@ cas_status_t prefix_attn_fwd_run(const cas_problem_t *p, const void *q, const vo
   fp.rows = (const DevRow *)(ws + pl.off_rows);
   fp.tiles = (const DevTile *)(ws + pl.off_tiles);
   fp.items = (const DevItem *)(ws + pl.off_items);
-  fp.ovf_flag = pl.dt == kBF16 ? (int32_t *)(ws + pl.off_ovf) : nullptr;
   fp.plane = pl.T * pl.Hq;
   fp.B = pl.B;
   fp.Smax = pl.Smax;

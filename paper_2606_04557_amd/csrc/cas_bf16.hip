@@ -198,12 +198,13 @@ struct TileTable {
 // moved, so O is never rescaled in the loop and later tiles need no maximum.
 // Later scores may exceed m: while the row sum stays below 2^kRefMargin every
 // P, every partial sum and O stay far inside fp32 and bf16 range. A row whose
-// sum reaches it (or overflows) flags its workgroup, and a second launch
-// (FIXUP) recomputes only the flagged workgroups with the exact online
-// softmax (running maximum, O and the sum rescaled at every tile). Unflagged
-// workgroups of the second launch exit at once.
+// sum reaches it (or overflows) sends its workgroup through the tiles again
+// with the exact online softmax (running maximum, O and the sum rescaled at
+// every tile). As a second launch of flagged workgroups, which mostly exit at
+// once, the exact pass cost every call 4.0-4.8 us; inside the kernel it costs
+// one workgroup vote.
 // ---------------------------------------------------------------------------
-template <int D, bool FIXUP>
+template <int D>
 __global__ __launch_bounds__(kFastThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void fwd_bf16_kernel(FwdParams p) {
   constexpr int NSTEP = D / 16;
@@ -232,9 +233,6 @@ void fwd_bf16_kernel(FwdParams p) {
   const int nrows = __builtin_amdgcn_readfirstlane(row.len) * g;
   const int wg_row0 = qblk * kFastRowsPerWg;
   if (wg_row0 >= nrows) return;   // (the host lists only blocks with rows)
-  if constexpr (FIXUP) {
-    if (load_const(p.ovf_flag, (int)blockIdx.x) == 0) return;
-  }
 
   const int wg_row1 = min(nrows, wg_row0 + kFastRowsPerWg);
   const int row0 = wg_row0 + wave * kFastRowsPerWave;
@@ -275,12 +273,9 @@ void fwd_bf16_kernel(FwdParams p) {
   wait_vmcnt<0>();
 
   f32x16 oacc[DT];
-#pragma unroll
-  for (int dt = 0; dt < DT; ++dt) oacc[dt] = zero16();
   // Exponent offset of this lane's row: fixed by its first visible tile, or
-  // (FIXUP) the running row maximum.
-  float m_run = -INFINITY;
-  float l_run = 0.0f;
+  // (exact pass) the running row maximum.
+  float m_run, l_run;
 
   // Group B's share of every tile copy (4 waves).
   CopyLanes<D, kKT, 4> cl;
@@ -289,264 +284,273 @@ void fwd_bf16_kernel(FwdParams p) {
   constexpr int kPieces = 2 * kCopyInst;                   // copy instructions per softmax phase
   static_assert(16 % kPieces == 0, "copy pieces spread over the 16 exponential pairs");
 
-  // Scores of the tile between its G and X phases; P of the tile between its
-  // X phase and the next G phase.
-  f32x16 s0 = zero16(), s1 = zero16();
-  bf16x8 pf[2][2];
+  // One pass over the split's tiles, with the exact online softmax or the
+  // fixed reference.
+  auto attend = [&](auto EXACT) __attribute__((always_inline)) {
+    constexpr bool kExact = decltype(EXACT)::value;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int dt = 0; dt < DT; ++dt) oacc[dt] = zero16();
+    m_run = -INFINITY;
+    l_run = 0.0f;
+    // Scores of the tile between its G and X phases; P of the tile between its
+    // X phase and the next G phase.
+    f32x16 s0 = zero16(), s1 = zero16();
+    bf16x8 pf[2][2];
 #pragma unroll
-    for (int s = 0; s < 2; ++s) pf[a][s] = Mma<__bf16>::zero();
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int s = 0; s < 2; ++s) pf[a][s] = Mma<__bf16>::zero();
 
-  // Local tile j: whether this wave sees any key of it (self tiles past the
-  // wave's last query position are skipped), and its mask data.
-  auto self0_of = [&](int j) __attribute__((always_inline)) {
-    return tb + j < ptiles ? -1 : (tb + j - ptiles) * kKT;
-  };
-  auto live = [&](int j) __attribute__((always_inline)) {
-    const int s0_ = self0_of(j);
-    return wave_active && !(s0_ >= 0 && s0_ > wave_t_hi);
-  };
+    // Local tile j: whether this wave sees any key of it (self tiles past the
+    // wave's last query position are skipped), and its mask data.
+    auto self0_of = [&](int j) __attribute__((always_inline)) {
+      return tb + j < ptiles ? -1 : (tb + j - ptiles) * kKT;
+    };
+    auto live = [&](int j) __attribute__((always_inline)) {
+      const int s0_ = self0_of(j);
+      return wave_active && !(s0_ >= 0 && s0_ > wave_t_hi);
+    };
 
-  // Matrix phase as one software-pipelined sequence of MFMAs: the PV product
-  // of the previous tile (16 MFMAs, two transposed LDS reads per fragment),
-  // then the scores of this one (16 MFMAs, one LDS read per fragment). The
-  // fragment of MFMA k+LEAD is read while MFMA k runs, into a ring of LEAD+1
-  // registers, and the scheduling groups pin exactly that order, so the LDS
-  // latency hides behind the MFMA pipe across the PV -> S boundary too.
-  auto matrix = [&](auto DO_PV, auto DO_S, const char *kb, const char *vb) __attribute__((always_inline)) {
-    constexpr bool PV = decltype(DO_PV)::value, S = decltype(DO_S)::value;
-    constexpr int NPV = PV ? 4 * DT : 0;          // PV MFMAs
-    constexpr int N = NPV + (S ? 2 * NSTEP : 0);  // all MFMAs
-    constexpr int LEAD = 4, R = LEAD + 1;
-    // MFMA k < NPV: s = k / (2*DT), dt = (k / 2) % DT, key half hh = k % 2.
-    // MFMA k >= NPV: st = (k - NPV) / 2, score half hh = (k - NPV) % 2.
-    auto load = [&](auto K) __attribute__((always_inline)) {
-      constexpr int k = decltype(K)::value;
-      if constexpr (k < NPV) {
-        constexpr int s = k / (2 * DT), dt = (k / 2) % DT, hh = k % 2;
-        return tr_frag_at<D>(vb, to, 32 * hh + 16 * s, dt);
-      } else {
-        constexpr int st = (k - NPV) / 2, hh = (k - NPV) % 2;
-        return row_frag_at<D>(kb, ro, 32 * hh, st);
+    // Matrix phase as one software-pipelined sequence of MFMAs: the PV product
+    // of the previous tile (16 MFMAs, two transposed LDS reads per fragment),
+    // then the scores of this one (16 MFMAs, one LDS read per fragment). The
+    // fragment of MFMA k+LEAD is read while MFMA k runs, into a ring of LEAD+1
+    // registers, and the scheduling groups pin exactly that order, so the LDS
+    // latency hides behind the MFMA pipe across the PV -> S boundary too.
+    auto matrix = [&](auto DO_PV, auto DO_S, const char *kb, const char *vb) __attribute__((always_inline)) {
+      constexpr bool PV = decltype(DO_PV)::value, S = decltype(DO_S)::value;
+      constexpr int NPV = PV ? 4 * DT : 0;          // PV MFMAs
+      constexpr int N = NPV + (S ? 2 * NSTEP : 0);  // all MFMAs
+      constexpr int LEAD = 4, R = LEAD + 1;
+      // MFMA k < NPV: s = k / (2*DT), dt = (k / 2) % DT, key half hh = k % 2.
+      // MFMA k >= NPV: st = (k - NPV) / 2, score half hh = (k - NPV) % 2.
+      auto load = [&](auto K) __attribute__((always_inline)) {
+        constexpr int k = decltype(K)::value;
+        if constexpr (k < NPV) {
+          constexpr int s = k / (2 * DT), dt = (k / 2) % DT, hh = k % 2;
+          return tr_frag_at<D>(vb, to, 32 * hh + 16 * s, dt);
+        } else {
+          constexpr int st = (k - NPV) / 2, hh = (k - NPV) % 2;
+          return row_frag_at<D>(kb, ro, 32 * hh, st);
+        }
+      };
+      auto mma = [&](auto K, const bf16x8 &f) __attribute__((always_inline)) {
+        constexpr int k = decltype(K)::value;
+        if constexpr (k < NPV) {
+          constexpr int s = k / (2 * DT), dt = (k / 2) % DT, hh = k % 2;
+          oacc[dt] = Mma<__bf16>::run(f, pf[hh][s], oacc[dt]);
+        } else {
+          constexpr int st = (k - NPV) / 2, hh = (k - NPV) % 2;
+          if constexpr (hh == 0) s0 = Mma<__bf16>::run(f, qf[st], s0);
+          else s1 = Mma<__bf16>::run(f, qf[st], s1);
+        }
+      };
+      if constexpr (S) {
+        s0 = zero16();
+        s1 = zero16();
       }
+      bf16x8 ring[R];
+      static_for<LEAD>([&](auto K) __attribute__((always_inline)) {
+        constexpr int k = decltype(K)::value;
+        if constexpr (k < N) ring[k % R] = load(K);
+      });
+      static_for<N>([&](auto K) __attribute__((always_inline)) {
+        constexpr int k = decltype(K)::value;
+        if constexpr (k + LEAD < N) ring[(k + LEAD) % R] = load(std::integral_constant<int, k + LEAD>{});
+        mma(K, ring[k % R]);
+      });
+      // Scheduling groups: the LEAD first fragments, then per MFMA k the reads
+      // of fragment k+LEAD.
+      static_for<LEAD>([&](auto K) __attribute__((always_inline)) {
+        constexpr int k = decltype(K)::value;
+        if constexpr (k < N) sched_ds_read<(k < NPV ? 2 : 1)>();
+      });
+      static_for<N>([&](auto K) __attribute__((always_inline)) {
+        constexpr int k = decltype(K)::value;
+        sched_mfma<1>();
+        if constexpr (k + LEAD < N) sched_ds_read<(k + LEAD < NPV ? 2 : 1)>();
+      });
     };
-    auto mma = [&](auto K, const bf16x8 &f) __attribute__((always_inline)) {
-      constexpr int k = decltype(K)::value;
-      if constexpr (k < NPV) {
-        constexpr int s = k / (2 * DT), dt = (k / 2) % DT, hh = k % 2;
-        oacc[dt] = Mma<__bf16>::run(f, pf[hh][s], oacc[dt]);
-      } else {
-        constexpr int st = (k - NPV) / 2, hh = (k - NPV) % 2;
-        if constexpr (hh == 0) s0 = Mma<__bf16>::run(f, qf[st], s0);
-        else s1 = Mma<__bf16>::run(f, qf[st], s1);
+    float alpha = 1.0f;   // exact pass: O rescale factor of the current tile
+    // piece(n), n < kPieces: copy instruction n of the phase (group B's tile
+    // copies), spread evenly over the exponentials.
+    auto softmax = [&](auto MASK, int lim, auto &&piece) __attribute__((always_inline)) {
+      if constexpr (decltype(MASK)::value) {
+        // lim: last visible key of this lane's query within the tile. Register
+        // j of group G holds key crow(j, G) = crow(j, 0) + 4G, so comparing
+        // lim - 4G against compile-time constants needs no index registers.
+        const int limg = lim - 4 * G;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+          s0[j] = crow(j, 0) <= limg ? s0[j] : -INFINITY;
+          s1[j] = 32 + crow(j, 0) <= limg ? s1[j] : -INFINITY;
+        }
       }
-    };
-    if constexpr (S) {
-      s0 = zero16();
-      s1 = zero16();
-    }
-    bf16x8 ring[R];
-    static_for<LEAD>([&](auto K) __attribute__((always_inline)) {
-      constexpr int k = decltype(K)::value;
-      if constexpr (k < N) ring[k % R] = load(K);
-    });
-    static_for<N>([&](auto K) __attribute__((always_inline)) {
-      constexpr int k = decltype(K)::value;
-      if constexpr (k + LEAD < N) ring[(k + LEAD) % R] = load(std::integral_constant<int, k + LEAD>{});
-      mma(K, ring[k % R]);
-    });
-    // Scheduling groups: the LEAD first fragments, then per MFMA k the reads
-    // of fragment k+LEAD.
-    static_for<LEAD>([&](auto K) __attribute__((always_inline)) {
-      constexpr int k = decltype(K)::value;
-      if constexpr (k < N) sched_ds_read<(k < NPV ? 2 : 1)>();
-    });
-    static_for<N>([&](auto K) __attribute__((always_inline)) {
-      constexpr int k = decltype(K)::value;
-      sched_mfma<1>();
-      if constexpr (k + LEAD < N) sched_ds_read<(k + LEAD < NPV ? 2 : 1)>();
-    });
-  };
-  float alpha = 1.0f;   // FIXUP: O rescale factor of the current tile
-  // piece(n), n < kPieces: copy instruction n of the phase (group B's tile
-  // copies), spread evenly over the exponentials.
-  auto softmax = [&](auto MASK, int lim, auto &&piece) __attribute__((always_inline)) {
-    if constexpr (decltype(MASK)::value) {
-      // lim: last visible key of this lane's query within the tile. Register
-      // j of group G holds key crow(j, G) = crow(j, 0) + 4G, so comparing
-      // lim - 4G against compile-time constants needs no index registers.
-      const int limg = lim - 4 * G;
+      auto tile_max = [&]() __attribute__((always_inline)) {
+        float mx = -INFINITY;
+#pragma unroll
+        for (int j = 0; j < 16; j += 2) mx = fmaxf(fmaxf(mx, fmaxf(s0[j], s1[j])), fmaxf(s0[j + 1], s1[j + 1]));
+        return fmaxf(mx, xor32(mx)) * c;
+      };
+      if constexpr (!kExact) {
+        // Only until every row of the wave has seen a key.
+        if (wave_any(m_run == -INFINITY)) {
+          const float mt = tile_max();
+          m_run = (m_run == -INFINITY) ? mt : m_run;
+        }
+      } else {
+        // Running maximum; the sum is rescaled here, O by the caller (outside
+        // its branches, so the accumulators are written in one place).
+        const float m_new = fmaxf(m_run, tile_max());
+        alpha = (m_new == -INFINITY) ? 1.0f : fast_exp2(m_run - m_new);
+        l_run *= alpha;
+        m_run = m_new;
+      }
+      const float mu = (m_run == -INFINITY) ? 0.0f : m_run;
 #pragma unroll
       for (int j = 0; j < 16; ++j) {
-        s0[j] = crow(j, 0) <= limg ? s0[j] : -INFINITY;
-        s1[j] = 32 + crow(j, 0) <= limg ? s1[j] : -INFINITY;
+        s0[j] = fast_exp2(fmaf(s0[j], c, -mu));
+        s1[j] = fast_exp2(fmaf(s1[j], c, -mu));
+        constexpr int EPP = 16 / kPieces;
+        if (j % EPP == EPP - 1) {
+          asm volatile("" : "+v"(s0[j]), "+v"(s1[j]));   // keep the copies spread
+          piece(j / EPP);
+        }
       }
-    }
-    auto tile_max = [&]() __attribute__((always_inline)) {
-      float mx = -INFINITY;
 #pragma unroll
-      for (int j = 0; j < 16; j += 2) mx = fmaxf(fmaxf(mx, fmaxf(s0[j], s1[j])), fmaxf(s0[j + 1], s1[j + 1]));
-      return fmaxf(mx, xor32(mx)) * c;
+      for (int s = 0; s < 2; ++s) {
+        pf[0][s] = pack_bf16x8(s0, s);
+        pf[1][s] = pack_bf16x8(s1, s);
+      }
+      // Row sums in fp32 (the LSE needs them to better than bf16 rounding).
+      float la = 0.0f, lb = 0.0f;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        la += s0[j];
+        lb += s1[j];
+      }
+      l_run += la + lb;
     };
-    if constexpr (!FIXUP) {
-      // Only until every row of the wave has seen a key.
-      if (wave_any(m_run == -INFINITY)) {
-        const float mt = tile_max();
-        m_run = (m_run == -INFINITY) ? mt : m_run;
-      }
-    } else {
-      // Running maximum; the sum is rescaled here, O by the caller (outside
-      // its branches, so the accumulators are written in one place).
-      const float m_new = fmaxf(m_run, tile_max());
-      alpha = (m_new == -INFINITY) ? 1.0f : fast_exp2(m_run - m_new);
-      l_run *= alpha;
-      m_run = m_new;
-    }
-    const float mu = (m_run == -INFINITY) ? 0.0f : m_run;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      s0[j] = fast_exp2(fmaf(s0[j], c, -mu));
-      s1[j] = fast_exp2(fmaf(s1[j], c, -mu));
-      constexpr int EPP = 16 / kPieces;
-      if (j % EPP == EPP - 1) {
-        asm volatile("" : "+v"(s0[j]), "+v"(s1[j]));   // keep the copies spread
-        piece(j / EPP);
-      }
-    }
-#pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      pf[0][s] = pack_bf16x8(s0, s);
-      pf[1][s] = pack_bf16x8(s1, s);
-    }
-    // Row sums in fp32 (the LSE needs them to better than bf16 rounding).
-    float la = 0.0f, lb = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      la += s0[j];
-      lb += s1[j];
-    }
-    l_run += la + lb;
-  };
 
-  // G_j: PV of tile j-1 (V_{j-1} in vbp) and scores of tile j (K_j in kb),
-  // always both: P is zero where there is no previous tile or it was not
-  // visible, and scores of a tile past the end or not visible are never
-  // read. (Conditionally skipping either half would make the register
-  // allocator copy the accumulators around every such branch.)
-  auto gphase = [&](int j, const char *kb, const char *vbp) __attribute__((always_inline)) {
-    if (j <= nt && wave_active) matrix(std::true_type{}, std::true_type{}, kb, vbp);
-  };
-  auto xphase_body = [&](int j, auto &&piece) __attribute__((always_inline)) {
-    auto all_pieces = [&]() __attribute__((always_inline)) {
-#pragma unroll
-      for (int n = 0; n < kPieces; ++n) piece(n);
+    // G_j: PV of tile j-1 (V_{j-1} in vbp) and scores of tile j (K_j in kb),
+    // always both: P is zero where there is no previous tile or it was not
+    // visible, and scores of a tile past the end or not visible are never
+    // read. (Conditionally skipping either half would make the register
+    // allocator copy the accumulators around every such branch.)
+    auto gphase = [&](int j, const char *kb, const char *vbp) __attribute__((always_inline)) {
+      if (j <= nt && wave_active) matrix(std::true_type{}, std::true_type{}, kb, vbp);
     };
-    if (j < 0 || j >= nt) {
-      all_pieces();
-      return;
-    }
-    if (!live(j)) {
+    auto xphase_body = [&](int j, auto &&piece) __attribute__((always_inline)) {
+      auto all_pieces = [&]() __attribute__((always_inline)) {
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+        for (int n = 0; n < kPieces; ++n) piece(n);
+      };
+      if (j < 0 || j >= nt) {
+        all_pieces();
+        return;
+      }
+      if (!live(j)) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) pf[a][s] = Mma<__bf16>::zero();
-      all_pieces();
-      return;
-    }
-    const int self0 = self0_of(j);
-    const int nvalid = __builtin_amdgcn_readfirstlane(tt.nvalid(tb + j));
-    if (nvalid < kKT || (self0 >= 0 && self0 + kKT - 1 > wave_t_lo)) {
-      const int lim = self0 < 0 ? nvalid - 1 : min(nvalid - 1, my_t - self0);
-      softmax(std::true_type{}, lim, piece);
-    } else {
-      softmax(std::false_type{}, kKT - 1, piece);
-    }
-  };
-  auto xphase = [&](int j, auto &&piece) __attribute__((always_inline)) {
-    if constexpr (FIXUP) alpha = 1.0f;
-    xphase_body(j, piece);
-    if constexpr (FIXUP) {
+        for (int a = 0; a < 2; ++a)
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) oacc[dt] *= alpha;
-    }
-  };
+          for (int s = 0; s < 2; ++s) pf[a][s] = Mma<__bf16>::zero();
+        all_pieces();
+        return;
+      }
+      const int self0 = self0_of(j);
+      const int nvalid = __builtin_amdgcn_readfirstlane(tt.nvalid(tb + j));
+      if (nvalid < kKT || (self0 >= 0 && self0 + kKT - 1 > wave_t_lo)) {
+        const int lim = self0 < 0 ? nvalid - 1 : min(nvalid - 1, my_t - self0);
+        softmax(std::true_type{}, lim, piece);
+      } else {
+        softmax(std::false_type{}, kKT - 1, piece);
+      }
+    };
+    auto xphase = [&](int j, auto &&piece) __attribute__((always_inline)) {
+      if constexpr (kExact) alpha = 1.0f;
+      xphase_body(j, piece);
+      if constexpr (kExact) {
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) oacc[dt] *= alpha;
+      }
+    };
 
-  // Group B's copies. tk: the K tile issued last (tile i+1 when phase 2i
-  // starts), whose V is issued next.
-  TileInfo tk;
-  auto copy_k = [&](char *kbn, int j) __attribute__((always_inline)) {
-    tk = tt.at(tb + j);
-    cl.issue(kbn, tk.kp, tk.st, tk.nvalid, wave & 3);
-  };
-  auto no_piece = [](int) {};
-  // Phase 2i: V_{i+1} and K_{i+2}, spread over the softmax of tile i-1 (copies
-  // past the last tile go through an empty resource and write zeros into
-  // buffers nothing reads); at its end the copies of phase 2i-2 are waited for.
-  auto even_b = [&](int i, char *kbn, char *vbn) __attribute__((always_inline)) {
-    const TileInfo tv = tk;                                   // tile i+1 (or the last)
-    const TileInfo tn = tt.at(tb + min(i + 2, nt - 1));
-    const BufRsrc rv = make_rsrc(tv.vp, i + 1 < nt ? ((tv.nvalid - 1) * tv.st + D) * 2 : 0);
-    const BufRsrc rk = make_rsrc(tn.kp, i + 2 < nt ? ((tn.nvalid - 1) * tn.st + D) * 2 : 0);
-    xphase(i - 1, [&](int n) __attribute__((always_inline)) {
-      if (n < kCopyInst) cl.issue_rs(vbn, rv, tv.st, tv.nvalid, wave & 3, n);
-      else cl.issue_rs(kbn, rk, tn.st, tn.nvalid, wave & 3, n - kCopyInst);
-    });
-    tk = tn;
-    wait_vmcnt<2 * kCopyInst>();
-  };
+    // Group B's copies. tk: the K tile issued last (tile i+1 when phase 2i
+    // starts), whose V is issued next.
+    TileInfo tk;
+    auto copy_k = [&](char *kbn, int j) __attribute__((always_inline)) {
+      tk = tt.at(tb + j);
+      cl.issue(kbn, tk.kp, tk.st, tk.nvalid, wave & 3);
+    };
+    auto no_piece = [](int) {};
+    // Phase 2i: V_{i+1} and K_{i+2}, spread over the softmax of tile i-1 (copies
+    // past the last tile go through an empty resource and write zeros into
+    // buffers nothing reads); at its end the copies of phase 2i-2 are waited for.
+    auto even_b = [&](int i, char *kbn, char *vbn) __attribute__((always_inline)) {
+      const TileInfo tv = tk;                                   // tile i+1 (or the last)
+      const TileInfo tn = tt.at(tb + min(i + 2, nt - 1));
+      const BufRsrc rv = make_rsrc(tv.vp, i + 1 < nt ? ((tv.nvalid - 1) * tv.st + D) * 2 : 0);
+      const BufRsrc rk = make_rsrc(tn.kp, i + 2 < nt ? ((tn.nvalid - 1) * tn.st + D) * 2 : 0);
+      xphase(i - 1, [&](int n) __attribute__((always_inline)) {
+        if (n < kCopyInst) cl.issue_rs(vbn, rv, tv.st, tv.nvalid, wave & 3, n);
+        else cl.issue_rs(kbn, rk, tn.st, tn.nvalid, wave & 3, n - kCopyInst);
+      });
+      tk = tn;
+      wait_vmcnt<2 * kCopyInst>();
+    };
 
-  if (nt > 0) {
-    // G_0 multiplies V buffer 2 by P = 0: clear it so no stale bit pattern
-    // (a NaN) can reach O.
-    for (int i = tid; i < TB / 16; i += kFastThreads) reinterpret_cast<uint4 *>(vb2)[i] = uint4{0, 0, 0, 0};
-    // Prologue (group B): K_0, then K_1 and V_0.
-    if (grp == 1) {
-      copy_k(kb0, 0);
+    if (nt > 0) {
+      // G_0 multiplies V buffer 2 by P = 0: clear it so no stale bit pattern
+      // (a NaN) can reach O.
+      for (int i = tid; i < TB / 16; i += kFastThreads) reinterpret_cast<uint4 *>(vb2)[i] = uint4{0, 0, 0, 0};
+      // Prologue (group B): K_0, then K_1 and V_0.
+      if (grp == 1) {
+        copy_k(kb0, 0);
+        wait_vmcnt<0>();
+        const TileInfo t0 = tk;
+        cl.issue(vb0, t0.vp, t0.st, t0.nvalid, wave & 3);
+        if (nt > 1) copy_k(kb1, 1);
+      }
+      lds_barrier();
+      // Six phases per iteration (three tiles), so every buffer is a fixed LDS
+      // address: G_i reads K_i from kb[i%3] and V_{i-1} from vb[(i-1)%3]; the
+      // copies of phase 2i go to kb[(i+2)%3] and vb[(i+1)%3]. Each group runs
+      // its own copy of the loop (straight-line phases); s_barrier pairs them.
+      auto run = [&](auto GROUP_A) __attribute__((always_inline)) {
+        constexpr bool A = decltype(GROUP_A)::value;
+        auto even = [&](int i, const char *kbi, const char *vbp, char *kbn, char *vbn) __attribute__((always_inline)) {
+          if constexpr (A) gphase(i, kbi, vbp);
+          else even_b(i, kbn, vbn);
+          lds_barrier();
+        };
+        auto odd = [&](int i, const char *kbi, const char *vbp) __attribute__((always_inline)) {
+          if constexpr (A) xphase(i, no_piece);
+          else gphase(i, kbi, vbp);
+          lds_barrier();
+        };
+        for (int i = 0; i <= nt; i += 3) {
+          even(i, kb0, vb2, kb2, vb1);
+          odd(i, kb0, vb2);
+          if (i + 1 > nt) break;
+          even(i + 1, kb1, vb0, kb0, vb2);
+          odd(i + 1, kb1, vb0);
+          if (i + 2 > nt) break;
+          even(i + 2, kb2, vb1, kb1, vb0);
+          odd(i + 2, kb2, vb1);
+        }
+      };
+      if (grp == 0) run(std::true_type{});
+      else run(std::false_type{});
       wait_vmcnt<0>();
-      const TileInfo t0 = tk;
-      cl.issue(vb0, t0.vp, t0.st, t0.nvalid, wave & 3);
-      if (nt > 1) copy_k(kb1, 1);
     }
-    lds_barrier();
-    // Six phases per iteration (three tiles), so every buffer is a fixed LDS
-    // address: G_i reads K_i from kb[i%3] and V_{i-1} from vb[(i-1)%3]; the
-    // copies of phase 2i go to kb[(i+2)%3] and vb[(i+1)%3]. Each group runs
-    // its own copy of the loop (straight-line phases); s_barrier pairs them.
-    auto run = [&](auto GROUP_A) __attribute__((always_inline)) {
-      constexpr bool A = decltype(GROUP_A)::value;
-      auto even = [&](int i, const char *kbi, const char *vbp, char *kbn, char *vbn) __attribute__((always_inline)) {
-        if constexpr (A) gphase(i, kbi, vbp);
-        else even_b(i, kbn, vbn);
-        lds_barrier();
-      };
-      auto odd = [&](int i, const char *kbi, const char *vbp) __attribute__((always_inline)) {
-        if constexpr (A) xphase(i, no_piece);
-        else gphase(i, kbi, vbp);
-        lds_barrier();
-      };
-      for (int i = 0; i <= nt; i += 3) {
-        even(i, kb0, vb2, kb2, vb1);
-        odd(i, kb0, vb2);
-        if (i + 1 > nt) break;
-        even(i + 1, kb1, vb0, kb0, vb2);
-        odd(i + 1, kb1, vb0);
-        if (i + 2 > nt) break;
-        even(i + 2, kb2, vb1, kb1, vb0);
-        odd(i + 2, kb2, vb1);
-      }
-    };
-    if (grp == 0) run(std::true_type{});
-    else run(std::false_type{});
-    wait_vmcnt<0>();
-  }
-  if constexpr (!FIXUP) {
-    // Every wave reaches this point: flag the workgroup if a row sum reached
-    // 2^kRefMargin or overflowed (exponent field also catches inf and NaN).
-    const unsigned eb = (__float_as_uint(l_run) >> 23) & 0xffu;
-    const int any = __syncthreads_or(eb >= 127u + (unsigned)kRefMargin ? 1 : 0);
-    if (tid == 0) p.ovf_flag[blockIdx.x] = any;
-  }
+  };
+
+  attend(std::false_type{});
+  // Every wave reaches this point: a row sum that reached 2^kRefMargin or
+  // overflowed (the exponent field also catches inf and NaN) sends the whole
+  // workgroup through the exact pass.
+  const unsigned eb = (__float_as_uint(l_run) >> 23) & 0xffu;
+  if (__syncthreads_or(eb >= 127u + (unsigned)kRefMargin ? 1 : 0)) attend(std::true_type{});
 
   const float lt = l_run + xor32(l_run);
   if (my_row >= nrows) return;
@@ -1655,11 +1659,9 @@ void dkdv_bf16_kernel(DkdvParams p) {
 hipError_t launch_fwd_bf16(const FwdParams &p, int D, hipStream_t s) {
   const int64_t grid = p.n_items;
   if (D == 64) {
-    hipLaunchKernelGGL((fwd_bf16_kernel<64, false>), dim3((unsigned)grid), dim3(kFastThreads), 0, s, p);
-    hipLaunchKernelGGL((fwd_bf16_kernel<64, true>), dim3((unsigned)grid), dim3(kFastThreads), 0, s, p);
+    hipLaunchKernelGGL(fwd_bf16_kernel<64>, dim3((unsigned)grid), dim3(kFastThreads), 0, s, p);
   } else {
-    hipLaunchKernelGGL((fwd_bf16_kernel<128, false>), dim3((unsigned)grid), dim3(kFastThreads), 0, s, p);
-    hipLaunchKernelGGL((fwd_bf16_kernel<128, true>), dim3((unsigned)grid), dim3(kFastThreads), 0, s, p);
+    hipLaunchKernelGGL(fwd_bf16_kernel<128>, dim3((unsigned)grid), dim3(kFastThreads), 0, s, p);
   }
   return hipGetLastError();
 }

@@ -120,7 +120,6 @@ struct FwdParams {
   const DevRow *rows;
   const DevTile *tiles;
   const DevItem *items;       // [n_items] bf16: workgroup i takes items[i]
-  int32_t *ovf_flag;  // [grid] bf16: workgroup needs the exact-maximum pass
   int64_t plane;      // T * Hq: rows of one split partial plane
   int32_t B, Smax, Hkv, g, nrows_max, nqblk, splits;
   int32_t lse_hs;     // lse head stride (q_len, or T for packed samples)

@@ -8,8 +8,8 @@
 #include "../../include/cas.h"
 #include "cas_internal.h"
 
-// Workspace of cas_prefix_attn_fwd_noalloc: launch tables, exact-pass flags
-// and split partials. Every GPU holds its own copy at its own address; host
+// Workspace of cas_prefix_attn_fwd_noalloc: launch tables and
+// split partials. Every GPU holds its own copy at its own address; host
 // code uses only the address hipGetSymbolAddress returns for the current
 // device (this name on the host is a stand-in, not a device address).
 static __device__ __align__(256) char scratch[CAS_NOALLOC_SCRATCH_BYTES];

@@ -189,6 +189,29 @@ def test_score_spike_takes_exact_pass(splits):
         assert rel_err(host(case.dv[cc]), rdv[cc]) <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_score_spike_in_one_workgroup(D):
+    """Several workgroups of 256 packed rows per (row, KV head), one spiking
+    key for one query of one of them: that workgroup alone repeats its tiles
+    with the exact online softmax; its other rows and the other workgroups
+    still match the oracle."""
+    wl = casgen.custom("spike", "bf16", batch=2, q_len=150, num_q_heads=8, num_kv_heads=2, head_dim=D,
+                       cart_lens=[130, 200], rows=[[0, 1], [1]], seed=306, cart_std=0.5)
+    T = casgen.make_tensors(wl)
+    q = casgen.to_float(T["q"], "bf16")
+    k = casgen.to_float(T["cart_k"][1], "bf16")
+    qv = q[0, 100, 0]
+    k[190, 0] = 60.0 * qv / np.linalg.norm(qv)
+    T["cart_k"][1] = casgen.rng.f64_to_bf16_bits(k)
+    assert 60.0 * float(np.linalg.norm(qv)) * float(wl.scale) / math.log(2) > 64 + 5   # the spiking query's score
+    case = GpuCase(wl, tensors=T)
+    o, lse = case.fwd()
+    _torch().cuda.synchronize()
+    O, LSE, _ = full_oracle(case, backward=False)
+    assert rel_err(host(o), O) <= TOL["bf16"]
+    assert float(np.abs(host(lse) - LSE).max()) <= 1e-3
+
+
 def test_order_invariance_and_concatenation():
     """Reordering a row's cartridges, or joining them into one cartridge, leaves O, LSE
     and dQ unchanged up to rounding and moves each cartridge's gradient with it."""
