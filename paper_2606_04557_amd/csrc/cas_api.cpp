@@ -99,20 +99,18 @@ struct Plan {
   std::vector<DevCart> carts;
   std::vector<int32_t> uses;
   std::vector<DevWg> order;       // dK/dV workgroups, longest first
-  std::vector<DevQueue> queues;   // bf16 dK/dV: per-XCD lists of `order` (empty: entry = workgroup id)
   int64_t dkdv_grid = 0;          // dK/dV workgroups launched
-  int self_tiles_max = 0;         // dK/dV self tiles of the longest row
+  int dkdv_lists = 1, dkdv_list_len = 0, dkdv_list_head = 0;   // bf16 (see DkdvParams)
   int64_t order_cap = 0;          // order entries with every self tile
   int64_t max_prefix = 0;
   int fwd_splits = 1, dq_splits = 1;
-  int xcds = 8;                   // XCDs of the device (workgroup order of the bf16 kernels)
+  int xcds = 8;                   // XCDs of the device (workgroup order)
   int cus = 256;                  // compute units of the device
   int nqblk_fwd = 0, nqblk_dq = 0;
-  int cart_tiles = 0;
   bool want_self_grad = false;
   // workspace layout
   size_t off_segs = 0, off_rows = 0, off_tiles = 0, off_items = 0, off_carts = 0, off_uses = 0, off_order = 0,
-         off_queues = 0, off_claim = 0,
+         off_claim = 0,
          table_bytes = 0;
   size_t off_part_o = 0, off_part_lse = 0, ws_fwd = 0;
   size_t off_nd = 0, off_lse2 = 0, off_part_dq = 0, off_qT = 0, off_doT = 0, ws_bwd = 0;
@@ -414,7 +412,6 @@ cas_status_t build_plan(const cas_problem_t *p, bool bwd, Plan &pl, int fwd_spli
       c.stride_tok = s.stride_tok;
       c.stride_head = s.stride_head;
       c.len = (int32_t)s.len;
-      c.tile_begin = (int32_t)tiles;
       c.use_begin = (int32_t)pl.uses.size();
       // Rows without queries add nothing and are left out.
       int64_t nblk = 0;
@@ -441,12 +438,10 @@ cas_status_t build_plan(const cas_problem_t *p, bool bwd, Plan &pl, int fwd_spli
         return fail(CAS_ERR_INVALID_ARGUMENT, "cartridge gradient layout overlaps itself");
     }
     if (tiles > INT32_MAX / 2) return fail(CAS_ERR_UNSUPPORTED, "too many key tiles");
-    pl.cart_tiles = (int)tiles;
-    pl.self_tiles_max = (int)ceil_div(pl.Smax, kDkdvKeyTile);
     int64_t self_tiles = 0;
     for (int b = 0; b < pl.B; ++b) self_tiles += ceil_div(pl.len[b], kDkdvKeyTile);
     pl.order_cap = (tiles + self_tiles) * Hkv;
-    if (tiles + (int64_t)pl.B * pl.self_tiles_max > INT32_MAX / 2 || pl.order_cap > INT32_MAX)
+    if (tiles + (int64_t)pl.B * ceil_div(pl.Smax, kDkdvKeyTile) > INT32_MAX / 2 || pl.order_cap > INT32_MAX)
       return fail(CAS_ERR_UNSUPPORTED, "too many key tiles");
   }
 
@@ -467,8 +462,6 @@ cas_status_t build_plan(const cas_problem_t *p, bool bwd, Plan &pl, int fwd_spli
     off = align_up(off + pl.uses.size() * sizeof(int32_t), 256);
     pl.off_order = off;
     off = align_up(off + (size_t)pl.order_cap * sizeof(DevWg), 256);
-    pl.off_queues = off;
-    off = align_up(off + (size_t)pl.xcds * sizeof(DevQueue), 256);
     pl.off_claim = off;   // claim counters: zero in every table upload
     off = align_up(off + (size_t)pl.xcds * sizeof(int32_t), 256);
   }
@@ -515,14 +508,16 @@ cas_status_t build_plan(const cas_problem_t *p, bool bwd, Plan &pl, int fwd_spli
 void build_dkdv_order(Plan &pl, bool with_self) {
   struct E {
     int64_t nblk;
-    int32_t tile, kvh, pos;   // pos: tile within its cartridge or the row's self keys
+    int32_t owner, pos, kvh;   // pos: tile within its cartridge or the row's self keys
+    DevWg wg() const { return {owner, pos, kvh}; }
   };
   std::vector<E> v;
   v.reserve((size_t)pl.order_cap);
-  for (const DevCart &c : pl.carts) {
+  for (size_t i = 0; i < pl.carts.size(); ++i) {
+    const DevCart &c = pl.carts[i];
     const int n = (int)ceil_div(c.len, kDkdvKeyTile);
     for (int kvh = 0; kvh < pl.Hkv; ++kvh)
-      for (int t = 0; t < n; ++t) v.push_back({c.nblk, c.tile_begin + t, kvh, t});
+      for (int t = 0; t < n; ++t) v.push_back({c.nblk, (int32_t)i, t, kvh});
   }
   if (with_self) {
     for (int b = 0; b < pl.B; ++b) {
@@ -530,56 +525,54 @@ void build_dkdv_order(Plan &pl, bool with_self) {
       const int n = (int)ceil_div(pl.len[b], kDkdvKeyTile);
       for (int kvh = 0; kvh < pl.Hkv; ++kvh)
         for (int j = 0; j < n; ++j)
-          v.push_back({nqb - ((int64_t)j * kDkdvKeyTile * pl.g) / kDkdvQBlock,
-                       pl.cart_tiles + b * pl.self_tiles_max + j, kvh, j});
+          v.push_back({nqb - ((int64_t)j * kDkdvKeyTile * pl.g) / kDkdvQBlock, -1 - b, j, kvh});
     }
   }
   std::stable_sort(v.begin(), v.end(), [](const E &a, const E &b) {
     if (a.nblk != b.nblk) return a.nblk > b.nblk;
     if (a.kvh != b.kvh) return a.kvh < b.kvh;
-    if (a.pos != b.pos) return a.pos < b.pos;
-    return a.tile < b.tile;
+    return a.pos < b.pos;   // (then cartridges, then rows, in order: the sort is stable)
   });
   pl.order.resize(v.size());
-  pl.queues.clear();
   pl.dkdv_grid = (int64_t)v.size();
   const int X = pl.xcds;
   if (v.empty()) return;
-  if (X > 1 && pl.Hkv % X == 0) {
-    // XCD-affine: workgroup i runs on XCD i % X (round-robin dispatch), and
-    // XCD x takes the entries of KV heads h with h % X == x, longest first.
-    // Every KV head has the same tiles, so the X lists are equally long; the
-    // query blocks of one (row, KV head) are then streamed by one XCD's L2.
-    std::vector<std::vector<E>> q(X);
-    for (const E &e : v) q[e.kvh % X].push_back(e);
-    const int64_t per_cu = std::max(1, pl.cus / X);   // CUs of one XCD
-    const int64_t cnt = (int64_t)q[0].size();
-    if (pl.dt == kBF16 && (int64_t)X * (cnt + per_cu) <= INT32_MAX) {
-      // Each XCD's list in one piece: a static head, taken by workgroup
-      // index, and a tail of its shortest entries (two rounds of the XCD's
-      // CUs, or an eighth of the list) claimed at run time, by the XCD's own
-      // workgroups first and then by XCDs that finished their own lists; one
-      // more round of workgroups per XCD is launched for that. XCDs run at
-      // different speeds (up to 4 % apart on one chip), so a fixed share per
-      // XCD ends with the slowest.
-      const int64_t tail = std::min(cnt, std::max(2 * per_cu, cnt / 8));
-      pl.queues.resize(X);
-      size_t at = 0;
-      for (int x = 0; x < X; ++x) {
-        pl.queues[x] = {(int32_t)at, (int32_t)cnt, (int32_t)(cnt - tail), 0};
-        for (const E &e : q[x]) pl.order[at++] = {e.tile, e.kvh};
-      }
-      pl.dkdv_grid = (int64_t)X * (cnt + per_cu);
-      return;
-    }
-    std::vector<size_t> next(X, 0);
+  if (pl.dt != kBF16) {
+    // fp32: workgroup i takes entry i. XCD-affine (as below) where the KV
+    // heads divide evenly.
+    const bool affine = X > 1 && pl.Hkv % X == 0;
+    std::vector<std::vector<E>> q(affine ? X : 1);
+    for (const E &e : v) q[affine ? e.kvh % X : 0].push_back(e);
+    std::vector<size_t> next(q.size(), 0);
     for (size_t i = 0; i < v.size(); ++i) {
-      const E &e = q[i % X][next[i % X]++];
-      pl.order[i] = {e.tile, e.kvh};
+      const E &e = q[i % q.size()][next[i % q.size()]++];
+      pl.order[i] = e.wg();
     }
     return;
   }
-  for (size_t i = 0; i < v.size(); ++i) pl.order[i] = {v[i].tile, v[i].kvh};
+  // bf16: one persistent workgroup per compute unit works through lists of
+  // entries, longest first. XCD-affine where the KV heads divide evenly:
+  // workgroup i runs on XCD i % X (round-robin dispatch) and starts on list
+  // i % X, the entries of KV heads h with h % X == i % X, so the query blocks
+  // of one (row, KV head) are streamed by one XCD's L2. Every KV head has the
+  // same tiles, so the lists are equally long. Otherwise one list for all.
+  // A workgroup claims its next entry when it has finished one, from its own
+  // list and then from those with work left: XCDs run at different speeds
+  // (up to 4 % apart on one chip), so a fixed share per XCD ends with the
+  // slowest, and a new workgroup per entry leaves its compute unit idle for
+  // 3-6 us between two of them.
+  const int L = X > 1 && pl.Hkv % X == 0 ? X : 1;
+  std::vector<std::vector<E>> q(L);
+  for (const E &e : v) q[e.kvh % L].push_back(e);
+  const int64_t cnt = (int64_t)q[0].size();
+  const int64_t wgs = std::min<int64_t>(cnt, std::max(1, pl.cus / L));   // workgroups of one list
+  pl.dkdv_lists = L;
+  pl.dkdv_list_len = (int)cnt;
+  pl.dkdv_list_head = (int)wgs;
+  size_t at = 0;
+  for (const std::vector<E> &l : q)
+    for (const E &e : l) pl.order[at++] = e.wg();
+  pl.dkdv_grid = L * wgs;
 }
 
 // Turns the self-tile offsets of the tile table into pointers.
@@ -699,8 +692,6 @@ void fill_tables(const Plan &pl, bool bwd, char *h) {
     if (!pl.carts.empty()) std::memcpy(h + pl.off_carts, pl.carts.data(), pl.carts.size() * sizeof(DevCart));
     if (!pl.uses.empty()) std::memcpy(h + pl.off_uses, pl.uses.data(), pl.uses.size() * sizeof(int32_t));
     if (!pl.order.empty()) std::memcpy(h + pl.off_order, pl.order.data(), pl.order.size() * sizeof(DevWg));
-    if (!pl.queues.empty())
-      std::memcpy(h + pl.off_queues, pl.queues.data(), pl.queues.size() * sizeof(DevQueue));
   }
 }
 
@@ -1440,12 +1431,10 @@ cas_status_t cas_prefix_attn_bwd(const cas_problem_t *p, const void *q, const vo
     kp.uses = (const int32_t *)(ws + pl.off_uses);
     kp.rows = pp.rows;
     kp.order = (const DevWg *)(ws + pl.off_order);
-    kp.queues = pl.queues.empty() ? nullptr : (const DevQueue *)(ws + pl.off_queues);
-    kp.claim = pl.queues.empty() ? nullptr : (int32_t *)(ws + pl.off_claim);
-    kp.xcds = pl.xcds;
-    kp.n_carts = (int32_t)pl.carts.size();
-    kp.cart_tiles = pl.cart_tiles;
-    kp.self_tiles = std::max(pl.self_tiles_max, 1);
+    kp.claim = (int32_t *)(ws + pl.off_claim);
+    kp.lists = pl.dkdv_lists;
+    kp.list_len = pl.dkdv_list_len;
+    kp.list_head = pl.dkdv_list_head;
     kp.B = pl.B;
     kp.Hkv = pl.Hkv;
     kp.g = pl.g;

@@ -106,42 +106,28 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-// The dK/dV order entry of this workgroup when the lists are per XCD
-// (DevQueue): workgroup j of XCD x takes entry j of the XCD's static head;
-// past the head, thread 0 claims the next tail entry with an atomic counter,
-// of its own XCD first, then of the XCD with the most unclaimed entries
-// left, and the workgroup reads it from LDS. -1: nothing left. Every tail
-// entry is claimed exactly once: each XCD launches at least as many tail
-// workgroups as its tail holds, and each tries its own tail first.
-__device__ __forceinline__ int dkdv_entry(const DkdvParams &p, int tid, int &slot) {
-  const int X = p.xcds;
-  const int x = (int)blockIdx.x % X, j = (int)blockIdx.x / X;
-  const DevQueue own = load_const(p.queues, x);
-  if (j < own.head) return own.off + j;
-  if (tid == 0) {
-    int e = -1, y = x;
-    for (int attempt = 0; attempt < 2 * X && e < 0; ++attempt) {
-      if (attempt > 0) {
-        int best = -1, most = 0;
-        for (int z = 0; z < X; ++z) {
-          const DevQueue qz = p.queues[z];
-          const int left = (qz.cnt - qz.head) - __hip_atomic_load(p.claim + z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          if (left > most) {
-            most = left;
-            best = z;
-          }
-        }
-        if (best < 0) break;
-        y = best;
+// The next dK/dV entry of a workgroup that has finished one (see DkdvParams):
+// `claimed` is what it drew from its own list's counter; past the list's end it
+// draws from the list with the most unclaimed entries left. One lane's work.
+// -1: nothing left anywhere. Each entry is drawn exactly once, and no
+// workgroup waits for another.
+__device__ __forceinline__ int dkdv_claimed_entry(const DkdvParams &p, int own, int claimed) {
+  const int tail = p.list_len - p.list_head;
+  if (claimed < tail) return own * p.list_len + p.list_head + claimed;
+  for (int attempt = 0; attempt < 2 * p.lists; ++attempt) {
+    int best = -1, most = 0;
+    for (int z = 0; z < p.lists; ++z) {
+      const int left = tail - __hip_atomic_load(p.claim + z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (left > most) {
+        most = left;
+        best = z;
       }
-      const DevQueue qy = p.queues[y];
-      const int i = __hip_atomic_fetch_add(p.claim + y, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (i < qy.cnt - qy.head) e = qy.off + qy.head + i;
     }
-    slot = e;
+    if (best < 0) break;
+    const int i = __hip_atomic_fetch_add(p.claim + best, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (i < tail) return best * p.list_len + p.list_head + i;
   }
-  __syncthreads();
-  return __builtin_amdgcn_readfirstlane(slot);
+  return -1;
 }
 
 // Key tiles of one batch row at one KV head, from the row's slice of the
@@ -1034,6 +1020,13 @@ __global__ __launch_bounds__(256) void bwd_prologue_bf16_kernel(PreParams p) {
 // ahead. Copies for blocks past the end use an empty buffer resource (they
 // write zeros that nothing reads).
 //
+// The workgroups are persistent: one per compute unit, each working through
+// entries (key tile, KV head) that it draws when it has finished one. Against
+// one workgroup per entry this saves the dispatch between two entries of a
+// compute unit: 858 -> 836 us on 8,192 packed tokens (8 entries of ~100 us per
+// compute unit), 2,142 -> 2,085 us on 64 ragged cartridges x 512 queries (34
+// of ~60 us), 578 -> 567 us on 4 x 1,024 cartridges x 1,024 queries.
+//
 // P needs no mask for keys beyond the tile (their dK / dV columns are never
 // stored) or for packed rows beyond the batch row's last (Q, dO, Q^T, dO^T,
 // LSE2 and D all read as zero there: P = 1 and dS = 0 add nothing). On self
@@ -1041,7 +1034,7 @@ __global__ __launch_bounds__(256) void bwd_prologue_bf16_kernel(PreParams p) {
 // ---------------------------------------------------------------------------
 template <int D, bool GFAST>
 __global__ __launch_bounds__(kFastThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void dkdv_bf16_kernel(DkdvParams p) {
+void dkdv_bf16_kernel(DkdvParams) {
   constexpr int NSTEP = D / 16;
   constexpr int DT = D / 32;
   constexpr int QB = kDkdvQBlock;              // 64 query rows per block
@@ -1056,7 +1049,7 @@ void dkdv_bf16_kernel(DkdvParams p) {
   // immediates.
   constexpr int XCH = 8 * RB;                  // P of each SIMD's 32 keys x 64 rows, 4 KiB per SIMD
   constexpr int STATS = XCH + 16384;           // LSE2 x2, D x2
-  constexpr int CLAIM = STATS + 4 * QB * 4;   // claimed order entry (DevQueue lists)
+  constexpr int CLAIM = STATS + 4 * QB * 4;   // the next entry
   // One arena for every LDS use: a second LDS object would keep the
   // compiler from telling the direct-to-LDS copies' targets from the LDS
   // reads, and it would then wait for every outstanding copy before each read.
@@ -1070,17 +1063,24 @@ void dkdv_bf16_kernel(DkdvParams p) {
   float *const dv0 = ls0 + 2 * QB;
   float *const dv1 = ls0 + 3 * QB;
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int entry;
+  {
+    const DkdvParams p = load_kernarg<DkdvParams>();
+    entry = (int)blockIdx.x % p.lists * p.list_len + (int)blockIdx.x / p.lists;
+  }
+  for (;;) {
+  // Per entry, the lane index and the parameters are read anew: values kept
+  // across entries would be held in registers through the block loop.
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const DkdvParams p = load_kernarg<DkdvParams>();
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = lane >> 5, n = lane & 31;
   const int q = wave & 3;                      // SIMD, key quarter, index within the wave's group
   const bool pwave = wave < 4;
-  int entry = (int)blockIdx.x;
-  if (p.queues) {
-    entry = dkdv_entry(p, tid, *reinterpret_cast<int *>(smem + CLAIM));
-    if (entry < 0) return;   // every list is done
-  }
+  int claimed = 0;                             // thread 0's draw from its list for the entry after this one
   const DevWg wg = load_const(p.order, entry);
-  const int tile = __builtin_amdgcn_readfirstlane(wg.tile), kvh = __builtin_amdgcn_readfirstlane(wg.kvh);
+  const int kvh = __builtin_amdgcn_readfirstlane(wg.kvh), key0 = __builtin_amdgcn_readfirstlane(wg.tile) * KTB;
   const int g = p.g, Hkv = p.Hkv, Hq = Hkv * g;
   const float c = p.scale_log2;
 
@@ -1089,17 +1089,12 @@ void dkdv_bf16_kernel(DkdvParams p) {
   __bf16 *dkp;
   __bf16 *dvp;
   int64_t st;
-  int klen, key0, use_b = 0, nblk_all;
-  const bool self = tile >= p.cart_tiles;
-  int self_b = 0;
+  int klen, use_b = 0, nblk_all;
+  const int owner = __builtin_amdgcn_readfirstlane(wg.owner);
+  const bool self = owner < 0;
+  const int self_b = -1 - owner;
   if (!self) {
-    int lo = 0, hi = p.n_carts - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (load_const(p.carts, mid).tile_begin <= tile) lo = mid; else hi = mid - 1;
-    }
-    const DevCart cd = load_const(p.carts, lo);
-    key0 = (tile - cd.tile_begin) * KTB;
+    const DevCart cd = load_const(p.carts, owner);
     klen = cd.len;
     kbase = (const __bf16 *)cd.k + kvh * cd.stride_head;
     vbase = (const __bf16 *)cd.v + kvh * cd.stride_head;
@@ -1109,12 +1104,8 @@ void dkdv_bf16_kernel(DkdvParams p) {
     use_b = cd.use_begin;
     nblk_all = cd.nblk;
   } else {
-    const int rel = tile - p.cart_tiles;
-    self_b = rel / p.self_tiles;
-    key0 = (rel % p.self_tiles) * KTB;
     const DevRow sr = load_const(p.rows, self_b);
     klen = sr.len;
-    if (key0 >= klen) return;   // grid sized for the longest row
     const int64_t base = ((int64_t)sr.tok0 * Hkv + kvh) * D;
     kbase = (const __bf16 *)p.k_self + base;
     vbase = (const __bf16 *)p.v_self + base;
@@ -1621,6 +1612,14 @@ void dkdv_bf16_kernel(DkdvParams p) {
       wait_vmcnt<0>();
     }
 
+    // The next entry's draw travels while the gradients are stored.
+    {
+      const DkdvParams pe = load_kernarg<DkdvParams>();
+      if (tid == 0 && pe.list_len > pe.list_head)
+        claimed = __hip_atomic_fetch_add(pe.claim + (int)blockIdx.x % pe.lists, 1, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+    }
+
     // Store through LDS: each lane holds 4-channel pieces of its key's row;
     // staged as whole rows, every store instruction writes full 16-byte
     // pieces of consecutive rows (whole cache lines instead of 8-byte pieces
@@ -1628,32 +1627,42 @@ void dkdv_bf16_kernel(DkdvParams p) {
     // (wait above), so after this barrier the arena is free.
     __syncthreads();
     __bf16 *dst = pwave ? dvp : dkp;
-    if (!dst) return;
-    const float sc = pwave ? 1.0f : p.scale;
-    constexpr int SRS = (D + 8) * 2;                 // staged row bytes (padded against bank conflicts)
-    char *const stg = smem + wave * 32 * SRS;
+    if (dst) {
+      const float sc = pwave ? 1.0f : p.scale;
+      constexpr int SRS = (D + 8) * 2;                 // staged row bytes (padded against bank conflicts)
+      char *const stg = smem + wave * 32 * SRS;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+      for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-      for (int jj = 0; jj < 4; ++jj)
-        store4(reinterpret_cast<__bf16 *>(stg + n * SRS) + dt * 32 + jj * 8 + G * 4, acc[dt][jj * 4 + 0] * sc,
-               acc[dt][jj * 4 + 1] * sc, acc[dt][jj * 4 + 2] * sc, acc[dt][jj * 4 + 3] * sc);
-    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's LDS writes are done
-    asm volatile("" ::: "memory");
-    constexpr int CPR = D / 8;                       // 16-byte pieces per row
-    constexpr int RPI = 64 / CPR;                    // rows per store instruction
-    const int nrow = min(32, nk - 32 * q);           // valid keys of this wave
-    const int pr = lane / CPR, pc = lane % CPR;
+        for (int jj = 0; jj < 4; ++jj)
+          store4(reinterpret_cast<__bf16 *>(stg + n * SRS) + dt * 32 + jj * 8 + G * 4, acc[dt][jj * 4 + 0] * sc,
+                 acc[dt][jj * 4 + 1] * sc, acc[dt][jj * 4 + 2] * sc, acc[dt][jj * 4 + 3] * sc);
+      __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this wave's LDS writes are done
+      asm volatile("" ::: "memory");
+      constexpr int CPR = D / 8;                       // 16-byte pieces per row
+      constexpr int RPI = 64 / CPR;                    // rows per store instruction
+      const int nrow = min(32, nk - 32 * q);           // valid keys of this wave
+      const int pr = lane / CPR, pc = lane % CPR;
 #pragma unroll
-    for (int i = 0; i < 32 / RPI; ++i) {
-      const int r = RPI * i + pr;
-      const uint4 v = *reinterpret_cast<const uint4 *>(stg + r * SRS + pc * 16);
-      if (r < nrow) *reinterpret_cast<uint4 *>(dst + (int64_t)(key0 + 32 * q + r) * st + pc * 8) = v;
+      for (int i = 0; i < 32 / RPI; ++i) {
+        const int r = RPI * i + pr;
+        const uint4 v = *reinterpret_cast<const uint4 *>(stg + r * SRS + pc * 16);
+        if (r < nrow) *reinterpret_cast<uint4 *>(dst + (int64_t)(key0 + 32 * q + r) * st + pc * 8) = v;
+      }
     }
-
   };
   if (pwave) body(std::true_type{});
   else body(std::false_type{});
+  const DkdvParams pe = load_kernarg<DkdvParams>();
+  if (pe.list_len == pe.list_head) return;   // every list was handed out at the start
+  // After the barrier every wave has read its staged rows back, and the next
+  // entry's copies may overwrite the arena.
+  int *const slot = reinterpret_cast<int *>(smem + CLAIM);
+  if (tid == 0) *slot = dkdv_claimed_entry(pe, (int)blockIdx.x % pe.lists, claimed);
+  lds_barrier();
+  entry = __builtin_amdgcn_readfirstlane(*slot);
+  if (entry < 0) return;
+  }
 }
 
 hipError_t launch_fwd_bf16(const FwdParams &p, int D, hipStream_t s) {

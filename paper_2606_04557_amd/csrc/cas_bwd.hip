@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kThreads) void dkdv_kernel(DkdvParams p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int G = lane >> 5, n = lane & 31;
   const DevWg wg = p.order[blockIdx.x];
-  const int tile = wg.tile, kvh = wg.kvh;
+  const int kvh = wg.kvh, key0 = wg.tile * kDkdvKeyTile;
   const int g = p.g, Hkv = p.Hkv, Hq = Hkv * g;
   const float c = p.scale_log2;
 
@@ -87,17 +87,11 @@ __global__ __launch_bounds__(kThreads) void dkdv_kernel(DkdvParams p) {
   T *dkp;
   T *dvp;
   int64_t st;
-  int klen, key0, use_b = 0, use_e = 1;
-  const bool self = tile >= p.cart_tiles;
-  int self_b = 0;
+  int klen, use_b = 0, use_e = 1;
+  const bool self = wg.owner < 0;
+  const int self_b = -1 - wg.owner;
   if (!self) {
-    int lo = 0, hi = p.n_carts - 1;
-    while (lo < hi) {
-      const int mid = (lo + hi + 1) >> 1;
-      if (p.carts[mid].tile_begin <= tile) lo = mid; else hi = mid - 1;
-    }
-    const DevCart cd = p.carts[lo];
-    key0 = (tile - cd.tile_begin) * kDkdvKeyTile;
+    const DevCart cd = p.carts[wg.owner];
     klen = cd.len;
     kbase = (const T *)cd.k + kvh * cd.stride_head;
     vbase = (const T *)cd.v + kvh * cd.stride_head;
@@ -107,12 +101,8 @@ __global__ __launch_bounds__(kThreads) void dkdv_kernel(DkdvParams p) {
     use_b = cd.use_begin;
     use_e = cd.use_end;
   } else {
-    const int rel = tile - p.cart_tiles;
-    self_b = rel / p.self_tiles;
-    key0 = (rel % p.self_tiles) * kDkdvKeyTile;
     const DevRow sr = p.rows[self_b];
     klen = sr.len;
-    if (key0 >= klen) return;   // grid sized for the longest row
     const int64_t base = ((int64_t)sr.tok0 * Hkv + kvh) * D;
     kbase = (const T *)p.k_self + base;
     vbase = (const T *)p.v_self + base;

@@ -331,4 +331,19 @@ __device__ __forceinline__ T load_const(const T *base, int i) {
   return r;
 }
 
+// The kernel's only parameter, read from the kernel argument segment at this
+// point and not kept from an earlier read.
+template <typename T>
+__device__ __forceinline__ T load_kernarg() {
+  static_assert(sizeof(T) % 4 == 0, "4-byte words");
+  typedef const __attribute__((address_space(4))) uint32_t cword_t;
+  cword_t *w = (cword_t *)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(w));
+  T r;
+  uint32_t *rw = reinterpret_cast<uint32_t *>(&r);
+#pragma unroll
+  for (int k = 0; k < (int)(sizeof(T) / 4); ++k) rw[k] = w[k];
+  return r;
+}
+
 }  // namespace cas

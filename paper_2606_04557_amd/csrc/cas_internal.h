@@ -70,31 +70,18 @@ struct DevCart {
   int64_t stride_tok;
   int64_t stride_head;
   int32_t len;
-  int32_t tile_begin;   // first kDkdvKeyTile tile in the dK/dV grid
   int32_t use_begin;    // uses[use_begin .. use_end) = batch rows referencing it
   int32_t use_end;
   int32_t nblk;         // 64-row query blocks over all uses (sum of the rows' block counts)
-  int32_t pad_;
 };
 
-// One dK/dV workgroup: a key tile (cartridge tiles first, then self tile
-// j of batch row b as cart_tiles + b * self_tiles + j) and a KV head. The host
-// lists them longest first (most query blocks), so the long workgroups of
-// every KV head start in the first wave of the dispatch.
+// One entry of dK/dV work: 128-key tile `tile` of distinct cartridge `owner`
+// (or, for owner = -1 - b, of batch row b's self keys) at KV head kvh. The host
+// lists them longest first (most query blocks).
 struct DevWg {
+  int32_t owner;
   int32_t tile;
   int32_t kvh;
-};
-
-// The bf16 dK/dV list of one XCD: entries [off, off + cnt) of the order table.
-// Workgroup j of the XCD takes entry off + j while j < head; the entries from
-// head on (the list's shortest) are claimed at run time, first by the XCD's
-// own workgroups, then by any XCD that has run out of its own.
-struct DevQueue {
-  int32_t off;
-  int32_t cnt;
-  int32_t head;
-  int32_t pad;
 };
 
 // One workgroup of the bf16 forward or dQ kernel: 256-row query block qblk
@@ -193,13 +180,13 @@ struct DkdvParams {
   const DevCart *carts;
   const int32_t *uses;
   const DevRow *rows;
-  const DevWg *order;       // the workgroups' tiles and KV heads ([grid] without queues)
-  const DevQueue *queues;   // bf16: [xcds] per-XCD lists of `order`, or null (entry = workgroup id)
-  int32_t *claim;           // bf16: [xcds] tail entries claimed so far (zero at launch)
-  int32_t xcds;             // bf16 with queues: workgroup i runs on XCD i % xcds
-  int32_t n_carts;
-  int32_t cart_tiles;       // dK/dV tiles over all distinct cartridges
-  int32_t self_tiles;       // dK/dV tiles per batch row over the self keys (longest row)
+  const DevWg *order;       // fp32: workgroup i takes entry i
+  // bf16: `lists` lists (one per XCD, or one) of list_len entries, one after
+  // the other in `order`. Workgroup i works on list i % lists: it starts with
+  // entry i / lists (< list_head) and claims entries from list_head on at run
+  // time, first of its own list, then of any list that has some left.
+  int32_t *claim;           // [lists] entries claimed so far (zero at launch)
+  int32_t lists, list_len, list_head;
   int32_t B, Hkv, g;
   float scale_log2;
   float scale;

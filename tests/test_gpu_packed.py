@@ -105,3 +105,15 @@ def test_packed_8k_full():
     err = (tot - exp).abs().max().item() / exp.abs().max().item()
     print("P8K sum dV rel err", f"{err:.2e}")
     assert err <= 2e-2
+
+
+@pytest.mark.parametrize("Hkv", [3, 8])
+@pytest.mark.parametrize("n_carts", [8, 60])
+def test_dkdv_entry_lists(Hkv, n_carts):
+    """More and fewer dK/dV entries than compute units, on one list (3 KV
+    heads) and on a list per XCD (8): every entry is taken exactly once, the
+    ones drawn at run time included."""
+    wl = casgen.custom("lists", "bf16", batch=3, q_len=0, num_q_heads=2 * Hkv, num_kv_heads=Hkv, head_dim=64,
+                       q_lens=[40, 9, 130], cart_lens=[129 + 3 * i for i in range(n_carts)],
+                       rows=[list(range(n_carts)), [0, n_carts - 1], list(range(0, n_carts, 3))], seed=777, cart_std=0.5)
+    _check_full(GpuCase(wl), f"lists {Hkv} {n_carts}")
