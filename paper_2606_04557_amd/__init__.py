@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes
 import dataclasses
+import struct
 from typing import List, Optional, Sequence, Tuple
 
 from . import _lib
@@ -61,6 +62,11 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# cas_segment_t: k, v, dk, dv, len, stride_tok, stride_head.
+_SEGMENT = struct.Struct("@PPPPqqq")
+assert _SEGMENT.size == ctypes.sizeof(_lib.Segment)
+
+
 class Problem:
     """Host-side segment table (cas_problem_t) built from torch tensors.
 
@@ -77,6 +83,10 @@ class Problem:
             if len(q_offsets) != batch + 1:
                 raise ValueError("q_offsets must have batch+1 entries")
             self._qoffs = (ctypes.c_int32 * (batch + 1))(*[int(x) for x in q_offsets])
+        # One pass over the entries, each packed in one go into its
+        # cas_segment_t: a serving batch lists hundreds of them per call, and
+        # field by field this table took longer to build than the forward of
+        # 64 requests x 4 cartridges takes to run.
         n = sum(len(r) for r in rows)
         self._segs = (_lib.Segment * max(n, 1))()
         self._offs = (ctypes.c_int32 * (batch + 1))()
@@ -84,19 +94,24 @@ class Problem:
         for b, row in enumerate(rows):
             self._offs[b] = i
             for s in row:
-                k, v = s.k, s.v
-                if k.dim() != 3 or k.shape != v.shape or k.stride() != v.stride():
+                k, v, dk, dv = s.k, s.v, s.dk, s.dv
+                shape, stride = k.shape, k.stride()
+                if len(shape) != 3 or v.shape != shape or v.stride() != stride:
                     raise ValueError("segment k and v must be [len, Hkv, d] with equal strides")
-                for gt in (s.dk, s.dv):
-                    if gt is not None and (gt.shape != k.shape or gt.stride() != k.stride()):
+                p_dk = p_dv = 0
+                if dk is not None:
+                    if dk.shape != shape or dk.stride() != stride:
                         raise ValueError("segment dk/dv must match k's shape and strides")
-                if k.shape[0] > 0 and k.stride(2) != 1:
+                    p_dk = dk.data_ptr()
+                if dv is not None:
+                    if dv.shape != shape or dv.stride() != stride:
+                        raise ValueError("segment dk/dv must match k's shape and strides")
+                    p_dv = dv.data_ptr()
+                length, (st_tok, st_head, st_ch) = shape[0], stride
+                if length > 0 and st_ch != 1:
                     raise ValueError("segment channel stride must be 1")
-                e = self._segs[i]
-                e.k, e.v, e.dk, e.dv = _ptr(k), _ptr(v), _ptr(s.dk), _ptr(s.dv)
-                e.len = int(k.shape[0])
-                e.stride_tok = int(k.stride(0))
-                e.stride_head = int(k.stride(1))
+                _SEGMENT.pack_into(self._segs, i * _SEGMENT.size, k.data_ptr(), v.data_ptr(), p_dk, p_dv, length, st_tok,
+                                   st_head)
                 i += 1
         self._offs[batch] = i
         qo = (ctypes.cast(self._qoffs, ctypes.POINTER(ctypes.c_int32)) if self._qoffs is not None
@@ -157,6 +172,19 @@ def _workspace(nbytes: int, device):
     return torch.empty(max(nbytes, 1), dtype=torch.uint8, device=device)
 
 
+def _with_workspace(call, size, workspace, device) -> None:
+    """call(ptr, bytes) with the caller's workspace, or, without one or where
+    the library finds it too small (before it enqueues anything), with a new
+    one of size() bytes. The library's own check stands in for asking for the
+    size first, which plans the whole problem a second time."""
+    if workspace is not None:
+        status = call(workspace.data_ptr(), workspace.numel())
+        if status != _lib.CAS_ERR_WORKSPACE:
+            return _check(status)
+    ws = _workspace(size(), device)
+    _check(call(ws.data_ptr(), ws.numel()))
+
+
 def prefix_attn_fwd(q, k_self, v_self, rows: Sequence[Sequence[Segment]], num_kv_heads: int,
                     group_size: int, softmax_scale: float, o=None, lse=None, need_lse: bool = True,
                     stream=None, workspace=None,
@@ -176,11 +204,10 @@ def prefix_attn_fwd(q, k_self, v_self, rows: Sequence[Sequence[Segment]], num_kv
         else:
             T, Hq, _ = q.shape
             lse = torch.empty((Hq, T), dtype=torch.float32, device=q.device)
-    ws_n = workspace_size(prob, False)
-    ws = workspace if workspace is not None and workspace.numel() >= ws_n else _workspace(ws_n, q.device)
-    _check(load().cas_prefix_attn_fwd(ctypes.byref(prob.c), q.data_ptr(), k_self.data_ptr(),
-                                      v_self.data_ptr(), o.data_ptr(), _ptr(lse), ws.data_ptr(),
-                                      ws.numel(), _stream_handle(q.device, stream)))
+    args = (ctypes.byref(prob.c), q.data_ptr(), k_self.data_ptr(), v_self.data_ptr(), o.data_ptr(), _ptr(lse))
+    st = _stream_handle(q.device, stream)
+    _with_workspace(lambda ptr, n: load().cas_prefix_attn_fwd(*args, ptr, n, st), lambda: workspace_size(prob, False),
+                    workspace, q.device)
     return o, lse
 
 
@@ -211,12 +238,11 @@ def prefix_attn_bwd(q, k_self, v_self, rows: Sequence[Sequence[Segment]], num_kv
             dk_self = torch.empty_like(k_self)
         if dv_self is None:
             dv_self = torch.empty_like(v_self)
-    ws_n = workspace_size(prob, True)
-    ws = workspace if workspace is not None and workspace.numel() >= ws_n else _workspace(ws_n, q.device)
-    _check(load().cas_prefix_attn_bwd(ctypes.byref(prob.c), q.data_ptr(), k_self.data_ptr(),
-                                      v_self.data_ptr(), o.data_ptr(), lse.data_ptr(), d_o.data_ptr(),
-                                      _ptr(dq), _ptr(dk_self), _ptr(dv_self), ws.data_ptr(),
-                                      ws.numel(), _stream_handle(q.device, stream)))
+    args = (ctypes.byref(prob.c), q.data_ptr(), k_self.data_ptr(), v_self.data_ptr(), o.data_ptr(), lse.data_ptr(),
+            d_o.data_ptr(), _ptr(dq), _ptr(dk_self), _ptr(dv_self))
+    st = _stream_handle(q.device, stream)
+    _with_workspace(lambda ptr, n: load().cas_prefix_attn_bwd(*args, ptr, n, st), lambda: workspace_size(prob, True),
+                    workspace, q.device)
     return dq, dk_self, dv_self
 
 
@@ -304,6 +330,9 @@ class DecodeProblem:
         self._kv = (ctypes.c_int32 * max(B, 1))(*[int(x) for x in kv_lens])
         self._po = (ctypes.c_int32 * (B + 1))(*po)
         self._ids = (ctypes.c_int32 * max(len(ids), 1))(*ids)
+        # Workspace bytes of the last call; only a first guess for the next
+        # (the library checks it, and the size is asked for again if it fails).
+        self.ws_bytes = 0
         I = ctypes.POINTER(ctypes.c_int32)
         self.c = _lib.DecodeProblem(B, num_kv_heads, group_size, head_dim, float(softmax_scale), page_size,
                                     int(num_pages), ctypes.cast(self._qo, I), ctypes.cast(self._kv, I),
@@ -327,12 +356,18 @@ def paged_decode_fwd(q, k_pages, v_pages, q_counts: Sequence[int], kv_lens: Sequ
         o = torch.empty_like(q)
     if lse is None and need_lse:
         lse = torch.empty((q.shape[1], q.shape[0]), dtype=torch.float32, device=q.device)
-    n = ctypes.c_size_t(0)
-    _check(load().cas_paged_decode_workspace_size(ctypes.byref(prob.c), ctypes.byref(n)))
-    ws = workspace if workspace is not None and workspace.numel() >= n.value else _workspace(n.value, q.device)
-    _check(load().cas_paged_decode_fwd(ctypes.byref(prob.c), q.data_ptr(), k_pages.data_ptr(), v_pages.data_ptr(),
-                                       o.data_ptr(), _ptr(lse), ws.data_ptr(), ws.numel(),
-                                       _stream_handle(q.device, stream)))
+    args = (ctypes.byref(prob.c), q.data_ptr(), k_pages.data_ptr(), v_pages.data_ptr(), o.data_ptr(), _ptr(lse))
+    st = _stream_handle(q.device, stream)
+
+    def size():
+        n = ctypes.c_size_t(0)
+        _check(load().cas_paged_decode_workspace_size(ctypes.byref(prob.c), ctypes.byref(n)))
+        prob.ws_bytes = n.value
+        return n.value
+
+    if workspace is None and prob.ws_bytes:
+        workspace = _workspace(prob.ws_bytes, q.device)
+    _with_workspace(lambda ptr, n: load().cas_paged_decode_fwd(*args, ptr, n, st), size, workspace, q.device)
     return o, lse
 
 

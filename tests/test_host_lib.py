@@ -418,3 +418,38 @@ def test_noalloc_forward_validation(lib):
     f = Fake(rows=((1 << 25,),), grads=False)
     assert call(f) == _lib.CAS_ERR_UNSUPPORTED
     assert "scratch" in _msg(lib)
+
+
+@pytest.mark.parametrize("layout", ["tok", "padded", "head", "one", "empty"])
+def test_binding_segment_table(layout):
+    """The binding's segment table holds every tensor's address, length and
+    strides, and refuses what is not a [len, Hkv, d] view with equal strides."""
+    import torch
+    import paper_2606_04557_amd as cas
+    L, H, D = (0 if layout == "empty" else 1 if layout == "one" else 5), 2, 64
+
+    def make():
+        if layout == "padded":
+            return torch.zeros(L, H * D + 64).to(torch.bfloat16)[:, : H * D].view(L, H, D)
+        if layout == "head":
+            return torch.zeros(H, L, D).to(torch.bfloat16).permute(1, 0, 2)
+        return torch.zeros(L, H, D).to(torch.bfloat16)
+
+    k, v, dk, dv = (make() for _ in range(4))
+    q = torch.zeros(2, 3, 4, D).to(torch.bfloat16)
+    rows = [[cas.Segment(k, v, dk, None), cas.Segment(v, k)], [cas.Segment(k, v, dk, dv)]]
+    p = cas.Problem.from_tensors(q, rows, 2, 2, 0.1)
+    assert list(p._offs) == [0, 2, 3]
+    for e, (a, b, c, d) in zip(p._segs, [(k, v, dk, None), (v, k, None, None), (k, v, dk, dv)]):
+        assert (e.k or 0, e.v or 0) == (a.data_ptr(), b.data_ptr())
+        assert (e.dk or 0, e.dv or 0) == (c.data_ptr() if c is not None else 0, d.data_ptr() if d is not None else 0)
+        assert (e.len, e.stride_tok, e.stride_head) == (L, k.stride(0), k.stride(1))
+    wide = torch.zeros(L, H, 2 * D).to(torch.bfloat16)
+    for seg in (cas.Segment(k[0] if L else k.view(0, H * D), v), cas.Segment(k, wide[..., :D]), cas.Segment(k, v, wide[..., :D]),
+                cas.Segment(k, v, None, make()[..., : D // 2])):
+        with pytest.raises(ValueError):
+            cas.Problem.from_tensors(q, [[seg], []], 2, 2, 0.1)
+    if L > 0:
+        odd = wide[..., ::2]
+        with pytest.raises(ValueError):
+            cas.Problem.from_tensors(q, [[cas.Segment(odd, odd)], []], 2, 2, 0.1)
