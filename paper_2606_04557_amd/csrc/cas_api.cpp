@@ -145,9 +145,48 @@ Topology device_topology() {
   return t;
 }
 
-// Key-axis splits for a grid of base_wgs workgroups: aim at two workgroups
-// per compute unit.
-int auto_splits(int64_t base_wgs, int64_t min_row_tiles, int cus) {
+// Key-axis splits of the forward or dQ pass, for base_wgs workgroups unsplit
+// that walk avg_tiles key tiles on average and max_tiles at most, one
+// workgroup per compute unit at a time (bf16). Costs are in key tiles (about
+// 1.2-1.7 us each): a workgroup costs kWgTiles on top of the tiles it walks
+// (dispatch, first loads, pipeline fill and drain, epilogue: 11-13 us), a
+// split pass kMergeTiles for the merge's launch plus the partials' bytes.
+//
+// Rounds of workgroups decide. Forward and merge, each timed with its launch:
+// 32 workgroups' 139 tiles take 53 us in 8 splits, one round, and 67 us in 16,
+// two rounds (what aiming at two workgroups per compute unit chose); 24
+// workgroups' 18 tiles 32 us unsplit, 26 us in 4 to 10 splits; 152 workgroups'
+// 17 tiles 31 us unsplit, 44 us in 2 splits.
+//
+// Where one round would leave splits of kLongTiles or more, one and two
+// rounds measure alike (64 workgroups of 2,056 tiles, forward and dQ: 2,287 us
+// in 4 splits, 2,320 us in 8); such calls keep two workgroups per compute
+// unit. With more workgroups than compute units, two splits at most are tried
+// (the partials' memory grows with the queries).
+int auto_splits(int64_t base_wgs, int64_t avg_tiles, int64_t max_tiles, int64_t partial_bytes, int cus) {
+  constexpr int64_t kWgTiles = 8, kMergeTiles = 3, kLongTiles = 128;
+  constexpr double kBytesPerTile = 5e6;   // partials written, then read
+  if (base_wgs < 1) return 1;
+  const int64_t one_round = std::max<int64_t>(1, cus / base_wgs);
+  if (base_wgs <= cus && ceil_div(max_tiles, one_round) >= kLongTiles)
+    return (int)std::min<int64_t>(ceil_div(2 * (int64_t)cus, base_wgs), kMaxSplits);
+  const int64_t cap = base_wgs > cus ? 2 : std::min<int64_t>(kMaxSplits, std::max<int64_t>(1, max_tiles));
+  int64_t best = 1;
+  double best_cost = 0.0;
+  for (int64_t s = 1; s <= cap; ++s) {
+    const int64_t rounds = ceil_div(base_wgs * s, cus) * (kWgTiles + ceil_div(avg_tiles, s));
+    double cost = (double)std::max(rounds, kWgTiles + ceil_div(max_tiles, s));
+    if (s > 1) cost += (double)kMergeTiles + (double)s * (double)partial_bytes / kBytesPerTile;
+    if (s == 1 || cost < best_cost) {
+      best = s;
+      best_cost = cost;
+    }
+  }
+  return (int)best;
+}
+
+// The same for the fp32 kernels: aim at two workgroups per compute unit.
+int auto_splits_fp32(int64_t base_wgs, int64_t min_row_tiles, int cus) {
   const int64_t target = 2 * (int64_t)cus;
   if (base_wgs >= (target * 3) / 4) return 1;
   int64_t s = ceil_div(target, std::max<int64_t>(1, base_wgs));
@@ -357,18 +396,28 @@ cas_status_t build_plan(const cas_problem_t *p, bool bwd, Plan &pl, int fwd_spli
   pl.nqblk_dq = (int)ceil_div(pl.nrows_max, rpw_dq);
   // The grids are sized for the longest row; the split heuristic counts the
   // workgroups that have rows.
-  int64_t base_fwd = 0, base_dq = 0;
+  int64_t base_fwd = 0, base_dq = 0, sum_tiles = 0, max_tiles = 0;
   for (int b = 0; b < pl.B; ++b) {
-    base_fwd += Hkv * ceil_div((int64_t)pl.len[b] * pl.g, rpw_fwd);
-    base_dq += Hkv * ceil_div((int64_t)pl.len[b] * pl.g, rpw_dq);
+    const int64_t nrows = (int64_t)pl.len[b] * pl.g;
+    base_fwd += Hkv * ceil_div(nrows, rpw_fwd);
+    base_dq += Hkv * ceil_div(nrows, rpw_dq);
+    // bf16: key tiles that the row's query blocks walk (prefix, then the self
+    // tiles up to the block's last position: half of them on average).
+    const int64_t self = ceil_div(pl.len[b], kKeyTile);
+    sum_tiles += Hkv * ceil_div(nrows, rpw_fwd) * (pl.rows[b].prefix_tiles + (self + 1) / 2);
+    if (nrows > 0) max_tiles = std::max(max_tiles, pl.rows[b].prefix_tiles + self);
   }
   const Topology topo = device_topology();
   pl.xcds = topo.xcds;
   pl.cus = topo.cus;
-  pl.fwd_splits = tu.fwd_splits > 0 ? std::min(tu.fwd_splits, kMaxSplits)
-                                    : auto_splits(base_fwd, min_row_tiles, topo.cus);
+  auto choose = [&](int tuned, int64_t base) {
+    if (tuned > 0) return std::min(tuned, kMaxSplits);
+    if (!bf16) return auto_splits_fp32(base, min_row_tiles, topo.cus);
+    return auto_splits(base, ceil_div(sum_tiles, std::max<int64_t>(1, base)), max_tiles, pl.T * pl.Hq * D * 4, topo.cus);
+  };
+  pl.fwd_splits = choose(tu.fwd_splits, base_fwd);
   if (fwd_split_cap > 0) pl.fwd_splits = std::min(pl.fwd_splits, fwd_split_cap);
-  pl.dq_splits = tu.dq_splits > 0 ? std::min(tu.dq_splits, kMaxSplits) : auto_splits(base_dq, min_row_tiles, topo.cus);
+  pl.dq_splits = choose(tu.dq_splits, base_dq);
   if ((int64_t)pl.B * Hkv * pl.nqblk_fwd * pl.fwd_splits > INT32_MAX ||
       (int64_t)pl.B * Hkv * pl.nqblk_dq * pl.dq_splits > INT32_MAX)
     return fail(CAS_ERR_UNSUPPORTED, "grid too large");

@@ -125,6 +125,22 @@ def test_small_forced_splits(spec):
         cas.set_tuning(0, 0)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("splits", [2, 8, 9, 17, 32])
+def test_split_merge_counts(D, splits):
+    """Split counts around the merge's batches of eight and its one or two
+    LSEs per lane, with more splits than some rows have tiles (empty splits)."""
+    import paper_2606_04557_amd as cas
+    wl = casgen.custom("merge", "bf16", batch=2, q_len=70, num_q_heads=6, num_kv_heads=2, head_dim=D,
+                       cart_lens=[700, 64, 130], rows=[[0, 1, 2], []], seed=210 + splits, cart_std=0.5)
+    case = GpuCase(wl)
+    try:
+        cas.set_tuning(fwd_splits=splits, dq_splits=splits)
+        _check_full(case, f"merge {splits}")
+    finally:
+        cas.set_tuning(0, 0)
+
+
 def test_wide_token_stride():
     """A 1,024-token cartridge stored with a token stride of 2^21 elements
     (4 MiB), so that its keys and gradients span 4 GiB: byte offsets within a

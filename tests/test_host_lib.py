@@ -420,6 +420,23 @@ def test_noalloc_forward_validation(lib):
     assert "scratch" in _msg(lib)
 
 
+@pytest.mark.parametrize("B,Sq,rows", [(1, 64, (512,)), (1, 16, (1024,) * 4), (4, 72, (450,) * 3), (3, 210, (900,) * 9),
+                                       (19, 53, (1000,)), (31, 64, (1,)), (33, 64, (300,)), (40, 64, (2000,)), (1, 64, ())])
+def test_splits_fill_the_compute_units_once(lib, B, Sq, rows):
+    """Short bf16 calls: splits never push a call that one round of workgroups
+    holds into a second round, nor go past the row's tiles; calls with more
+    workgroups than compute units take at most two."""
+    f = Fake(B=B, Sq=Sq, Hkv=8, g=4, D=128, rows=(rows,) * B)
+    info = _lib.PlanInfo()
+    assert lib.cas_plan_info(ctypes.byref(f.p), ctypes.byref(info)) == _lib.CAS_OK
+    base = B * 8 * -(-Sq * 4 // 256)
+    tiles = sum(-(-n // 64) for n in rows) + -(-Sq // 64)
+    for s in (info.fwd_splits, info.dq_splits):
+        assert 1 <= s <= min(32, max(1, tiles))
+        assert base * s <= 256 if base <= 256 else s <= 2
+    assert info.fwd_workgroups == base * info.fwd_splits
+
+
 @pytest.mark.parametrize("layout", ["tok", "padded", "head", "one", "empty"])
 def test_binding_segment_table(layout):
     """The binding's segment table holds every tensor's address, length and
