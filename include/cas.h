@@ -445,7 +445,7 @@ typedef struct {
   int32_t fwd_splits;       /* key-axis splits used by the forward */
   int32_t dq_splits;        /* key-axis splits used by the dQ pass */
   int32_t fwd_workgroups;   /* forward grid size */
-  int32_t dkdv_workgroups;  /* dK/dV grid size */
+  int32_t dkdv_workgroups;  /* dK/dV work: 128-key tiles x KV heads */
   int32_t unique_segments;  /* distinct cartridges after alias folding */
   int32_t total_key_tiles;  /* dK/dV key tiles over unique cartridges and self */
   int64_t max_prefix_len;   /* longest row prefix, tokens */

@@ -101,7 +101,8 @@ struct Plan {
   std::vector<DevWg> order;       // dK/dV workgroups, longest first
   int64_t dkdv_grid = 0;          // dK/dV workgroups launched
   int dkdv_lists = 1, dkdv_list_len = 0, dkdv_list_head = 0;   // bf16 (see DkdvParams)
-  int64_t order_cap = 0;          // order entries with every self tile
+  int64_t order_cap = 0;          // 128-key tiles x KV heads, with every self tile
+  int64_t order_alloc = 0;        // order entries with every self tile
   int64_t max_prefix = 0;
   int fwd_splits = 1, dq_splits = 1;
   int xcds = 8;                   // XCDs of the device (workgroup order)
@@ -163,35 +164,31 @@ Topology device_topology() {
 // in 4 splits, 2,320 us in 8); such calls keep two workgroups per compute
 // unit. With more workgroups than compute units, two splits at most are tried
 // (the partials' memory grows with the queries).
-int auto_splits(int64_t base_wgs, int64_t avg_tiles, int64_t max_tiles, int64_t partial_bytes, int cus) {
-  constexpr int64_t kWgTiles = 8, kMergeTiles = 3, kLongTiles = 128;
-  constexpr double kBytesPerTile = 5e6;   // partials written, then read
+struct SplitCost {
+  double wg_tiles, merge_tiles, bytes_per_tile;
+  int64_t long_tiles;
+};
+constexpr SplitCost kBf16Splits{8.0, 3.0, 5e6, 128};   // (partials written, then read)
+// fp32: a tile takes 6-13 us, so the fixed costs weigh less, and a long split
+// is not worth a second round: 4 splits of 64 workgroups' 28 tiles take 131 us
+// in dQ, 8 take 150 us, unsplit 397 us.
+constexpr SplitCost kFp32Splits{1.2, 0.7, 3.5e7, INT64_MAX};
+int auto_splits(const SplitCost &c, int64_t base_wgs, int64_t avg_tiles, int64_t max_tiles, int64_t partial_bytes,
+                int cus) {
   if (base_wgs < 1) return 1;
   const int64_t one_round = std::max<int64_t>(1, cus / base_wgs);
-  if (base_wgs <= cus && ceil_div(max_tiles, one_round) >= kLongTiles)
-    return (int)std::min<int64_t>(ceil_div(2 * (int64_t)cus, base_wgs), kMaxSplits);
   const int64_t cap = base_wgs > cus ? 2 : std::min<int64_t>(kMaxSplits, std::max<int64_t>(1, max_tiles));
+  auto cost = [&](int64_t s) {
+    const double rounds = (double)ceil_div(base_wgs * s, cus) * (c.wg_tiles + (double)ceil_div(avg_tiles, s));
+    const double x = std::max(rounds, c.wg_tiles + (double)ceil_div(max_tiles, s));
+    return s > 1 ? x + c.merge_tiles + (double)s * (double)partial_bytes / c.bytes_per_tile : x;
+  };
+  if (base_wgs <= cus && ceil_div(max_tiles, one_round) >= c.long_tiles)
+    return (int)std::min<int64_t>(ceil_div(2 * (int64_t)cus, base_wgs), kMaxSplits);
   int64_t best = 1;
-  double best_cost = 0.0;
-  for (int64_t s = 1; s <= cap; ++s) {
-    const int64_t rounds = ceil_div(base_wgs * s, cus) * (kWgTiles + ceil_div(avg_tiles, s));
-    double cost = (double)std::max(rounds, kWgTiles + ceil_div(max_tiles, s));
-    if (s > 1) cost += (double)kMergeTiles + (double)s * (double)partial_bytes / kBytesPerTile;
-    if (s == 1 || cost < best_cost) {
-      best = s;
-      best_cost = cost;
-    }
-  }
+  for (int64_t s = 2; s <= cap; ++s)
+    if (cost(s) < cost(best)) best = s;
   return (int)best;
-}
-
-// The same for the fp32 kernels: aim at two workgroups per compute unit.
-int auto_splits_fp32(int64_t base_wgs, int64_t min_row_tiles, int cus) {
-  const int64_t target = 2 * (int64_t)cus;
-  if (base_wgs >= (target * 3) / 4) return 1;
-  int64_t s = ceil_div(target, std::max<int64_t>(1, base_wgs));
-  s = std::min<int64_t>(s, std::max<int64_t>(1, min_row_tiles / 8));
-  return (int)std::max<int64_t>(1, std::min<int64_t>(s, kMaxSplits));
 }
 
 // Workgroups of the bf16 forward and dQ kernels, in dispatch order, with
@@ -320,7 +317,6 @@ cas_status_t build_plan(const cas_problem_t *p, bool bwd, Plan &pl, int fwd_spli
   pl.scale = p->softmax_scale;
 
   const int D = pl.D, es = pl.esize, Hkv = pl.Hkv;
-  int64_t min_row_tiles = INT64_MAX;
   int64_t tblk = 0;
   pl.rows.resize(pl.B);
   for (int b = 0; b < pl.B; ++b) {
@@ -386,38 +382,36 @@ cas_status_t build_plan(const cas_problem_t *p, bool bwd, Plan &pl, int fwd_spli
     }
     pl.rows[b] = r;
     pl.max_prefix = std::max(pl.max_prefix, plen);
-    min_row_tiles = std::min(min_row_tiles, tiles + 1);
   }
 
   const cas_tuning_t tu = tuning();
   const bool bf16 = pl.dt == kBF16;
-  const int rpw_fwd = bf16 ? kBf16RowsPerWg : kRowsPerWg, rpw_dq = bf16 ? kBf16RowsPerWg : kDqRowsPerWg;
-  pl.nqblk_fwd = (int)ceil_div(pl.nrows_max, rpw_fwd);
-  pl.nqblk_dq = (int)ceil_div(pl.nrows_max, rpw_dq);
-  // The grids are sized for the longest row; the split heuristic counts the
-  // workgroups that have rows.
-  int64_t base_fwd = 0, base_dq = 0, sum_tiles = 0, max_tiles = 0;
-  for (int b = 0; b < pl.B; ++b) {
-    const int64_t nrows = (int64_t)pl.len[b] * pl.g;
-    base_fwd += Hkv * ceil_div(nrows, rpw_fwd);
-    base_dq += Hkv * ceil_div(nrows, rpw_dq);
-    // bf16: key tiles that the row's query blocks walk (prefix, then the self
-    // tiles up to the block's last position: half of them on average).
-    const int64_t self = ceil_div(pl.len[b], kKeyTile);
-    sum_tiles += Hkv * ceil_div(nrows, rpw_fwd) * (pl.rows[b].prefix_tiles + (self + 1) / 2);
-    if (nrows > 0) max_tiles = std::max(max_tiles, pl.rows[b].prefix_tiles + self);
-  }
   const Topology topo = device_topology();
   pl.xcds = topo.xcds;
   pl.cus = topo.cus;
-  auto choose = [&](int tuned, int64_t base) {
-    if (tuned > 0) return std::min(tuned, kMaxSplits);
-    if (!bf16) return auto_splits_fp32(base, min_row_tiles, topo.cus);
-    return auto_splits(base, ceil_div(sum_tiles, std::max<int64_t>(1, base)), max_tiles, pl.T * pl.Hq * D * 4, topo.cus);
+  // Plans one pass for workgroups of rpw rows. The grids are sized for the
+  // longest row; the split costs count the workgroups that have rows, and the
+  // key tiles that they walk (prefix, then the self tiles up to the block's
+  // last position: half of them on average).
+  auto plan_splits = [&](const SplitCost &c, int rpw) {
+    int64_t base = 0, sum_tiles = 0, max_tiles = 0;
+    for (int b = 0; b < pl.B; ++b) {
+      if (pl.len[b] == 0) continue;
+      const int64_t blocks = Hkv * ceil_div((int64_t)pl.len[b] * pl.g, rpw), self = ceil_div(pl.len[b], kKeyTile);
+      base += blocks;
+      sum_tiles += blocks * (pl.rows[b].prefix_tiles + (self + 1) / 2);
+      max_tiles = std::max(max_tiles, pl.rows[b].prefix_tiles + self);
+    }
+    return auto_splits(c, base, ceil_div(sum_tiles, std::max<int64_t>(1, base)), max_tiles, pl.T * pl.Hq * D * 4, topo.cus);
   };
-  pl.fwd_splits = choose(tu.fwd_splits, base_fwd);
+  const int rpw_fwd = bf16 ? kBf16RowsPerWg : kFwdRowsPerWg, rpw_dq = bf16 ? kBf16RowsPerWg : kDqRowsPerWg;
+  const SplitCost &sc = bf16 ? kBf16Splits : kFp32Splits;
+  const int fwd_auto = plan_splits(sc, rpw_fwd), dq_auto = rpw_dq == rpw_fwd ? fwd_auto : plan_splits(sc, rpw_dq);
+  pl.fwd_splits = tu.fwd_splits > 0 ? std::min(tu.fwd_splits, kMaxSplits) : fwd_auto;
   if (fwd_split_cap > 0) pl.fwd_splits = std::min(pl.fwd_splits, fwd_split_cap);
-  pl.dq_splits = choose(tu.dq_splits, base_dq);
+  pl.dq_splits = tu.dq_splits > 0 ? std::min(tu.dq_splits, kMaxSplits) : dq_auto;
+  pl.nqblk_fwd = (int)ceil_div(pl.nrows_max, rpw_fwd);
+  pl.nqblk_dq = (int)ceil_div(pl.nrows_max, rpw_dq);
   if ((int64_t)pl.B * Hkv * pl.nqblk_fwd * pl.fwd_splits > INT32_MAX ||
       (int64_t)pl.B * Hkv * pl.nqblk_dq * pl.dq_splits > INT32_MAX)
     return fail(CAS_ERR_UNSUPPORTED, "grid too large");
@@ -492,6 +486,13 @@ cas_status_t build_plan(const cas_problem_t *p, bool bwd, Plan &pl, int fwd_spli
     pl.order_cap = (tiles + self_tiles) * Hkv;
     if (tiles + (int64_t)pl.B * ceil_div(pl.Smax, kDkdvKeyTile) > INT32_MAX / 2 || pl.order_cap > INT32_MAX)
       return fail(CAS_ERR_UNSUPPORTED, "too many key tiles");
+    pl.order_alloc = pl.order_cap;
+    if (!bf16) {
+      pl.order_alloc = 0;
+      for (const DevCart &c : pl.carts) pl.order_alloc += ceil_div(c.len, kDkdvKeyTileFp32) * Hkv;
+      for (int b = 0; b < pl.B; ++b) pl.order_alloc += ceil_div(pl.len[b], kDkdvKeyTileFp32) * Hkv;
+      if (pl.order_alloc > INT32_MAX) return fail(CAS_ERR_UNSUPPORTED, "too many key tiles");
+    }
   }
 
   // Workspace layout.
@@ -510,7 +511,7 @@ cas_status_t build_plan(const cas_problem_t *p, bool bwd, Plan &pl, int fwd_spli
     pl.off_uses = off;
     off = align_up(off + pl.uses.size() * sizeof(int32_t), 256);
     pl.off_order = off;
-    off = align_up(off + (size_t)pl.order_cap * sizeof(DevWg), 256);
+    off = align_up(off + (size_t)pl.order_alloc * sizeof(DevWg), 256);
     pl.off_claim = off;   // claim counters: zero in every table upload
     off = align_up(off + (size_t)pl.xcds * sizeof(int32_t), 256);
   }
@@ -561,20 +562,21 @@ void build_dkdv_order(Plan &pl, bool with_self) {
     DevWg wg() const { return {owner, pos, kvh}; }
   };
   std::vector<E> v;
-  v.reserve((size_t)pl.order_cap);
+  const int key_tile = pl.dt == kBF16 ? kDkdvKeyTile : kDkdvKeyTileFp32;
+  v.reserve((size_t)pl.order_alloc);
   for (size_t i = 0; i < pl.carts.size(); ++i) {
     const DevCart &c = pl.carts[i];
-    const int n = (int)ceil_div(c.len, kDkdvKeyTile);
+    const int n = (int)ceil_div(c.len, key_tile);
     for (int kvh = 0; kvh < pl.Hkv; ++kvh)
       for (int t = 0; t < n; ++t) v.push_back({c.nblk, (int32_t)i, t, kvh});
   }
   if (with_self) {
     for (int b = 0; b < pl.B; ++b) {
       const int64_t nqb = ceil_div((int64_t)pl.len[b] * pl.g, kDkdvQBlock);
-      const int n = (int)ceil_div(pl.len[b], kDkdvKeyTile);
+      const int n = (int)ceil_div(pl.len[b], key_tile);
       for (int kvh = 0; kvh < pl.Hkv; ++kvh)
         for (int j = 0; j < n; ++j)
-          v.push_back({nqb - ((int64_t)j * kDkdvKeyTile * pl.g) / kDkdvQBlock, -1 - b, j, kvh});
+          v.push_back({nqb - ((int64_t)j * key_tile * pl.g) / kDkdvQBlock, -1 - b, j, kvh});
     }
   }
   std::stable_sort(v.begin(), v.end(), [](const E &a, const E &b) {

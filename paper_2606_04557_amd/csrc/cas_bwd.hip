@@ -5,11 +5,11 @@
 //
 // Three passes, all recomputing P from the stored row LSE:
 //   bwd_pre:  D = rowsum(dO * O) and LSE*log2(e) per packed row (fp32).
-//   dkdv:     key-stationary. A workgroup owns 128 keys (4 waves x 32) of one
-//             distinct cartridge (or of one row's self keys) and one kv head;
-//             it loops over every query row of the GQA group in every batch
-//             row that references the cartridge, with Q/dO blocks staged
-//             through LDS:
+//   dkdv:     key-stationary. A workgroup owns 32 keys of one distinct
+//             cartridge (or of one row's self keys) and one kv head; its waves
+//             share out every query row of the GQA group in every batch row
+//             that references the cartridge, with Q/dO blocks staged through
+//             LDS:
 //               S = Q K^T, dP = dO V^T        (K, V held in registers)
 //               P = exp2(S c - LSE2), dS = P (dP - D)
 //               dV^T += dO^T P, dK^T += Q^T dS  (P, dS straight from the C
@@ -59,26 +59,38 @@ __global__ __launch_bounds__(kThreads) void bwd_pre_kernel(PreParams p) {
   }
 }
 
+// 32 keys per workgroup. The four waves share the keys and take every fourth
+// 32-row block of the queries each, staged through a wave's own LDS (no
+// workgroup barrier until their sums meet at the end), with the next block's
+// rows in flight while a block is worked on. Bound by the matrix products of
+// one wave per SIMD: a wave's chain over the queries is a quarter of what it
+// was with 32 keys per wave and 128 per workgroup, and four times the
+// workgroups cover the compute units (2 x 128 keys, 64 queries, d = 64: 33.7 ->
+// 17.5 us; 3 x 400 keys, 400 queries, d = 128, 8 KV heads: 269 -> 187 us).
 template <int D>
 __global__ __launch_bounds__(kThreads) void dkdv_kernel(DkdvParams p) {
   using T = float;
   using M = Mma<T>;
   using Frag = typename M::Frag;
   constexpr int NSTEP = D / M::kStep;
-  constexpr int QB = kDkdvQBlock;
-  constexpr int QSUB = QB / 32;
+  constexpr int RB = 32;                      // query rows of a block
   constexpr int DT = D / 32;
   constexpr int RS = lds_row_stride<T, D>();
+  constexpr int CPR = D / 4;                  // 16-byte chunks per row
+  constexpr int NC = RB * CPR / 64;           // chunks of a block per lane
+  constexpr int WAVE = 2 * RB * RS;           // floats of a wave's Q and dO blocks
+  static_assert(2 * DT * 16 * 64 <= WAVE, "a wave's sums fit where its blocks were");
 
-  __shared__ __attribute__((aligned(16))) T q_row[QB * RS];
-  __shared__ __attribute__((aligned(16))) T do_row[QB * RS];
-  __shared__ float lse2_l[QB];
-  __shared__ float nd_l[QB];
+  __shared__ __attribute__((aligned(16))) T blocks[kWaves * WAVE];
+  __shared__ float stats[kWaves][2][RB];
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int G = lane >> 5, n = lane & 31;
+  T *const q_row = blocks + wave * WAVE;
+  T *const do_row = q_row + RB * RS;
+  float *const lse2_l = stats[wave][0], *const nd_l = stats[wave][1];
   const DevWg wg = p.order[blockIdx.x];
-  const int kvh = wg.kvh, key0 = wg.tile * kDkdvKeyTile;
+  const int kvh = wg.kvh, key0 = wg.tile * kDkdvKeyTileFp32;
   const int g = p.g, Hkv = p.Hkv, Hq = Hkv * g;
   const float c = p.scale_log2;
 
@@ -110,10 +122,49 @@ __global__ __launch_bounds__(kThreads) void dkdv_kernel(DkdvParams p) {
     dvp = p.dv_self ? (T *)p.dv_self + base : nullptr;
     st = (int64_t)Hkv * D;
   }
-  const int wkey0 = key0 + wave * kDkdvKeysPerWave;
-  const int my_key = wkey0 + n;
+  const int my_key = key0 + n;
   const bool key_ok = my_key < klen;
-  const bool wave_has_keys = wkey0 < klen;
+
+  // The wave's blocks: every fourth of the uses' 32-row blocks, in order (self
+  // keys: from the first block that sees the tile's first key).
+  const int blk0 = self ? (key0 * g) / RB : 0;
+  int u = use_b, blk = blk0 + wave, nrows = 0, tok0 = 0;
+  auto open_use = [&]() {
+    const DevRow rw = p.rows[self ? self_b : p.uses[u]];
+    nrows = rw.len * g;
+    tok0 = rw.tok0;
+  };
+  // Moves to the use that holds block blk, counted from the current use.
+  auto settle = [&]() {
+    while (u < use_e) {
+      open_use();
+      const int nb = (nrows + RB - 1) / RB;
+      if (blk < nb) return true;
+      blk -= nb;
+      ++u;
+    }
+    return false;
+  };
+  u32x4 qr[NC], dor[NC];
+  float stat_n[2] = {INFINITY, 0.0f};
+  auto fetch = [&]() {
+    const int r0 = blk * RB, nv = min(RB, nrows - r0);
+    const int64_t head0 = ((int64_t)tok0 * Hq + kvh * g) * D;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      const int ch = lane + 64 * i, r = ch / CPR, cc = ch % CPR;
+      const int rr = r0 + r, t = rr / g;
+      const int64_t off = head0 + ((int64_t)t * Hq + (rr - t * g)) * D + cc * 4;
+      const u32x4 z = {0u, 0u, 0u, 0u};
+      qr[i] = r < nv ? *reinterpret_cast<const u32x4 *>((const T *)p.q + off) : z;
+      dor[i] = r < nv ? *reinterpret_cast<const u32x4 *>((const T *)p.d_o + off) : z;
+    }
+    const int64_t pk = (int64_t)tok0 * Hq + (int64_t)kvh * nrows + r0 + n;
+    stat_n[0] = n < nv ? p.lse2[pk] : INFINITY;
+    stat_n[1] = n < nv ? p.nd[pk] : 0.0f;
+  };
+  bool more = settle();
+  if (more) fetch();
 
   Frag kf[NSTEP], vf[NSTEP];
 #pragma unroll
@@ -128,88 +179,95 @@ __global__ __launch_bounds__(kThreads) void dkdv_kernel(DkdvParams p) {
     dv[dt] = zero16();
   }
 
-  const int qb0 = self ? (key0 * g) / QB : 0;
-  for (int u = use_b; u < use_e; ++u) {
-    const int b = self ? self_b : p.uses[u];
-    const DevRow rw = p.rows[b];
-    const int nrows = rw.len * g;
-    const int nqb = (nrows + QB - 1) / QB;
-    const T *qb_base = (const T *)p.q + ((int64_t)rw.tok0 * Hq + kvh * g) * D;
-    const T *dob_base = (const T *)p.d_o + ((int64_t)rw.tok0 * Hq + kvh * g) * D;
-    const float *lse2_b = p.lse2 + (int64_t)rw.tok0 * Hq + (int64_t)kvh * nrows;
-    const float *nd_b = p.nd + (int64_t)rw.tok0 * Hq + (int64_t)kvh * nrows;
-    for (int qb = qb0; qb < nqb; ++qb) {
-      const int r0 = qb * QB;
-      const int nv = min(QB, nrows - r0);
-      auto qptr = [&](int r) {
-        const int rr = r0 + r, t = rr / g;
-        return qb_base + ((int64_t)t * Hq + (rr - t * g)) * D;
-      };
-      auto doptr = [&](int r) {
-        const int rr = r0 + r, t = rr / g;
-        return dob_base + ((int64_t)t * Hq + (rr - t * g)) * D;
-      };
-      __syncthreads();
-      load_rows<T, D, QB>(q_row, qptr, nv, tid);
-      load_rows<T, D, QB>(do_row, doptr, nv, tid);
-      if (tid < QB) {
-        const int rr = r0 + tid;
-        lse2_l[tid] = rr < nrows ? lse2_b[rr] : INFINITY;
-        nd_l[tid] = rr < nrows ? nd_b[rr] : 0.0f;
-      }
-      __syncthreads();
-      if (!wave_has_keys) continue;
-      const int blk_t_lo = r0 / g, blk_t_hi = (r0 + nv - 1) / g;
-      if (self && wkey0 > blk_t_hi) continue;
-      const bool need_mask = self && (wkey0 + kDkdvKeysPerWave - 1 > blk_t_lo);
-
+  while (more) {
+    const int r0 = blk * RB, nv = min(RB, nrows - r0);
 #pragma unroll
-      for (int qs = 0; qs < QSUB; ++qs) {
-        f32x16 sa = zero16(), dpa = zero16();
-#pragma unroll
-        for (int s = 0; s < NSTEP; ++s) {
-          sa = M::run(row_frag<T, D>(q_row, 32 * qs + n, s, G), kf[s], sa);
-          dpa = M::run(row_frag<T, D>(do_row, 32 * qs + n, s, G), vf[s], dpa);
-        }
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-          const int ql = 32 * qs + crow(j, G);
-          float pv = exp2f(fmaf(sa[j], c, -lse2_l[ql]));
-          if (need_mask) pv = (my_key <= (r0 + ql) / g) ? pv : 0.0f;
-          pv = key_ok ? pv : 0.0f;
-          const float ds = pv * (dpa[j] + nd_l[ql]);
-          sa[j] = pv;
-          dpa[j] = ds;
-        }
-#pragma unroll
-        for (int s = 0; s < 16; ++s)
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt) {
-            dv[dt] = M::run(trans_frag_f32<D>(do_row, qs, s, G, dt * 32 + n), sa[s], dv[dt]);
-            dk[dt] = M::run(trans_frag_f32<D>(q_row, qs, s, G, dt * 32 + n), dpa[s], dk[dt]);
-          }
-      }
+    for (int i = 0; i < NC; ++i) {
+      const int ch = lane + 64 * i, r = ch / CPR, cc = ch % CPR;
+      *reinterpret_cast<u32x4 *>(q_row + r * RS + cc * 4) = qr[i];
+      *reinterpret_cast<u32x4 *>(do_row + r * RS + cc * 4) = dor[i];
     }
+    if (G == 0) {
+      lse2_l[n] = stat_n[0];
+      nd_l[n] = stat_n[1];
+    }
+    // The wave's own LDS writes, then reads of them by its other lanes.
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    blk += kWaves;
+    more = settle();
+    if (more) fetch();
+    // (Self keys: the first block sees the tile's first key.)
+    const bool need_mask = self && key0 + kDkdvKeyTileFp32 - 1 > r0 / g;
+
+    f32x16 sa = zero16(), dpa = zero16();
+#pragma unroll
+    for (int s = 0; s < NSTEP; ++s) {
+      sa = M::run(row_frag<T, D>(q_row, n, s, G), kf[s], sa);
+      dpa = M::run(row_frag<T, D>(do_row, n, s, G), vf[s], dpa);
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      const int ql = crow(j, G);
+      float pv = exp2f(fmaf(sa[j], c, -lse2_l[ql]));
+      if (need_mask) pv = (my_key <= (r0 + ql) / g) ? pv : 0.0f;
+      pv = key_ok ? pv : 0.0f;
+      const float ds = pv * (dpa[j] + nd_l[ql]);
+      sa[j] = pv;
+      dpa[j] = ds;
+    }
+#pragma unroll
+    for (int s = 0; s < 16; ++s)
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) {
+        dv[dt] = M::run(trans_frag_f32<D>(do_row, 0, s, G, dt * 32 + n), sa[s], dv[dt]);
+        dk[dt] = M::run(trans_frag_f32<D>(q_row, 0, s, G, dt * 32 + n), dpa[s], dk[dt]);
+      }
+    // Reads of this block before the next block's writes.
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
 
-  if (!key_ok) return;
-  const float sc = p.scale;
+  // The waves' sums meet in LDS, [sum][register][lane] per wave (each wave
+  // writes where its own blocks were); wave w adds up and stores sums w, w + 4,
+  // ... of the DT dK and DT dV ones.
+  T *const mine = q_row;
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const int d0 = dt * 32 + jj * 8 + G * 4;
-      if (dkp)
-        store4(dkp + my_key * st + d0, dk[dt][jj * 4 + 0] * sc, dk[dt][jj * 4 + 1] * sc,
-               dk[dt][jj * 4 + 2] * sc, dk[dt][jj * 4 + 3] * sc);
-      if (dvp)
-        store4(dvp + my_key * st + d0, dv[dt][jj * 4 + 0], dv[dt][jj * 4 + 1], dv[dt][jj * 4 + 2],
-               dv[dt][jj * 4 + 3]);
+    for (int j = 0; j < 16; ++j) {
+      mine[(dt * 16 + j) * 64 + lane] = dk[dt][j];
+      mine[((DT + dt) * 16 + j) * 64 + lane] = dv[dt][j];
     }
+  __syncthreads();
+  const float sc = p.scale;
+  for (int x = wave; x < 2 * DT; x += kWaves) {
+    float sum[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      sum[j] = 0.0f;
+#pragma unroll
+      for (int v = 0; v < kWaves; ++v) sum[j] += blocks[v * WAVE + (x * 16 + j) * 64 + lane];
+    }
+    const bool is_dk = x < DT;
+    T *const dst = is_dk ? dkp : dvp;
+    const float m = is_dk ? sc : 1.0f;
+    const int dt = is_dk ? x : x - DT;
+    if (dst && key_ok) {
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj)
+        store4(dst + my_key * st + dt * 32 + jj * 8 + G * 4, sum[jj * 4 + 0] * m, sum[jj * 4 + 1] * m, sum[jj * 4 + 2] * m,
+               sum[jj * 4 + 3] * m);
+    }
+  }
 }
 
+// As in the forward, the next tile's rows are loaded while a tile is worked on,
+// and with 64 channels two workgroups share a compute unit.
 template <int D>
-__global__ __launch_bounds__(kThreads) void dq_kernel(DqParams p) {
+__global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void dq_kernel(DqParams p) {
   using T = float;
   using M = Mma<T>;
   using Frag = typename M::Frag;
@@ -284,12 +342,15 @@ __global__ __launch_bounds__(kThreads) void dq_kernel(DqParams p) {
   const int te = (int)((int64_t)ntiles * (split + 1) / p.splits);
   int seg = row.seg_begin;
 
-  for (int tile = tb; tile < te; ++tile) {
+  // Where the rows of a tile are; asked for in increasing order.
+  struct Tile {
     const T *kp;
     const T *vp;
     int64_t st;
-    int nvalid;
-    int self0 = -1;
+    int nvalid, self0;
+  };
+  auto locate = [&](int tile) {
+    Tile x;
     if (tile < ptiles) {
       for (;;) {
         const DevSeg sd = p.segs[seg];
@@ -298,21 +359,40 @@ __global__ __launch_bounds__(kThreads) void dq_kernel(DqParams p) {
       }
       const DevSeg sd = p.segs[seg];
       const int key0 = (tile - sd.tile_begin) * KT;
-      kp = (const T *)sd.k + kvh * sd.stride_head + (int64_t)key0 * sd.stride_tok;
-      vp = (const T *)sd.v + kvh * sd.stride_head + (int64_t)key0 * sd.stride_tok;
-      st = sd.stride_tok;
-      nvalid = min(KT, sd.len - key0);
+      x.kp = (const T *)sd.k + kvh * sd.stride_head + (int64_t)key0 * sd.stride_tok;
+      x.vp = (const T *)sd.v + kvh * sd.stride_head + (int64_t)key0 * sd.stride_tok;
+      x.st = sd.stride_tok;
+      x.nvalid = min(KT, sd.len - key0);
+      x.self0 = -1;
     } else {
-      self0 = (tile - ptiles) * KT;
-      kp = (const T *)p.k_self + (((int64_t)tok0 + self0) * Hkv + kvh) * D;
-      vp = (const T *)p.v_self + (((int64_t)tok0 + self0) * Hkv + kvh) * D;
-      st = (int64_t)Hkv * D;
-      nvalid = min(KT, len - self0);
+      x.self0 = (tile - ptiles) * KT;
+      x.kp = (const T *)p.k_self + (((int64_t)tok0 + x.self0) * Hkv + kvh) * D;
+      x.vp = (const T *)p.v_self + (((int64_t)tok0 + x.self0) * Hkv + kvh) * D;
+      x.st = (int64_t)Hkv * D;
+      x.nvalid = min(KT, len - x.self0);
     }
+    return x;
+  };
+  RowTile<T, D, KT> kr, vr;
+  auto fetch = [&](const Tile &x) {
+    kr.fetch([&](int r) { return x.kp + r * x.st; }, x.nvalid, tid);
+    vr.fetch([&](int r) { return x.vp + r * x.st; }, x.nvalid, tid);
+  };
+  Tile next{};
+  if (tb < te) {
+    next = locate(tb);
+    fetch(next);
+  }
+  for (int tile = tb; tile < te; ++tile) {
+    const int nvalid = next.nvalid, self0 = next.self0;
     __syncthreads();
-    load_rows<T, D, KT>(k_row, [&](int r) { return kp + r * st; }, nvalid, tid);
-    load_rows<T, D, KT>(v_row, [&](int r) { return vp + r * st; }, nvalid, tid);
+    kr.put(k_row, tid);
+    vr.put(v_row, tid);
     __syncthreads();
+    if (tile + 1 < te) {
+      next = locate(tile + 1);
+      fetch(next);
+    }
 
     if (!wave_active) continue;
     if (self0 >= 0 && self0 > wave_t_hi) continue;

@@ -116,30 +116,37 @@ __device__ __forceinline__ float trans_frag_f32(const float *tile, int sub, int 
 // or beyond `nvalid` are never read and are stored as zeros.
 // ---------------------------------------------------------------------------
 
-template <typename T, int D, int R, typename RowPtr>
-__device__ __forceinline__ void load_rows(T *tile, RowPtr rowptr, int nvalid, int tid) {
-  constexpr int CH = 16 / (int)sizeof(T);     // elements per 16-byte chunk
-  constexpr int CPR = D / CH;                 // chunks per row
-  constexpr int TOTAL = R * CPR;
-  constexpr int RS = lds_row_stride<T, D>();
+// In two halves, so that a tile's loads can be in flight while the tile before
+// is worked on: fetch() into registers, put() from there into the LDS tile.
+template <typename T, int D, int R>
+struct RowTile {
+  static constexpr int CH = 16 / (int)sizeof(T);     // elements per 16-byte chunk
+  static constexpr int CPR = D / CH;                 // chunks per row
+  static constexpr int TOTAL = R * CPR;
   static_assert(TOTAL % kThreads == 0, "tile must split evenly over the workgroup");
   u32x4 buf[TOTAL / kThreads];
-#pragma unroll
-  for (int i = 0; i < TOTAL / kThreads; ++i) {
-    const int c = tid + i * kThreads;
-    const int r = c / CPR, cc = c % CPR;
-    u32x4 v = {0u, 0u, 0u, 0u};
-    if (r < nvalid) v = *reinterpret_cast<const u32x4 *>(rowptr(r) + cc * CH);
-    buf[i] = v;
-  }
-#pragma unroll
-  for (int i = 0; i < TOTAL / kThreads; ++i) {
-    const int c = tid + i * kThreads;
-    const int r = c / CPR, cc = c % CPR;
-    *reinterpret_cast<u32x4 *>(tile + r * RS + cc * CH) = buf[i];
-  }
-}
 
+  template <typename RowPtr>
+  __device__ __forceinline__ void fetch(RowPtr rowptr, int nvalid, int tid) {
+#pragma unroll
+    for (int i = 0; i < TOTAL / kThreads; ++i) {
+      const int c = tid + i * kThreads;
+      const int r = c / CPR, cc = c % CPR;
+      u32x4 v = {0u, 0u, 0u, 0u};
+      if (r < nvalid) v = *reinterpret_cast<const u32x4 *>(rowptr(r) + cc * CH);
+      buf[i] = v;
+    }
+  }
+  __device__ __forceinline__ void put(T *tile, int tid) const {
+    constexpr int RS = lds_row_stride<T, D>();
+#pragma unroll
+    for (int i = 0; i < TOTAL / kThreads; ++i) {
+      const int c = tid + i * kThreads;
+      const int r = c / CPR, cc = c % CPR;
+      *reinterpret_cast<u32x4 *>(tile + r * RS + cc * CH) = buf[i];
+    }
+  }
+};
 
 __device__ __forceinline__ float xor32(float v) { return __shfl_xor(v, 32, 64); }
 

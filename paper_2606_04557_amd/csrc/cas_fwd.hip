@@ -1,6 +1,6 @@
 // Forward of multi-cartridge prefix attention on gfx950.
 //
-// One workgroup owns 256 packed query rows (4 waves x 64) of one (batch row,
+// One workgroup owns 128 packed query rows (4 waves x 32) of one (batch row,
 // kv head) and walks that row's key axis -- every cartridge segment in table
 // order, then the causal self keys -- in 64-key tiles staged through LDS. The
 // GQA group's query heads share each tile. Per tile and wave:
@@ -20,13 +20,21 @@
 
 namespace cas {
 
+//
+// The next tile's rows are loaded while the current tile is worked on. Bound by
+// the matrix products of one wave per SIMD (64 cycles each): 32 rows per wave
+// with the loads ahead take 5.8 us a tile of 64 channels and 9.4 of 128, where
+// 64 rows without them took 13.2 and 21, and leave twice the workgroups (of
+// which two share a compute unit with 64 channels). Together with the splits:
+// 64 queries over 2 x 128 keys, d = 64: 73.6 -> 13.6 us and a 4 us merge; 400
+// queries over 3 x 400 keys, d = 128, 8 KV heads: 350 -> 86 us and 4 us.
 template <int D>
-__global__ __launch_bounds__(kThreads) void fwd_kernel(FwdParams p) {
+__global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void fwd_kernel(FwdParams p) {
   using T = float;
   using M = Mma<T>;
   using Frag = typename M::Frag;
   constexpr int NSTEP = D / M::kStep;
-  constexpr int QS = kRowsPerWave / 32;
+  constexpr int QS = kFwdRowsPerWave / 32;
   constexpr int KT = kKeyTile;
   constexpr int NSUB = KT / 32;
   constexpr int DT = D / 32;
@@ -48,13 +56,13 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(FwdParams p) {
   const int g = p.g, Hkv = p.Hkv, Hq = Hkv * g;
   const DevRow row = p.rows[b];
   const int tok0 = row.tok0, len = row.len, nrows = len * g;
-  const int wg_row0 = qblk * kRowsPerWg;
+  const int wg_row0 = qblk * kFwdRowsPerWg;
   if (wg_row0 >= nrows) return;   // grid sized for the longest row
-  const int wg_row1 = min(nrows, wg_row0 + kRowsPerWg);
-  const int row0 = wg_row0 + wave * kRowsPerWave;
+  const int wg_row1 = min(nrows, wg_row0 + kFwdRowsPerWg);
+  const int row0 = wg_row0 + wave * kFwdRowsPerWave;
   const bool wave_active = row0 < nrows;
   const int wave_t_lo = row0 / g;
-  const int wave_t_hi = (min(row0 + kRowsPerWave, nrows) - 1) / g;
+  const int wave_t_hi = (min(row0 + kFwdRowsPerWave, nrows) - 1) / g;
   const int wg_t_hi = (wg_row1 - 1) / g;
   const float c = p.scale_log2;
 
@@ -91,12 +99,15 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(FwdParams p) {
   const int te = (int)((int64_t)ntiles * (split + 1) / p.splits);
   int seg = row.seg_begin;
 
-  for (int tile = tb; tile < te; ++tile) {
+  // Where the rows of a tile are; asked for in increasing order.
+  struct Tile {
     const T *kp;
     const T *vp;
     int64_t st;
-    int nvalid;
-    int self0 = -1;
+    int nvalid, self0;
+  };
+  auto locate = [&](int tile) {
+    Tile x;
     if (tile < ptiles) {
       for (;;) {
         const DevSeg sd = p.segs[seg];
@@ -105,21 +116,40 @@ __global__ __launch_bounds__(kThreads) void fwd_kernel(FwdParams p) {
       }
       const DevSeg sd = p.segs[seg];
       const int key0 = (tile - sd.tile_begin) * KT;
-      kp = (const T *)sd.k + kvh * sd.stride_head + (int64_t)key0 * sd.stride_tok;
-      vp = (const T *)sd.v + kvh * sd.stride_head + (int64_t)key0 * sd.stride_tok;
-      st = sd.stride_tok;
-      nvalid = min(KT, sd.len - key0);
+      x.kp = (const T *)sd.k + kvh * sd.stride_head + (int64_t)key0 * sd.stride_tok;
+      x.vp = (const T *)sd.v + kvh * sd.stride_head + (int64_t)key0 * sd.stride_tok;
+      x.st = sd.stride_tok;
+      x.nvalid = min(KT, sd.len - key0);
+      x.self0 = -1;
     } else {
-      self0 = (tile - ptiles) * KT;
-      kp = (const T *)p.k_self + (((int64_t)tok0 + self0) * Hkv + kvh) * D;
-      vp = (const T *)p.v_self + (((int64_t)tok0 + self0) * Hkv + kvh) * D;
-      st = (int64_t)Hkv * D;
-      nvalid = min(KT, len - self0);
+      x.self0 = (tile - ptiles) * KT;
+      x.kp = (const T *)p.k_self + (((int64_t)tok0 + x.self0) * Hkv + kvh) * D;
+      x.vp = (const T *)p.v_self + (((int64_t)tok0 + x.self0) * Hkv + kvh) * D;
+      x.st = (int64_t)Hkv * D;
+      x.nvalid = min(KT, len - x.self0);
     }
+    return x;
+  };
+  RowTile<T, D, KT> kr, vr;
+  auto fetch = [&](const Tile &x) {
+    kr.fetch([&](int r) { return x.kp + r * x.st; }, x.nvalid, tid);
+    vr.fetch([&](int r) { return x.vp + r * x.st; }, x.nvalid, tid);
+  };
+  Tile next{};
+  if (tb < te) {
+    next = locate(tb);
+    fetch(next);
+  }
+  for (int tile = tb; tile < te; ++tile) {
+    const int nvalid = next.nvalid, self0 = next.self0;
     __syncthreads();
-    load_rows<T, D, KT>(k_lds, [&](int r) { return kp + r * st; }, nvalid, tid);
-    load_rows<T, D, KT>(v_lds, [&](int r) { return vp + r * st; }, nvalid, tid);
+    kr.put(k_lds, tid);
+    vr.put(v_lds, tid);
     __syncthreads();
+    if (tile + 1 < te) {
+      next = locate(tile + 1);
+      fetch(next);
+    }
 
     if (!wave_active) continue;
     if (self0 >= 0 && self0 > wave_t_hi) continue;

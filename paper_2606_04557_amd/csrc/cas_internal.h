@@ -11,14 +11,15 @@ namespace cas {
 // Work decomposition (gfx950: 64-lane waves, 4 SIMDs per CU).
 constexpr int kThreads = 256;       // 4 waves per workgroup
 constexpr int kWaves = kThreads / 64;
-constexpr int kRowsPerWave = 64;    // packed query rows a wave owns in fwd / dQ
-constexpr int kRowsPerWg = kRowsPerWave * kWaves;   // 256
+// fp32: packed query rows of a forward or dQ workgroup.
+constexpr int kFwdRowsPerWave = 32;
+constexpr int kFwdRowsPerWg = kFwdRowsPerWave * kWaves;   // 128
 constexpr int kDqRowsPerWave = 32;  // dQ holds Q, dO and the dQ sums in registers
 constexpr int kDqRowsPerWg = kDqRowsPerWave * kWaves;  // 128
 constexpr int kKeyTile = 64;        // keys per LDS tile in fwd / dQ
-constexpr int kDkdvKeysPerWave = 32;
-constexpr int kDkdvKeyTile = kDkdvKeysPerWave * kWaves;  // 128 keys per dK/dV workgroup
-constexpr int kDkdvQBlock = 64;     // query rows per LDS block in dK/dV
+constexpr int kDkdvKeyTile = 128;   // keys per bf16 dK/dV entry
+constexpr int kDkdvKeyTileFp32 = 32;   // keys per fp32 dK/dV workgroup
+constexpr int kDkdvQBlock = 64;     // query rows per LDS block in the bf16 dK/dV
 constexpr int kMaxSplits = 32;
 
 // A "packed row" r of (batch b, kv head kvh) is query position t = r / g of
@@ -75,7 +76,7 @@ struct DevCart {
   int32_t nblk;         // 64-row query blocks over all uses (sum of the rows' block counts)
 };
 
-// One entry of dK/dV work: 128-key tile `tile` of distinct cartridge `owner`
+// One entry of dK/dV work: 128-key (fp32: 32-key) tile `tile` of distinct cartridge `owner`
 // (or, for owner = -1 - b, of batch row b's self keys) at KV head kvh. The host
 // lists them longest first (most query blocks).
 struct DevWg {

@@ -141,6 +141,19 @@ def test_split_merge_counts(D, splits):
         cas.set_tuning(0, 0)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("q_len,g", [(1, 1), (31, 1), (32, 1), (43, 3), (64, 2), (129, 1)])
+def test_fp32_block_edges(D, q_len, g):
+    """fp32 around the edges of its 32-row blocks (shared out over a
+    workgroup's waves, across the rows that use a cartridge), 32-key dK/dV
+    tiles and 128-row workgroups; one cartridge is used by every row and twice
+    by one."""
+    wl = casgen.custom("edges", "fp32", batch=3, q_len=q_len, num_q_heads=2 * g, num_kv_heads=2, head_dim=D,
+                       cart_lens=[1, 31, 32, 33, 65, 200], rows=[[0, 3, 5], [3, 1, 2, 3], [4, 3]], seed=230 + q_len,
+                       cart_std=0.5)
+    _check_full(GpuCase(wl), f"edges {q_len}")
+
+
 def test_wide_token_stride():
     """A 1,024-token cartridge stored with a token stride of 2^21 elements
     (4 MiB), so that its keys and gradients span 4 GiB: byte offsets within a
