@@ -330,9 +330,16 @@ class DecodeProblem:
         self._kv = (ctypes.c_int32 * max(B, 1))(*[int(x) for x in kv_lens])
         self._po = (ctypes.c_int32 * (B + 1))(*po)
         self._ids = (ctypes.c_int32 * max(len(ids), 1))(*ids)
-        # Workspace bytes of the last call; only a first guess for the next
-        # (the library checks it, and the size is asked for again if it fails).
-        self.ws_bytes = 0
+        # Workspace bytes to offer a call that brings none: the tables and about
+        # as many partials of every row as the longest request is cut into
+        # (pieces of 8 to 16 tiles of 32 keys), or what the library last asked
+        # for. A guess: the library checks it, and its size is asked for if it
+        # does not do (0: ask at once). Asking plans the call a second time.
+        tiles = [-(-int(x) // 32) for x in kv_lens]
+        per_wg = min(16, max(8, sum(tiles) * num_kv_heads // 512))
+        parts = min(64, max(tiles, default=0) // per_wg + 6)
+        guess = (1 << 18) + 4 * len(ids) + parts * self.Tq * num_kv_heads * group_size * (4 * head_dim + 4)
+        self.ws_bytes = guess if guess <= 64 << 20 else 0
         I = ctypes.POINTER(ctypes.c_int32)
         self.c = _lib.DecodeProblem(B, num_kv_heads, group_size, head_dim, float(softmax_scale), page_size,
                                     int(num_pages), ctypes.cast(self._qo, I), ctypes.cast(self._kv, I),

@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <map>
 #include <memory>
 #include <mutex>
@@ -916,19 +917,95 @@ cas_status_t check_workspace(void *ws, size_t have, size_t need) {
 // ---------------------------------------------------------------------------
 // Paged decode: validation, key-axis split planning and launch tables.
 // ---------------------------------------------------------------------------
-constexpr int kMaxDecSplits = 64;
+constexpr int kMaxDecParts = 64;   // partials of one request
 
 struct DecodePlan {
   int Tq = 0, Hq = 0;
-  std::vector<DevDecodeReq> reqs;
+  std::vector<DevDecodeRow> rows;
   std::vector<DevDecodeWork> work;
-  std::vector<int32_t> tok_nsplit;
-  int max_split = 1;
+  std::vector<int32_t> tok_parts;
+  int max_parts = 1;
   // 16-row blocks of one workgroup: 2 when a request has more than 16 packed
-  // rows, so that those share one pass over the request's K and V.
+  // rows, or when that shares enough page runs between more requests, so that
+  // those rows take one pass over the keys.
   int row_blocks = 1;
-  size_t off_work = 0, off_pages = 0, off_toksplit = 0, off_plse = 0, off_po = 0, bytes = 0;
+  size_t off_work = 0, off_pages = 0, off_tokparts = 0, off_plse = 0, off_po = 0, bytes = 0;
 };
+
+// A run of consecutive page ids that several requests read: page_ids[page0 ..
+// page0 + npages) of its first reader, and the (request, index of the run in
+// its page list) of every reader.
+struct SharedRun {
+  int32_t page0, npages;
+  std::vector<std::pair<int32_t, int32_t>> users;
+  int64_t saved[2] = {0, 0};   // tiles of one KV head saved in blocks of 16 and of 32 rows
+};
+
+// Runs of at least min_pages that are read at least twice. The pages that every
+// query of a request sees (the first safe_pages of its list) fall into
+// stretches of consecutive ids (a cartridge's pages, usually); the ends of all
+// stretches cut the id axis into intervals, each read whole by the same
+// stretches. Lists whose stretches are short (pages scattered over the pool)
+// share nothing here, nor does a call in which a stretch holds more than
+// kMaxDecParts runs. Costs one scan of the lists and a sort of the ends: of
+// the 70 us that planning 64 requests with 16,640 pages and 65 runs takes on
+// one host core, 27 (without anything shared 6 of 24).
+std::vector<SharedRun> shared_runs(const cas_decode_problem_t *p, const std::vector<int32_t> &safe_pages,
+                                   int min_pages) {
+  struct Stretch {
+    int32_t id0, id1, b, at;   // pages [id0, id1) from index `at` of request b's list
+  };
+  std::vector<Stretch> st;
+  for (int b = 0; b < p->batch; ++b) {
+    const int32_t *ids = p->page_ids + p->page_offsets[b];
+    const int32_t n = safe_pages[b];
+    for (int32_t i = 0; i < n;) {
+      int32_t e = i + 1;
+      for (; e + 16 <= n; e += 16) {
+        int32_t off = 0;
+        for (int k = 0; k < 16; ++k) off |= ids[e + k] ^ (ids[i] + (e - i) + k);
+        if (off) break;
+      }
+      while (e < n && ids[e] == ids[e - 1] + 1) ++e;
+      if (e - i >= min_pages) st.push_back({ids[i], ids[i] + (e - i), b, i});
+      i = e;
+    }
+  }
+  std::vector<SharedRun> runs;
+  if (st.size() < 2) return runs;
+  std::vector<int32_t> ends;
+  ends.reserve(2 * st.size());
+  for (const Stretch &x : st) {
+    ends.push_back(x.id0);
+    ends.push_back(x.id1);
+  }
+  std::sort(ends.begin(), ends.end());
+  ends.erase(std::unique(ends.begin(), ends.end()), ends.end());
+  auto index = [&](int32_t id) { return std::lower_bound(ends.begin(), ends.end(), id) - ends.begin(); };
+  std::vector<int32_t> readers(ends.size(), 0);   // of interval [ends[k], ends[k + 1]): summed from the differences
+  for (const Stretch &x : st) {
+    ++readers[index(x.id0)];
+    --readers[index(x.id1)];
+  }
+  std::vector<int32_t> starts;                    // first page of every run
+  for (size_t k = 0; k + 1 < ends.size(); ++k) {
+    if (k > 0) readers[k] += readers[k - 1];
+    if (readers[k] >= 2 && ends[k + 1] - ends[k] >= min_pages) {
+      starts.push_back(ends[k]);
+      runs.push_back({0, ends[k + 1] - ends[k], {}});
+    }
+  }
+  for (const Stretch &x : st) {
+    size_t r = std::lower_bound(starts.begin(), starts.end(), x.id0) - starts.begin();
+    for (int held = 0; r < starts.size() && starts[r] < x.id1; ++r, ++held) {
+      if (held == kMaxDecParts) return {};
+      const int32_t i = x.at + (starts[r] - x.id0);
+      if (runs[r].users.empty()) runs[r].page0 = p->page_offsets[x.b] + i;
+      runs[r].users.push_back({x.b, i});
+    }
+  }
+  return runs;
+}
 
 cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
   if (!p) return fail(CAS_ERR_INVALID_ARGUMENT, "problem is NULL");
@@ -966,68 +1043,212 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
   dp.Tq = (int)Tq;
   dp.Hq = (int)Hq;
   const int g = p->group_size, Hkv = p->num_kv_heads;
-  // Split planning: workgroups of at least 8 tiles (two per wave), about as
-  // many as the compute units hold at once (two each), so the whole step
-  // runs in one round of workgroups when the requests allow it.
-  for (int b = 0; b < B; ++b)
-    if ((int64_t)(p->q_offsets[b + 1] - p->q_offsets[b]) * g > kDecRows) dp.row_blocks = 2;
-  const int rows_per_wg = kDecRows * dp.row_blocks;
-  int64_t total = 0;
+  // Packed rows and row blocks (of 16 and of 32) of every request.
+  std::vector<int32_t> rows_of(B), blocks_of[2];
+  int32_t rows_max = 0;
+  for (int nb = 1; nb <= 2; ++nb) blocks_of[nb - 1].resize(B);
   for (int b = 0; b < B; ++b) {
-    const int64_t n = p->q_offsets[b + 1] - p->q_offsets[b];
-    total += ceil_div(p->kv_lens[b], kDecTile) * Hkv * ceil_div(n * g, rows_per_wg);
+    rows_of[b] = (p->q_offsets[b + 1] - p->q_offsets[b]) * g;
+    blocks_of[0][b] = (int32_t)(((int64_t)rows_of[b] + kDecRows - 1) / kDecRows);
+    blocks_of[1][b] = (blocks_of[0][b] + 1) / 2;
+    rows_max = std::max(rows_max, rows_of[b]);
   }
-  const int64_t per_wg = std::max<int64_t>(8, ceil_div(total, 2 * (int64_t)device_topology().cus));
-  dp.reqs.resize(B);
-  dp.tok_nsplit.resize(Tq);
-  struct W {
-    int64_t tiles;
-    DevDecodeWork w;
-  };
-  std::vector<W> work;
+  dp.row_blocks = rows_max > kDecRows ? 2 : 1;
+  // Page runs shared between requests (typically whole cartridges) are streamed
+  // once per 16 or 32 rows of all their readers instead of once per reader. A
+  // run is worth it from kMinSharedTiles tiles (a workgroup with a partial of
+  // its own costs about three tiles), the call when it streams at most 0.85 of
+  // the tiles; two row blocks instead of one have to save another tenth.
+  constexpr int kMinSharedTiles = 8;
+  std::vector<SharedRun> runs;
+  if (B > 1 && Tq * g <= (1 << 14)) {   // (longer query blocks would only grow the table of rows)
+    std::vector<int32_t> safe(B);
+    for (int b = 0; b < B; ++b) {
+      // The first query of a request sees keys 0 .. kv_len - n.
+      const int32_t n = p->q_offsets[b + 1] - p->q_offsets[b];
+      safe[b] = (p->kv_lens[b] - n + 1) / P;
+    }
+    runs = shared_runs(p, safe, std::max<int>(1, kMinSharedTiles * kDecTile / P));
+  }
+  // Streamed key tiles of one KV head, every request on its own and with what
+  // the shared runs save, in blocks of 16 and of 32 rows.
+  int64_t t_alone[2] = {0, 0}, t_shared[2];
   for (int b = 0; b < B; ++b) {
-    const int n = p->q_offsets[b + 1] - p->q_offsets[b];
     const int64_t nt = ceil_div(p->kv_lens[b], kDecTile);
-    const int ns = (int)std::min<int64_t>(kMaxDecSplits, ceil_div(nt, per_wg));
-    DevDecodeReq &r = dp.reqs[b];
-    r.q0 = p->q_offsets[b];
-    r.n = n;
-    r.kv_len = p->kv_lens[b];
-    r.page0 = p->page_offsets[b];
-    dp.max_split = std::max(dp.max_split, ns);
-    for (int t = 0; t < n; ++t) dp.tok_nsplit[r.q0 + t] = ns;
-    for (int kvh = 0; kvh < Hkv; ++kvh)
-      for (int row0 = 0; row0 < n * g; row0 += rows_per_wg)
-        for (int s = 0; s < ns; ++s) {
-          DevDecodeWork d{};
-          d.b = b;
-          d.kvh = kvh;
-          d.row0 = row0;
-          d.split = ns > 1 ? s : -1;
-          d.tile0 = (int)(nt * s / ns);
-          d.tile1 = (int)(nt * (s + 1) / ns);
-          work.push_back({d.tile1 - d.tile0, d});
-        }
+    for (int k = 0; k < 2; ++k) t_alone[k] += nt * blocks_of[k][b];
   }
-  if (work.size() > (size_t)INT32_MAX) return fail(CAS_ERR_UNSUPPORTED, "too many workgroups");
-  // Longest ranges first.
-  std::stable_sort(work.begin(), work.end(), [](const W &a, const W &b) { return a.tiles > b.tiles; });
-  dp.work.resize(work.size());
-  for (size_t i = 0; i < work.size(); ++i) dp.work[i] = work[i].w;
-  size_t off = align_up(dp.reqs.size() * sizeof(DevDecodeReq), 256);
+  for (int k = 0; k < 2; ++k) t_shared[k] = t_alone[k];
+  for (SharedRun &r : runs) {
+    int64_t rows = 0, blocks[2] = {0, 0};
+    for (const auto &u : r.users) {
+      rows += rows_of[u.first];
+      for (int k = 0; k < 2; ++k) blocks[k] += blocks_of[k][u.first];
+    }
+    const int64_t nt = ceil_div((int64_t)r.npages * P, kDecTile);
+    for (int k = 0; k < 2; ++k) {
+      r.saved[k] = std::max<int64_t>(0, blocks[k] - ceil_div(rows, kDecRows * (k + 1))) * nt;
+      t_shared[k] -= r.saved[k];
+    }
+  }
+  int nb_shared = dp.row_blocks;
+  if (nb_shared == 1 && t_shared[1] * 10 <= t_shared[0] * 9) nb_shared = 2;
+  bool sharing = t_shared[nb_shared - 1] * 100 <= t_alone[dp.row_blocks - 1] * 85;
+
+  // Segments: shared runs, and what is left of each request's pages.
+  struct Seg {
+    int32_t page0, nkeys, full, tiles;
+    int32_t run, b;   // the run, or -1 and the only reader
+    bool own_end;     // holds the end of the reader's keys
+    int32_t pieces;
+  };
+  std::vector<Seg> segs;
+  struct Range {
+    int32_t b, first, last;   // shared pages [first, last) of request b's list
+  };
+  std::vector<Range> taken;
+  auto cut = [&]() {
+    segs.clear();
+    taken.clear();
+    if (sharing)
+      for (size_t k = 0; k < runs.size(); ++k) {
+        const SharedRun &r = runs[k];
+        if (r.saved[nb_shared - 1] == 0) continue;
+        segs.push_back({r.page0, r.npages * P, r.npages * P - 1, (r.npages * P + kDecTile - 1) / kDecTile, (int32_t)k, 0, false, 0});
+        for (const auto &u : r.users) taken.push_back({u.first, u.second, u.second + r.npages});
+      }
+    std::sort(taken.begin(), taken.end(), [](const Range &x, const Range &y) { return x.b != y.b ? x.b < y.b : x.first < y.first; });
+    size_t k = 0;
+    for (int b = 0; b < B; ++b) {
+      const int32_t np = p->page_offsets[b + 1] - p->page_offsets[b], L = p->kv_lens[b];
+      const int32_t n = p->q_offsets[b + 1] - p->q_offsets[b];
+      int32_t at = 0;
+      for (;;) {
+        const bool more = k < taken.size() && taken[k].b == b;
+        const int32_t to = more ? taken[k].first : np;
+        if (to > at) {
+          const bool end = to == np;
+          const int32_t nkeys = (end ? L : to * P) - at * P;
+          segs.push_back({p->page_offsets[b] + at, nkeys, end ? nkeys - n : nkeys - 1, (nkeys + kDecTile - 1) / kDecTile, -1, b, end, 0});
+        }
+        if (!more) break;
+        at = taken[k++].last;
+      }
+    }
+  };
+  // f(request) for every reader of a segment.
+  auto readers = [&](const Seg &s, auto &&f) {
+    if (s.run < 0) f(s.b);
+    else
+      for (const auto &u : runs[s.run].users) f(u.first);
+  };
+  // Split planning. Without sharing: workgroups of at least 8 tiles (two per
+  // wave), about as many as the compute units hold at once (two each), so the
+  // whole step runs in one round of workgroups when the requests allow it.
+  // With sharing there are many segments of a cartridge's length, whose
+  // workgroups need no further cutting while they fill the compute units:
+  // pieces of at most 32 tiles, 64 requests over 4 of 256 cartridges of 32 tiles
+  // 136 us (143 us with one of at most 85), 50 over 3 of 16 27 us (31 us in
+  // pieces of 8).
+  const int64_t cus = device_topology().cus;
+  std::vector<int32_t> parts(B);
+  auto set_pieces = [&](int64_t per_wg) {
+    int64_t wgs = 0;
+    for (Seg &s : segs) {
+      s.pieces = (int32_t)std::min<int64_t>(kMaxDecParts, (s.tiles + per_wg - 1) / per_wg);
+      int64_t rows = 0;
+      readers(s, [&](int32_t b) { rows += rows_of[b]; });
+      wgs += s.pieces * ceil_div(rows, kDecRows * dp.row_blocks) * Hkv;
+    }
+    return wgs;
+  };
+  int64_t wgs = 0;
+  const int nb_alone = dp.row_blocks;
+  for (;;) {
+    cut();
+    dp.row_blocks = sharing ? nb_shared : nb_alone;
+    if (!sharing) {
+      wgs = set_pieces(std::max<int64_t>(8, ceil_div(t_alone[nb_alone - 1] * Hkv, 2 * cus)));
+    } else {
+      for (int64_t per_wg = 32; (wgs = set_pieces(per_wg)) < cus && per_wg > 8;) per_wg /= 2;
+    }
+    std::fill(parts.begin(), parts.end(), 0);
+    int32_t most = 0;
+    for (const Seg &s : segs) readers(s, [&](int32_t b) { most = std::max(most, parts[b] += s.pieces); });
+    if (most <= kMaxDecParts || !sharing) break;
+    sharing = false;   // too many pieces of one request
+  }
+  if (wgs > INT32_MAX) return fail(CAS_ERR_UNSUPPORTED, "too many workgroups");
+  dp.tok_parts.resize(Tq);
+  for (int b = 0; b < B; ++b) {
+    dp.max_parts = std::max(dp.max_parts, parts[b]);
+    for (int32_t t = p->q_offsets[b]; t < p->q_offsets[b + 1]; ++t) dp.tok_parts[t] = parts[b];
+  }
+  // Rows and workgroups. The workgroups go longest range first, ties in the
+  // order of segment, KV head, row block, piece: the first walk counts the
+  // lengths, the second puts each workgroup in its place.
+  const int rows_per_wg = kDecRows * dp.row_blocks;
+  struct Span {
+    int32_t t0, t1;
+  };
+  auto span = [](const Seg &s, int32_t i) {
+    return Span{(int32_t)((int64_t)s.tiles * i / s.pieces), (int32_t)((int64_t)s.tiles * (i + 1) / s.pieces)};
+  };
+  std::vector<int32_t> next_part(B, 0), row0(segs.size() + 1, 0);
+  std::map<int32_t, int64_t, std::greater<int32_t>> at;   // length -> workgroups, then the next one's place
+  for (size_t k = 0; k < segs.size(); ++k) {
+    const Seg &s = segs[k];
+    readers(s, [&](int32_t b) {
+      const int32_t q0 = p->q_offsets[b], n = p->q_offsets[b + 1] - q0;
+      const int32_t part = parts[b] > 1 ? next_part[b] : -1;
+      for (int32_t i = 0; i < n; ++i)
+        for (int32_t h = 0; h < g; ++h)
+          dp.rows.push_back({(q0 + i) * (int32_t)Hq + h, s.own_end ? s.full + i : s.nkeys - 1, part});
+      next_part[b] += s.pieces;
+    });
+    row0[k + 1] = (int32_t)dp.rows.size();
+    const int64_t wgs_of_piece = ceil_div(row0[k + 1] - row0[k], rows_per_wg) * Hkv;
+    for (int32_t i = 0; i < s.pieces; ++i) {
+      const Span t = span(s, i);
+      at[t.t1 - t.t0] += wgs_of_piece;
+    }
+  }
+  int64_t place = 0;
+  for (auto &x : at) {
+    const int64_t n = x.second;
+    x.second = place;
+    place += n;
+  }
+  dp.work.resize((size_t)wgs);
+  std::vector<Span> spans;
+  std::vector<int64_t *> places;
+  for (size_t k = 0; k < segs.size(); ++k) {
+    const Seg &s = segs[k];
+    spans.resize(s.pieces);
+    places.resize(s.pieces);
+    for (int32_t i = 0; i < s.pieces; ++i) {
+      spans[i] = span(s, i);
+      places[i] = &at[spans[i].t1 - spans[i].t0];
+    }
+    for (int kvh = 0; kvh < Hkv; ++kvh)
+      for (int32_t r = row0[k]; r < row0[k + 1]; r += rows_per_wg)
+        for (int32_t i = 0; i < s.pieces; ++i)
+          dp.work[(*places[i])++] = {s.page0, s.nkeys, s.full, kvh, spans[i].t0, spans[i].t1, r,
+                                     std::min(rows_per_wg, row0[k + 1] - r), i};
+  }
+  size_t off = align_up(dp.rows.size() * sizeof(DevDecodeRow), 256);
   dp.off_work = off;
   off = align_up(off + dp.work.size() * sizeof(DevDecodeWork), 256);
   dp.off_pages = off;
   off = align_up(off + (size_t)p->page_offsets[B] * sizeof(int32_t), 256);
-  dp.off_toksplit = off;
+  dp.off_tokparts = off;
   off = align_up(off + (size_t)Tq * sizeof(int32_t), 256);
   const size_t table_end = off;
-  if (dp.max_split > 1) {
+  if (dp.max_parts > 1) {
     const size_t plane = (size_t)Tq * Hq;
     dp.off_plse = off;
-    off = align_up(off + (size_t)dp.max_split * plane * 4, 256);
+    off = align_up(off + (size_t)dp.max_parts * plane * 4, 256);
     dp.off_po = off;
-    off = align_up(off + (size_t)dp.max_split * plane * p->head_dim * 4, 256);
+    off = align_up(off + (size_t)dp.max_parts * plane * p->head_dim * 4, 256);
   }
   dp.bytes = off;
   (void)table_end;
@@ -1239,10 +1460,10 @@ cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, 
   char *ws = (char *)workspace;
   const int npage_ids = p->page_offsets[p->batch];
   s = ring_upload(dp.off_plse ? dp.off_plse : dp.bytes, workspace, stream, [&](char *h) {
-    std::memcpy(h, dp.reqs.data(), dp.reqs.size() * sizeof(DevDecodeReq));
+    std::memcpy(h, dp.rows.data(), dp.rows.size() * sizeof(DevDecodeRow));
     std::memcpy(h + dp.off_work, dp.work.data(), dp.work.size() * sizeof(DevDecodeWork));
     if (npage_ids) std::memcpy(h + dp.off_pages, p->page_ids, (size_t)npage_ids * sizeof(int32_t));
-    std::memcpy(h + dp.off_toksplit, dp.tok_nsplit.data(), dp.tok_nsplit.size() * sizeof(int32_t));
+    std::memcpy(h + dp.off_tokparts, dp.tok_parts.data(), dp.tok_parts.size() * sizeof(int32_t));
   });
   if (s != CAS_OK) return s;
   DecodeParams kp{};
@@ -1251,12 +1472,12 @@ cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, 
   kp.v_pages = v_pages;
   kp.o = o;
   kp.lse = lse;
-  kp.reqs = (const DevDecodeReq *)ws;
+  kp.rows = (const DevDecodeRow *)ws;
   kp.work = (const DevDecodeWork *)(ws + dp.off_work);
   kp.page_ids = (const int32_t *)(ws + dp.off_pages);
-  kp.tok_nsplit = (const int32_t *)(ws + dp.off_toksplit);
-  kp.part_lse = dp.max_split > 1 ? (float *)(ws + dp.off_plse) : nullptr;
-  kp.part_o = dp.max_split > 1 ? (float *)(ws + dp.off_po) : nullptr;
+  kp.tok_parts = (const int32_t *)(ws + dp.off_tokparts);
+  kp.part_lse = dp.max_parts > 1 ? (float *)(ws + dp.off_plse) : nullptr;
+  kp.part_o = dp.max_parts > 1 ? (float *)(ws + dp.off_po) : nullptr;
   kp.plane = (int64_t)dp.Tq * dp.Hq;
   kp.Hkv = p->num_kv_heads;
   kp.g = p->group_size;
@@ -1265,8 +1486,8 @@ cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, 
   kp.scale_log2 = p->softmax_scale * 1.4426950408889634f;
   hipError_t e = timed("decode", stream, [&] { return launch_decode_bf16(kp, p->head_dim, (int)dp.work.size(), dp.row_blocks, stream); });
   if (e != hipSuccess) return hip_fail("decode launch", e);
-  if (dp.max_split > 1) {
-    e = timed("decode_merge", stream, [&] { return launch_decode_merge_bf16(kp, p->head_dim, dp.max_split, stream); });
+  if (dp.max_parts > 1) {
+    e = timed("decode_merge", stream, [&] { return launch_decode_merge_bf16(kp, p->head_dim, dp.max_parts, stream); });
     if (e != hipSuccess) return hip_fail("decode_merge launch", e);
   }
   return CAS_OK;

@@ -7,9 +7,10 @@
 // A decode step has very few query rows per (request, KV head) (n * g, e.g.
 // 4) against thousands of keys, so the work is streaming K and V out of HBM.
 // One workgroup takes a block of up to 16 (NB = 1) or 32 (NB = 2) packed rows
-// of one (request, KV head) and a range of 32-key tiles (the host splits a
-// request's key axis so that every compute unit holds two workgroups;
-// partials are merged by their LSE). Its four waves work independently on
+// of one KV head and a range of 32-key tiles of a segment of keys: a request's
+// own, or a page run that several requests share, whose rows then take one
+// pass over it together (the host cuts the segments so that the compute units
+// are full; a request's partials are merged by their LSE). Its four waves work independently on
 // every fourth tile of the range, so no wave ever waits on another until the
 // end, where the four partial softmax states are combined through LDS. The
 // products use v_mfma_f32_16x16x32_bf16, whose 16 columns fit the few rows of
@@ -29,7 +30,9 @@
 // Bound by HBM. Per call, before and after the second row block and the
 // single V set: 16 requests x 8 new tokens x 4 heads per group over ~4,250
 // keys 101.6 -> 72.2 us; 64 requests x 1 new token over 4,161 keys 177.9 ->
-// 175.2 us (1.09 GB of K and V).
+// 175.2 us (1.09 GB of K and V, 0.73 GB of it distinct). With the runs shared
+// between those 64 requests (each 4 of 256 cartridges) streamed once: 146.8 us;
+// 50 requests over 3 of 16 cartridges 82 -> 28 us of kernel.
 #include "cas_device.h"
 
 namespace cas {
@@ -65,24 +68,21 @@ void decode_bf16_kernel(DecodeParams p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j = lane & 15, bq = lane >> 4;    // MFMA column (row of the block) and k-group
   const DevDecodeWork w = load_const(p.work, (int)blockIdx.x);
-  const DevDecodeReq rq = load_const(p.reqs, w.b);
   const int g = p.g, Hkv = p.Hkv, Hq = Hkv * g, P = p.page_size;
   const int kvh = __builtin_amdgcn_readfirstlane(w.kvh);
-  const int kv_len = __builtin_amdgcn_readfirstlane(rq.kv_len);
-  const int nrows = rq.n * g;
-  // Row block rb of lane (j, bq): row row0 + 16 rb + j.
+  const int kv_len = __builtin_amdgcn_readfirstlane(w.nkeys);   // keys of the segment
+  // Row block rb of lane (j, bq): row row0 + 16 rb + j. Rows past the
+  // workgroup's see every key (their Q is zero and nothing of theirs is stored).
   bool row_ok[NB];
-  int my_i[NB], my_h[NB];                                 // query index within the request, query head
-  // Last key each row sees (rows past the block's end see every key: their
-  // Q is zero and nothing of theirs is stored).
-  int my_lim[NB];
+  int my_R[NB], my_lim[NB], my_part[NB];                  // row of q, o and the partial planes; last key; partial
 #pragma unroll
   for (int rb = 0; rb < NB; ++rb) {
-    const int r = w.row0 + 16 * rb + j;
-    row_ok[rb] = r < nrows;
-    my_i[rb] = r / g;
-    my_h[rb] = kvh * g + (r - my_i[rb] * g);
-    my_lim[rb] = row_ok[rb] ? kv_len - rq.n + my_i[rb] : kv_len - 1;
+    row_ok[rb] = 16 * rb + j < w.nrows;
+    DevDecodeRow r{0, kv_len - 1, -1};
+    if (row_ok[rb]) r = p.rows[w.row0 + 16 * rb + j];
+    my_R[rb] = r.base + kvh * g;
+    my_lim[rb] = r.lim;
+    my_part[rb] = r.part < 0 ? -1 : r.part + w.piece;
   }
   const float c = p.scale_log2;
   char *const vt = vs + wave * TB;
@@ -92,8 +92,7 @@ void decode_bf16_kernel(DecodeParams p) {
   bf16x8 qf[NB][NQ];
 #pragma unroll
   for (int rb = 0; rb < NB; ++rb) {
-    const __bf16 *qp = (const __bf16 *)p.q +
-                       ((int64_t)(rq.q0 + (row_ok[rb] ? my_i[rb] : 0)) * Hq + (row_ok[rb] ? my_h[rb] : kvh * g)) * D + 8 * bq;
+    const __bf16 *qp = (const __bf16 *)p.q + (int64_t)my_R[rb] * D + 8 * bq;
 #pragma unroll
     for (int st = 0; st < NQ; ++st)
       qf[rb][st] = row_ok[rb] ? *reinterpret_cast<const bf16x8 *>(qp + 32 * st) : Mma<__bf16>::zero();
@@ -108,8 +107,8 @@ void decode_bf16_kernel(DecodeParams p) {
     TilePages tp{0, 0};
     const int k0 = tile * kDecTile;
     if (k0 < kv_len) {
-      tp.a = load_const(p.page_ids, rq.page0 + k0 / P);
-      tp.b = k0 + 16 < kv_len ? load_const(p.page_ids, rq.page0 + (k0 + 16) / P) : tp.a;
+      tp.a = load_const(p.page_ids, w.page0 + k0 / P);
+      tp.b = k0 + 16 < kv_len ? load_const(p.page_ids, w.page0 + (k0 + 16) / P) : tp.a;
     }
     return tp;
   };
@@ -205,7 +204,7 @@ void decode_bf16_kernel(DecodeParams p) {
 #pragma unroll
         for (int st = 0; st < NQ; ++st) s[kb] = mfma16(kr[kb * NQ + st], qf[rb][st], s[kb]);
       }
-      if (key0 + kDecTile - 1 > kv_len - rq.n) {
+      if (key0 + kDecTile - 1 > w.full) {
         const int lim = my_lim[rb] - key0 - 4 * bq;
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
@@ -306,7 +305,7 @@ void decode_bf16_kernel(DecodeParams p) {
         wv[v] = (M == -INFINITY || mv == -INFINITY) ? 0.0f : fast_exp2(mv - M);
         L += wv[v] * mlb[v * 128 + 64 + lane];
       }
-      const int64_t R = (int64_t)(rq.q0 + my_i[rb]) * Hq + my_h[rb];   // row of q, o and the partial planes
+      const int64_t R = my_R[rb];
       const float inv = L > 0.0f ? 1.0f / L : 0.0f;
       // Wave v stores channel blocks v, v + 4, ...: lane (j, bq) channels
       // 16 db + 4 bq .. + 3 of row j.
@@ -319,26 +318,27 @@ void decode_bf16_kernel(DecodeParams p) {
           for (int e = 0; e < 4; ++e) o[e] += wv[v] * ov[(db * 4 + e) * 64 + lane];
         }
         const int ch = 16 * db + 4 * bq;
-        if (w.split < 0)
+        if (my_part[rb] < 0)
           store4((__bf16 *)p.o + R * D + ch, o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
         else
-          store4(p.part_o + (w.split * p.plane + R) * D + ch, o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
+          store4(p.part_o + (my_part[rb] * p.plane + R) * D + ch, o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
       }
       if (wave == 0 && bq == 0) {
         const float lse = L > 0.0f ? (M + log2f(L)) * kLn2 : -INFINITY;
-        if (w.split < 0) {
-          if (p.lse != nullptr) p.lse[(int64_t)my_h[rb] * p.Tq + rq.q0 + my_i[rb]] = lse;
+        if (my_part[rb] < 0) {
+          const int t = my_R[rb] / Hq, h = my_R[rb] - t * Hq;
+          if (p.lse != nullptr) p.lse[(int64_t)h * p.Tq + t] = lse;
         } else {
-          p.part_lse[w.split * p.plane + R] = lse;
+          p.part_lse[my_part[rb] * p.plane + R] = lse;
         }
       }
     }
   }
 }
 
-// LSE-weighted combination of a split request's partials. A (query token,
-// head) row is D/4 lanes of 4 channels each, GR of these lane groups taking
-// every GR-th split; their sums meet in LDS. Bound by latency: one group
+// LSE-weighted combination of a request's partials. A (query token, head) row
+// is D/4 lanes of 4 channels each, GR of these lane groups taking every GR-th
+// partial; their sums meet in LDS. Bound by latency: one group
 // walking 17 splits in a row took 9.5 us of a single request's decode step
 // (32 rows, 4 workgroups); eight groups per row, one workgroup each, take
 // 3.9 us (the whole call 25.6 -> 23.4 us, most of it host work by then).
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams p) {
   const int Hq = p.Hkv * p.g;
   const bool live = R < p.plane;
   const int t = live ? (int)(R / Hq) : 0;
-  const int ns = live ? p.tok_nsplit[t] : 0;
+  const int ns = live ? p.tok_parts[t] : 0;
   float mx = -INFINITY;
   for (int s = c4; s < ns; s += CPR) mx = fmaxf(mx, p.part_lse[s * p.plane + R]);
 #pragma unroll
@@ -380,7 +380,7 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams p) {
       }
     }
   }
-  if (gr != 0 || ns <= 1) return;   // (an unsplit request wrote its output itself)
+  if (gr != 0 || ns <= 1) return;   // (a request with one partial wrote its output itself)
   const float inv = 1.0f / w_sum;
   store4((__bf16 *)p.o + R * D + c4 * 4, acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
   if (c4 == 0 && p.lse != nullptr) p.lse[(R - (int64_t)t * Hq) * p.Tq + t] = mx + logf(w_sum);
@@ -400,21 +400,21 @@ hipError_t launch_decode_bf16(const DecodeParams &p, int D, int n_work, int row_
   return hipGetLastError();
 }
 
-// Groups per row: each should take at least two of the row's splits (max_split
+// Groups per row: each should take at least two of the row's partials (max_parts
 // is the call's largest count). With fewer the extra workgroups cost more
 // than the shorter walk saves: 4,096 rows of 5 splits take 6.7 us with eight
 // groups, 4.9 us with one walking them all.
 template <int D>
-static void launch_decode_merge_t(const DecodeParams &p, int max_split, hipStream_t s) {
+static void launch_decode_merge_t(const DecodeParams &p, int max_parts, hipStream_t s) {
   auto grid = [&](int gr) { const int64_t rpw = 256 / (D / 4 * gr); return dim3((unsigned)((p.plane + rpw - 1) / rpw)); };
-  if (max_split >= 16) hipLaunchKernelGGL((decode_merge_kernel<D, 8>), grid(8), dim3(256), 0, s, p);
-  else if (max_split >= 8) hipLaunchKernelGGL((decode_merge_kernel<D, 4>), grid(4), dim3(256), 0, s, p);
+  if (max_parts >= 16) hipLaunchKernelGGL((decode_merge_kernel<D, 8>), grid(8), dim3(256), 0, s, p);
+  else if (max_parts >= 8) hipLaunchKernelGGL((decode_merge_kernel<D, 4>), grid(4), dim3(256), 0, s, p);
   else hipLaunchKernelGGL((decode_merge_kernel<D, 2>), grid(2), dim3(256), 0, s, p);
 }
 
-hipError_t launch_decode_merge_bf16(const DecodeParams &p, int D, int max_split, hipStream_t s) {
-  if (D == 64) launch_decode_merge_t<64>(p, max_split, s);
-  else launch_decode_merge_t<128>(p, max_split, s);
+hipError_t launch_decode_merge_bf16(const DecodeParams &p, int D, int max_parts, hipStream_t s) {
+  if (D == 64) launch_decode_merge_t<64>(p, max_parts, s);
+  else launch_decode_merge_t<128>(p, max_parts, s);
   return hipGetLastError();
 }
 

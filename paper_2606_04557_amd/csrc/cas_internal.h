@@ -223,20 +223,24 @@ struct AdamParams {
   float eps;
 };
 
-// Paged decode: one request (its queries are tokens q0 .. q0+n-1; its keys
-// the pages page_ids[page0 ..] in order, kv_len of them) and one workgroup's
-// share: packed rows row0 .. row0+15 (or +31, see DecodePlan; row r = query
-// r / g, head kvh*g + r % g) over 32-key tiles [tile0, tile1) of the
-// request's key axis.
+// Paged decode. The keys of a call are cut into segments: page runs that one
+// request reads, or that several share. A query row of a segment (a packed row
+// of a request that reads it): its row of q and o at KV head 0 (token * Hq +
+// head within the group), the last key of the segment it sees, and where its
+// partial goes (plane `part` + the workgroup's piece, or -1: it sees nothing
+// else, and the result goes straight to o and lse).
 constexpr int kDecTile = 32;
 constexpr int kDecRows = 16;
-struct DevDecodeReq {
-  int32_t q0, n, kv_len, page0;
+struct DevDecodeRow {
+  int32_t base, lim, part;
 };
+// One workgroup's share: rows row0 .. row0 + nrows - 1 (at most 16, or 32 with
+// two row blocks) at one KV head over 32-key tiles [tile0, tile1) of a segment
+// of nkeys keys in the pages page_ids[page0 ..]; every row sees keys up to full.
 struct DevDecodeWork {
-  int32_t b, kvh, row0, split;   // split index, or -1 when the range is the whole axis
-  int32_t tile0, tile1;
-  int32_t pad_[2];
+  int32_t page0, nkeys, full, kvh;
+  int32_t tile0, tile1, row0, nrows;
+  int32_t piece;
 };
 
 struct DecodeParams {
@@ -245,12 +249,12 @@ struct DecodeParams {
   const void *v_pages;
   void *o;
   float *lse;             // [Hq][Tq] or null
-  const DevDecodeReq *reqs;
+  const DevDecodeRow *rows;
   const DevDecodeWork *work;
   const int32_t *page_ids;
-  const int32_t *tok_nsplit; // [Tq] key-axis splits of each query token's request (merge)
-  float *part_o;          // [split][Tq * Hq][D] when a request is split
-  float *part_lse;        // [split][Tq * Hq]
+  const int32_t *tok_parts; // [Tq] partials of each query token's request (merge)
+  float *part_o;          // [part][Tq * Hq][D] when a request has several partials
+  float *part_lse;        // [part][Tq * Hq]
   int64_t plane;          // Tq * Hq
   int32_t Hkv, g, page_size, Tq;
   float scale_log2;

@@ -109,6 +109,59 @@ def test_decode_split_merge(D, keys):
     _run(kp, vp, kl, qc, pages, 2, 4, D, 1301)
 
 
+def _shared_problem(seed, P, D, Hkv, g, n_req, n_carts, cart_keys, pick, new, own, cut=None):
+    """Requests that share cartridges of cart_keys keys: request r reads the
+    cartridges pick(r) and own(r) tokens of its own, of which new(r) are
+    queries. cut(r): pages dropped from the end of its last cartridge."""
+    cp = cart_keys // P
+    reqs, pages, kv = [], [], []
+    nxt = n_carts * cp
+    for r in range(n_req):
+        ids = [c * cp + j for c in pick(r) for j in range(cp)]
+        if cut:
+            ids = ids[: len(ids) - cut(r)]
+        op = -(-own(r) // P)
+        pages.append(ids + list(range(nxt, nxt + op)))
+        nxt += op
+        kv.append(len(ids) * P + own(r))
+    shape = (nxt, P, Hkv, D)
+    bits = lambda tag: rng.f64_to_bf16_bits(rng.normal(rng.stream_key(seed, tag), int(np.prod(shape)), 0.5))
+    kp = rng.bf16_bits_to_f32(bits(1)).reshape(shape)
+    vp = rng.bf16_bits_to_f32(bits(2)).reshape(shape)
+    return kp, vp, kv, [new(r) for r in range(n_req)], pages
+
+
+SHARED = [
+    # every request reads the same cartridge first, then one of two others; ends off the page
+    dict(name="prefix", P=16, D=128, Hkv=2, g=4, n_req=9, n_carts=3, cart_keys=512, pick=lambda r: [0, 1 + r % 2],
+         new=lambda r: 1, own=lambda r: 1 + 7 * r),
+    # more than 32 rows of readers per run; a request that reads a cartridge twice, one that reads none
+    dict(name="many_twice", P=32, D=64, Hkv=1, g=5, n_req=12, n_carts=4, cart_keys=320,
+         pick=lambda r: [] if r == 3 else [2, 2] if r == 5 else [r % 4, (r + 1) % 4, 2][: 1 + r % 3],
+         new=lambda r: 1 + r % 3, own=lambda r: 3 + r),
+    # runs cut short by one reader; no own tokens past the queries, so a run's last pages hold a reader's queries
+    dict(name="cut", P=16, D=128, Hkv=8, g=4, n_req=6, n_carts=2, cart_keys=1024, pick=lambda r: [r % 2, 1 - r % 2],
+         new=lambda r: 1, own=lambda r: 0 if r % 2 else 40, cut=lambda r: r),
+    # large pages, runs split into pieces, the last tile of a piece partly past the run
+    dict(name="pieces", P=128, D=128, Hkv=1, g=2, n_req=5, n_carts=2, cart_keys=2048, pick=lambda r: [0, 1],
+         new=lambda r: 2, own=lambda r: 2 + 100 * r),
+    # below the shortest run worth sharing
+    dict(name="short", P=16, D=64, Hkv=2, g=2, n_req=8, n_carts=2, cart_keys=128, pick=lambda r: [0, 1],
+         new=lambda r: 1, own=lambda r: 5),
+]
+
+
+@pytest.mark.parametrize("case", SHARED, ids=[c["name"] for c in SHARED])
+def test_decode_shared_runs(case):
+    """Cartridges that several requests read are streamed once for all of
+    them: each request's output still equals its own gathered keys."""
+    c = dict(case)
+    c.pop("name")
+    Hkv, g, D = c["Hkv"], c["g"], c["D"]
+    kp, vp, kl, qc, pages = _shared_problem(1400, **c)
+    _run(kp, vp, kl, qc, pages, Hkv, g, D, 1401)
+
+
 def test_decode_retrieval_mix_full_size():
     """Cartridge-RAG decode step at full size: a pool of 256 cartridges of 1,024
     tokens (16,384 pages of 16 tokens, 8 KV heads x 128); 64 requests, each over
