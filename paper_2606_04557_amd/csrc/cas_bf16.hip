@@ -563,7 +563,9 @@ void fwd_bf16_kernel(FwdParams p) {
       for (int jj = 0; jj < 4; ++jj)
         store4(op + dt * 32 + jj * 8 + G * 4, oacc[dt][jj * 4 + 0] * inv, oacc[dt][jj * 4 + 1] * inv,
                oacc[dt][jj * 4 + 2] * inv, oacc[dt][jj * 4 + 3] * inv);
-    if (G == 0) p.part_lse[prow] = lt > 0.0f ? (m_out + log2f(lt)) * kLn2 : -INFINITY;
+    // A NaN sum stays NaN, so that the merge gives what one pass would (bits
+    // compared: this file's comparisons take NaN for impossible).
+    if (G == 0) p.part_lse[prow] = __float_as_uint(lt) == 0u ? -INFINITY : (m_out + log2f(lt)) * kLn2;
   }
 }
 

@@ -162,6 +162,29 @@ def test_decode_shared_runs(case):
     _run(kp, vp, kl, qc, pages, Hkv, g, D, 1401)
 
 
+@pytest.mark.parametrize("n_req", [1, 6])
+def test_decode_nan_key_stays(n_req):
+    """A key that is not a number makes every row that reads it NaN, whether the
+    row's keys take one pass, several pieces (one request of 2,100 keys) or a
+    run shared with other requests, and leaves the other requests alone."""
+    import torch
+    import paper_2606_04557_amd as cas
+    own = 2100 if n_req == 1 else 20
+    reqs = [([0, 1] if n_req > 1 and r % 2 else [0], own, 1) for r in range(n_req)] + [([], 700, 1)]
+    kp, vp, kl, qc, pages = _pool(1500 + n_req, 2, 32, 16, 2, 128, reqs)
+    o, lse = _run(kp, vp, kl, qc, pages, 2, 4, 128, 1501)
+    good = o.clone()
+    kp = kp.copy()
+    kp[5, 3, 1, 7] = np.nan          # cartridge 0, KV head 1
+    q = rng.bf16_bits_to_f32(rng.f64_to_bf16_bits(rng.normal(rng.stream_key(1501, 3), sum(qc) * 8 * 128, 1.0)))
+    q = torch.from_numpy(q.reshape(sum(qc), 8, 128)).to(torch.bfloat16).cuda()
+    o, _ = cas.paged_decode_fwd(q, torch.from_numpy(kp).to(torch.bfloat16).cuda(), torch.from_numpy(vp).to(torch.bfloat16).cuda(),
+                                qc, kl, pages, 2, 4, float(np.float32(1.0 / np.sqrt(128))))
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(o[:-1, 4:]).all())
+    assert torch.equal(o[:-1, :4], good[:-1, :4]) and torch.equal(o[-1], good[-1])
+
+
 def test_decode_retrieval_mix_full_size():
     """Cartridge-RAG decode step at full size: a pool of 256 cartridges of 1,024
     tokens (16,384 pages of 16 tokens, 8 KV heads x 128); 64 requests, each over
