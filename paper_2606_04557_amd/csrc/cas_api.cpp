@@ -523,7 +523,7 @@ cas_status_t build_plan(const cas_problem_t *p, bool bwd, Plan &pl, int fwd_spli
       pl.off_part_o = off;
       off = align_up(off + (size_t)pl.fwd_splits * plane * D * 4, 256);
       pl.off_part_lse = off;
-      off = align_up(off + (size_t)pl.fwd_splits * plane * 4, 256);
+      off = align_up(off + (size_t)pl.fwd_splits * plane * (bf16 ? 4 : 8), 256);
     }
     pl.ws_fwd = off;
   } else {

@@ -238,23 +238,26 @@ __global__ __launch_bounds__(kThreads, D == 64 ? 2 : 1) void fwd_kernel(FwdParam
       if (G == 0 && p.lse != nullptr)
         p.lse[(int64_t)row.lse0 + (int64_t)h * p.lse_hs + t] = (m_run[qs] + log2f(lt)) * kLn2;
     } else {
+      // The partial as it is, with its row maximum and sum: the merge then rounds
+      // no more than one pass would (an LSE of the partial would add two
+      // roundings of its own).
       const int64_t prow = split * p.plane + (int64_t)tok0 * Hq + kvh * nrows + r;
-      const float inv = lt > 0.0f ? 1.0f / lt : 0.0f;
       float *op = p.part_o + prow * D;
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj)
-          store4(op + dt * 32 + jj * 8 + G * 4, oacc[dt][qs][jj * 4 + 0] * inv,
-                 oacc[dt][qs][jj * 4 + 1] * inv, oacc[dt][qs][jj * 4 + 2] * inv,
-                 oacc[dt][qs][jj * 4 + 3] * inv);
-      if (G == 0) p.part_lse[prow] = lt > 0.0f ? (m_run[qs] + log2f(lt)) * kLn2 : -INFINITY;
+          store4(op + dt * 32 + jj * 8 + G * 4, oacc[dt][qs][jj * 4 + 0], oacc[dt][qs][jj * 4 + 1],
+                 oacc[dt][qs][jj * 4 + 2], oacc[dt][qs][jj * 4 + 3]);
+      if (G == 0) reinterpret_cast<float2 *>(p.part_lse)[prow] = float2{m_run[qs], lt};
     }
   }
 }
 
 // LSE-weighted combination of split partials:
 //   LSE = log sum_s exp(LSE_s),  O = sum_s exp(LSE_s - LSE) O_s.
+// fp32 partials are not normalised and bring (m, l), maximum in log2 units and sum:
+//   w_s = exp2(m_s - max m),  l = sum_s w_s l_s,  O = sum_s w_s O_s / l.
 // One thread per 4 channels of a packed row; grid.y is the batch row. Bound by
 // latency at the few splits of short calls, so the row's lanes load one LSE
 // each (their weights then come from lane to lane) and the partials of eight
@@ -274,12 +277,23 @@ __global__ __launch_bounds__(kThreads) void fwd_merge_kernel(MergeParams p) {
   if (rb >= (int64_t)p.Hkv * nrows) return;   // (all lanes of a row together)
   const int64_t plane = p.plane;
   const int64_t R = (int64_t)row.tok0 * p.Hkv * p.g + rb;
-  float w[NL];
+  constexpr bool kSums = sizeof(T) == 4;   // (m, l) partials
+  float w[NL], l[NL];
   float mx = -INFINITY;
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
     const int s = c4 + i * CPR;
-    w[i] = s < p.splits ? p.part_lse[s * plane + R] : -INFINITY;
+    w[i] = -INFINITY;
+    l[i] = 0.0f;
+    if (s < p.splits) {
+      if constexpr (kSums) {
+        const float2 ml = reinterpret_cast<const float2 *>(p.part_lse)[s * plane + R];
+        w[i] = ml.x;
+        l[i] = ml.y;
+      } else {
+        w[i] = p.part_lse[s * plane + R];
+      }
+    }
     mx = fmaxf(mx, w[i]);
   }
 #pragma unroll
@@ -287,8 +301,8 @@ __global__ __launch_bounds__(kThreads) void fwd_merge_kernel(MergeParams p) {
   float w_sum = 0.0f;
 #pragma unroll
   for (int i = 0; i < NL; ++i) {
-    w[i] = (w[i] == -INFINITY) ? 0.0f : expf(w[i] - mx);
-    w_sum += w[i];
+    w[i] = (w[i] == -INFINITY) ? 0.0f : kSums ? exp2f(w[i] - mx) : expf(w[i] - mx);
+    w_sum += kSums ? w[i] * l[i] : w[i];
   }
 #pragma unroll
   for (int m = CPR / 2; m >= 1; m >>= 1) w_sum += __shfl_xor(w_sum, m, CPR);
@@ -318,7 +332,8 @@ __global__ __launch_bounds__(kThreads) void fwd_merge_kernel(MergeParams p) {
   const int Hq = p.Hkv * p.g;
   T *op = (T *)p.o + (((int64_t)row.tok0 + t) * Hq + h) * D + c4 * 4;
   store4(op, acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
-  if (c4 == 0 && p.lse != nullptr) p.lse[(int64_t)row.lse0 + (int64_t)h * p.lse_hs + t] = mx + logf(w_sum);
+  if (c4 == 0 && p.lse != nullptr)
+    p.lse[(int64_t)row.lse0 + (int64_t)h * p.lse_hs + t] = kSums ? (mx + log2f(w_sum)) * kLn2 : mx + logf(w_sum);
 }
 
 template <int D>

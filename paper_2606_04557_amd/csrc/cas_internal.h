@@ -103,7 +103,7 @@ struct FwdParams {
   void *o;
   float *lse;
   float *part_o;      // [splits][plane][D] when splits > 1 (rows as the statistics)
-  float *part_lse;    // [splits][plane]
+  float *part_lse;    // [splits][plane]; fp32: (row maximum in log2 units, sum) pairs instead
   const DevSeg *segs;
   const DevRow *rows;
   const DevTile *tiles;

@@ -154,6 +154,55 @@ def test_fp32_block_edges(D, q_len, g):
     _check_full(GpuCase(wl), f"edges {q_len}")
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("splits", [2, 8, 17])
+def test_fp32_splits_lose_no_precision(D, splits):
+    """Partials carry their row maximum and sum, so the merge of a split key
+    axis rounds no more than one pass: its error against the fp64 oracle stays
+    within a tenth of the unsplit one's (the 2-norm over 15,360 or more rounded
+    values; shorter sums make it smaller in fact)."""
+    import paper_2606_04557_amd as cas
+    wl = casgen.custom("prec", "fp32", batch=1, q_len=60, num_q_heads=4, num_kv_heads=2, head_dim=D, cart_lens=[900, 400],
+                       rows=[[0, 1]], seed=250, cart_std=0.5)
+    case = GpuCase(wl)
+    O, LSE, _ = full_oracle(case, backward=False)
+    err = []
+    try:
+        for n in (1, splits):
+            cas.set_tuning(fwd_splits=n)
+            o, lse = case.fwd()
+            err.append((float(np.linalg.norm(host(o) - O)), float(np.linalg.norm(host(lse) - LSE))))
+    finally:
+        cas.set_tuning(0, 0)
+    print(f"O {err[0][0]:.3e} {err[1][0]:.3e} LSE {err[0][1]:.3e} {err[1][1]:.3e}")
+    assert err[1][0] <= 1.1 * err[0][0]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("splits", [1, 3, 9])
+def test_nan_key_stays(dtype, splits):
+    """A key that is not a number makes O and LSE of the rows that read it NaN,
+    however the key axis is split; other rows and KV heads are untouched."""
+    import paper_2606_04557_amd as cas
+    wl = casgen.custom("nan", dtype, batch=2, q_len=40, num_q_heads=4, num_kv_heads=2, head_dim=64, cart_lens=[300, 200],
+                       rows=[[0, 1], [0]], seed=240, cart_std=0.5)
+    T = casgen.make_tensors(wl)
+    try:
+        cas.set_tuning(fwd_splits=splits)
+        o0, l0 = (host(x) for x in GpuCase(wl, tensors=T).fwd())
+        k = np.array(casgen.to_float(T["cart_k"][1], dtype), dtype=np.float64)
+        k[77, 1, 5] = np.nan
+        T["cart_k"][1] = casgen.rng.f64_to_bf16_bits(k) if dtype == "bf16" else k.astype(np.float32)
+        if dtype == "bf16":
+            T["cart_k"][1][77, 1, 5] = 0x7FC0
+        o, lse = (host(x) for x in GpuCase(wl, tensors=T).fwd())
+    finally:
+        cas.set_tuning(0, 0)
+    assert np.isnan(o[0, :, 2:]).all() and np.isnan(lse[0, 2:]).all()
+    assert np.array_equal(o[0, :, :2], o0[0, :, :2]) and np.array_equal(o[1], o0[1])
+    assert np.array_equal(lse[0, :2], l0[0, :2]) and np.array_equal(lse[1], l0[1])
+
+
 def test_wide_token_stride():
     """A 1,024-token cartridge stored with a token stride of 2^21 elements
     (4 MiB), so that its keys and gradients span 4 GiB: byte offsets within a
