@@ -333,6 +333,32 @@ typedef struct {
  * depends on the compute-unit count of the current device. */
 cas_status_t cas_paged_decode_workspace_size(const cas_decode_problem_t *p, size_t *bytes);
 
+/*
+ * Launch plan of a paged decode call (host-side; no device access). For tests
+ * and profiling tools. rows and work may be NULL; otherwise they receive the
+ * plan's tables, 3 * info->num_rows and 9 * info->workgroups values (ask for
+ * the counts first):
+ *   rows: per query row of a segment of keys its row of q at KV head 0, the
+ *         last key of the segment it sees, its first partial (-1: none, the
+ *         result goes straight to o);
+ *   work: per workgroup the segment's first entry of page_ids and key count,
+ *         the last key every row sees, KV head, first and one past the last
+ *         32-key tile, first row, row count, and which piece of its segment.
+ */
+typedef struct {
+  int64_t key_tiles;        /* 32-key tiles streamed by all workgroups */
+  int32_t workgroups;
+  int32_t num_rows;
+  int32_t row_blocks;       /* 16-row blocks of one workgroup (1 or 2) */
+  int32_t max_partials;     /* most partials of one request (1: no merge) */
+  int32_t shared_runs;      /* page runs streamed once for several readers */
+  int32_t reserved;
+  size_t ws_bytes;
+} cas_decode_plan_info_t;
+
+cas_status_t cas_paged_decode_plan_info(const cas_decode_problem_t *p, cas_decode_plan_info_t *info, int32_t *rows,
+                                        int32_t *work);
+
 cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, const void *k_pages,
                                   const void *v_pages, void *o, float *lse, void *workspace,
                                   size_t ws_bytes, void *hip_stream);

@@ -516,3 +516,13 @@ def timing_read() -> dict:
     n = ctypes.c_int32(0)
     _check(load().cas_timing_read(arr, cap, ctypes.byref(n)))
     return {arr[i].name.decode(): (arr[i].launches, arr[i].total_ms) for i in range(min(n.value, cap))}
+
+
+def decode_plan(problem: DecodeProblem):
+    """The launch plan of a paged decode call (cas_paged_decode_plan_info): its
+    counts, its rows and its work list (per row and per workgroup a tuple)."""
+    info = _lib.DecodePlanInfo()
+    _check(load().cas_paged_decode_plan_info(ctypes.byref(problem.c), ctypes.byref(info), None, None))
+    rows, work = (ctypes.c_int32 * (3 * info.num_rows))(), (ctypes.c_int32 * (9 * info.workgroups))()
+    _check(load().cas_paged_decode_plan_info(ctypes.byref(problem.c), ctypes.byref(info), rows, work))
+    return info, list(zip(*[iter(rows)] * 3)), list(zip(*[iter(work)] * 9))

@@ -27,7 +27,7 @@ EXPORTS = [
     "cas_set_tuning", "cas_get_tuning", "cas_plan_info", "cas_timing_enable",
     "cas_timing_reset", "cas_timing_read", "cas_adam_lr_scale", "cas_cartridge_adam_workspace_size",
     "cas_cartridge_adam", "cas_paged_decode_workspace_size", "cas_paged_decode_fwd",
-    "cas_pool_plan_rotation", "cas_pool_create", "cas_pool_destroy", "cas_pool_host_cartridge",
+    "cas_paged_decode_plan_info", "cas_pool_plan_rotation", "cas_pool_create", "cas_pool_destroy", "cas_pool_host_cartridge",
     "cas_pool_load", "cas_pool_active", "cas_pool_end_step", "cas_pool_flush",
     "cas_prefix_attn_fwd_noalloc", "cas_pool_read_moments",
 ]
@@ -67,6 +67,12 @@ class DecodeProblem(ctypes.Structure):
                 ("num_pages", ctypes.c_int64), ("q_offsets", ctypes.POINTER(ctypes.c_int32)),
                 ("kv_lens", ctypes.POINTER(ctypes.c_int32)), ("page_offsets", ctypes.POINTER(ctypes.c_int32)),
                 ("page_ids", ctypes.POINTER(ctypes.c_int32))]
+
+
+class DecodePlanInfo(ctypes.Structure):
+    _fields_ = [("key_tiles", ctypes.c_int64), ("workgroups", ctypes.c_int32), ("num_rows", ctypes.c_int32),
+                ("row_blocks", ctypes.c_int32), ("max_partials", ctypes.c_int32), ("shared_runs", ctypes.c_int32),
+                ("reserved", ctypes.c_int32), ("ws_bytes", ctypes.c_size_t)]
 
 
 class PoolConfig(ctypes.Structure):
@@ -129,6 +135,7 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.cas_cartridge_adam.argtypes = [P(AdamCartridge), i32, i32, i32, P(AdamConfig), vp, sz, vp]
     lib.cas_paged_decode_workspace_size.argtypes = [P(DecodeProblem), P(sz)]
     lib.cas_paged_decode_fwd.argtypes = [P(DecodeProblem), vp, vp, vp, vp, vp, vp, sz, vp]
+    lib.cas_paged_decode_plan_info.argtypes = [P(DecodeProblem), P(DecodePlanInfo), P(i32), P(i32)]
     u8p = P(ctypes.c_uint8)
     lib.cas_pool_plan_rotation.argtypes = [P(i32), u8p, i32, i32, ctypes.c_float, P(i32), P(i32), P(i32)]
     lib.cas_pool_create.argtypes = [P(PoolConfig), P(vp)]
@@ -150,8 +157,8 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
                  "cas_cartridge_stage", "cas_set_tuning", "cas_get_tuning", "cas_plan_info",
                  "cas_timing_enable", "cas_timing_reset", "cas_timing_read",
                  "cas_cartridge_adam_workspace_size", "cas_cartridge_adam",
-                 "cas_paged_decode_workspace_size", "cas_paged_decode_fwd", "cas_pool_plan_rotation",
-                 "cas_pool_create", "cas_pool_destroy", "cas_pool_host_cartridge", "cas_pool_load",
+                 "cas_paged_decode_workspace_size", "cas_paged_decode_fwd", "cas_paged_decode_plan_info",
+                 "cas_pool_plan_rotation", "cas_pool_create", "cas_pool_destroy", "cas_pool_host_cartridge", "cas_pool_load",
                  "cas_pool_active", "cas_pool_end_step", "cas_pool_flush", "cas_pool_read_moments"):
         getattr(lib, name).restype = ctypes.c_int
     _lib = lib

@@ -925,6 +925,7 @@ struct DecodePlan {
   std::vector<DevDecodeWork> work;
   std::vector<int32_t> tok_parts;
   int max_parts = 1;
+  int shared = 0;   // page runs streamed for several requests
   // 16-row blocks of one workgroup: 2 when a request has more than 16 packed
   // rows, or when that shares enough page runs between more requests, so that
   // those rows take one pass over the keys.
@@ -1109,11 +1110,13 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
   auto cut = [&]() {
     segs.clear();
     taken.clear();
+    dp.shared = 0;
     if (sharing)
       for (size_t k = 0; k < runs.size(); ++k) {
         const SharedRun &r = runs[k];
         if (r.saved[nb_shared - 1] == 0) continue;
         segs.push_back({r.page0, r.npages * P, r.npages * P - 1, (r.npages * P + kDecTile - 1) / kDecTile, (int32_t)k, 0, false, 0});
+        ++dp.shared;
         for (const auto &u : r.users) taken.push_back({u.first, u.second, u.second + r.npages});
       }
     std::sort(taken.begin(), taken.end(), [](const Range &x, const Range &y) { return x.b != y.b ? x.b < y.b : x.first < y.first; });
@@ -1432,6 +1435,26 @@ cas_status_t cas_paged_decode_workspace_size(const cas_decode_problem_t *p, size
   cas_status_t s = build_decode(p, dp);
   if (s != CAS_OK) return s;
   *bytes = dp.bytes;
+  return CAS_OK;
+}
+
+cas_status_t cas_paged_decode_plan_info(const cas_decode_problem_t *p, cas_decode_plan_info_t *info, int32_t *rows,
+                                        int32_t *work) {
+  if (!info) return fail(CAS_ERR_INVALID_ARGUMENT, "info is NULL");
+  DecodePlan dp;
+  cas_status_t s = build_decode(p, dp);
+  if (s != CAS_OK) return s;
+  *info = cas_decode_plan_info_t{};
+  for (const DevDecodeWork &w : dp.work) info->key_tiles += w.tile1 - w.tile0;
+  info->workgroups = (int32_t)dp.work.size();
+  info->num_rows = (int32_t)dp.rows.size();
+  info->row_blocks = dp.row_blocks;
+  info->max_partials = dp.max_parts;
+  info->shared_runs = dp.shared;
+  info->ws_bytes = dp.bytes;
+  static_assert(sizeof(DevDecodeRow) == 12 && sizeof(DevDecodeWork) == 36, "tables of 32-bit values");
+  if (rows) std::memcpy(rows, dp.rows.data(), dp.rows.size() * sizeof(DevDecodeRow));
+  if (work) std::memcpy(work, dp.work.data(), dp.work.size() * sizeof(DevDecodeWork));
   return CAS_OK;
 }
 

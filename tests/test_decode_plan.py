@@ -1,0 +1,111 @@
+"""The launch plan of the paged decode (pure host): every query row sees each of
+its keys exactly once, every partial has its own place, and page runs that
+requests share are streamed once where that saves work."""
+import random
+
+import pytest
+
+from test_gpu_decode import SHARED, _shared_problem
+
+TILE = 32
+
+
+@pytest.fixture(scope="module")
+def cas():
+    import paper_2606_04557_amd as cas
+    cas.load()
+    return cas
+
+
+def problem(cas, q, kv, pages, P=16, Hkv=2, g=2, D=64):
+    npages = max((x for pl in pages for x in pl), default=0) + 1
+    return cas.DecodeProblem(q, kv, pages, npages, P, Hkv, g, D, 0.125)
+
+
+def check(cas, q, kv, pages, P=16, Hkv=2, g=2, D=64):
+    """Walks the plan's workgroups and compares what each (token, head) sees
+    with its request's own key list."""
+    info, rows, work = cas.decode_plan(problem(cas, q, kv, pages, P, Hkv, g, D))
+    ids = [x for pl in pages for x in pl]
+    Hq = Hkv * g
+    seen, parts = {}, {}
+    assert sum(w[5] - w[4] for w in work) == info.key_tiles
+    assert [w[5] - w[4] for w in work] == sorted((w[5] - w[4] for w in work), reverse=True)
+    for page0, nkeys, full, kvh, t0, t1, row0, nrows, piece in work:
+        assert 0 <= t0 < t1 <= -(-nkeys // TILE) and 1 <= nrows <= 16 * info.row_blocks and 0 <= kvh < Hkv
+        assert 0 <= row0 and row0 + nrows <= info.num_rows and page0 + -(-nkeys // P) <= len(ids)
+        for base, lim, part in rows[row0: row0 + nrows]:
+            assert full <= lim < nkeys
+            k = (base, kvh)
+            seen.setdefault(k, []).extend(ids[page0 + i // P] * P + i % P for i in range(t0 * TILE, min(t1 * TILE, lim + 1)))
+            parts.setdefault(k, []).append(part + piece if part >= 0 else -1)
+    tok = 0
+    for n, L, pl in zip(q, kv, pages):
+        keys = [pl[i // P] * P + i % P for i in range(L)]
+        for i in range(n):
+            want = sorted(keys[: L - n + i + 1])
+            for h in range(g):
+                for kvh in range(Hkv):
+                    k = ((tok + i) * Hq + h, kvh)
+                    assert sorted(seen.pop(k)) == want
+                    p = sorted(parts[k])
+                    assert p == ([-1] if len(p) == 1 else list(range(len(p)))) and len(p) <= info.max_partials
+        tok += n
+    assert not seen and info.max_partials <= 64
+    return info
+
+
+def draw(r):
+    """Requests over a pool of consecutive pages: cartridges, parts of them,
+    repeated, reordered and cut ones, scattered pages, own pages of any count."""
+    P = r.choice([16, 16, 32, 64, 128])
+    n_carts, cp = r.randint(1, 6), r.randint(1, 6 * 256 // P // 2)
+    q, kv, pages = [], [], []
+    nxt = n_carts * cp
+    forks = []
+    for _ in range(r.randint(1, 9)):
+        pl = []
+        for _ in range(r.randint(0, 5)):
+            c = r.randrange(n_carts)
+            a, b = (0, cp) if r.random() < 0.6 else sorted((r.randint(0, cp), r.randint(0, cp)))
+            run = list(range(c * cp + a, c * cp + b))
+            if r.random() < 0.1:
+                r.shuffle(run)
+            pl += run
+        if forks and r.random() < 0.3:
+            pl = list(r.choice(forks))
+        n = r.choice([1, 1, 2, 5, 9])
+        own = r.choice([0, 1, 7, P, 3 * P + 1])
+        op = -(-own // P)
+        pl += range(nxt, nxt + op)
+        nxt += op
+        L = len(pl) * P - (op * P - own)
+        if L < n:
+            pl, L = pl + [nxt], len(pl) * P + n
+            nxt += 1
+        forks.append(pl[: L // P])
+        q.append(n)
+        kv.append(L)
+        pages.append(pl)
+    return q, kv, pages, P, r.randint(1, 3), r.choice([1, 3, 4, 8]), r.choice([64, 128])
+
+
+@pytest.mark.parametrize("seed", range(300))
+def test_each_key_once(cas, seed):
+    check(cas, *draw(random.Random(seed)))
+
+
+RUNS = dict(prefix=3, many_twice=4, cut=2, pieces=1, few=2, short=0)
+
+
+@pytest.mark.parametrize("case", SHARED, ids=[c["name"] for c in SHARED])
+def test_shared_cases_share(cas, case):
+    """The plans that the GPU tests of shared runs take do share (and the one
+    with runs below the limit does not)."""
+    c = dict(case)
+    name = c.pop("name")
+    Hkv, g, D, P = c["Hkv"], c["g"], c["D"], c["P"]
+    _, _, kv, q, pages = _shared_problem(1400, **c)
+    info = check(cas, q, kv, pages, P, Hkv, g, D)
+    assert info.shared_runs == RUNS[name]
+    assert info.row_blocks == (1 if name in ("few", "short") else 2)

@@ -145,8 +145,11 @@ SHARED = [
     # large pages, runs split into pieces, the last tile of a piece partly past the run
     dict(name="pieces", P=128, D=128, Hkv=1, g=2, n_req=5, n_carts=2, cart_keys=2048, pick=lambda r: [0, 1],
          new=lambda r: 2, own=lambda r: 2 + 100 * r),
-    # below the shortest run worth sharing
-    dict(name="short", P=16, D=64, Hkv=2, g=2, n_req=8, n_carts=2, cart_keys=128, pick=lambda r: [0, 1],
+    # few readers: their rows fit one 16-row block
+    dict(name="few", P=16, D=128, Hkv=2, g=4, n_req=3, n_carts=2, cart_keys=768, pick=lambda r: [0, 1] if r else [0],
+         new=lambda r: 1, own=lambda r: 3 + 9 * r),
+    # below the shortest run worth sharing (in an order in which no two cartridges' page ids continue each other)
+    dict(name="short", P=16, D=64, Hkv=2, g=2, n_req=8, n_carts=3, cart_keys=128, pick=lambda r: [0, 2, 1],
          new=lambda r: 1, own=lambda r: 5),
 ]
 
