@@ -947,8 +947,7 @@ struct SharedRun {
 // stretches of consecutive ids (a cartridge's pages, usually); the ends of all
 // stretches cut the id axis into intervals, each read whole by the same
 // stretches. Lists whose stretches are short (pages scattered over the pool)
-// share nothing here, nor does a call in which a stretch holds more than
-// kMaxDecParts runs. Costs one scan of the lists and a sort of the ends: of
+// share nothing here, nor does a request that holds more than kMaxDecParts runs. Costs one scan of the lists and a sort of the ends: of
 // the 70 us that planning 64 requests with 16,640 pages and 65 runs takes on
 // one host core, 27 (without anything shared 6 of 24).
 std::vector<SharedRun> shared_runs(const cas_decode_problem_t *p, const std::vector<int32_t> &safe_pages,
@@ -996,13 +995,23 @@ std::vector<SharedRun> shared_runs(const cas_decode_problem_t *p, const std::vec
       runs.push_back({0, ends[k + 1] - ends[k], {}});
     }
   }
+  // The runs of a stretch. Requests that hold more than they may have partials read alone.
+  auto runs_of = [&](const Stretch &x) {
+    return std::make_pair(std::lower_bound(starts.begin(), starts.end(), x.id0) - starts.begin(),
+                          std::lower_bound(starts.begin(), starts.end(), x.id1) - starts.begin());
+  };
+  std::vector<int64_t> held(p->batch, 0);
   for (const Stretch &x : st) {
-    size_t r = std::lower_bound(starts.begin(), starts.end(), x.id0) - starts.begin();
-    for (int held = 0; r < starts.size() && starts[r] < x.id1; ++r, ++held) {
-      if (held == kMaxDecParts) return {};
-      const int32_t i = x.at + (starts[r] - x.id0);
-      if (runs[r].users.empty()) runs[r].page0 = p->page_offsets[x.b] + i;
-      runs[r].users.push_back({x.b, i});
+    const auto r = runs_of(x);
+    held[x.b] += r.second - r.first;
+  }
+  for (const Stretch &x : st) {
+    if (held[x.b] > kMaxDecParts) continue;
+    const auto r = runs_of(x);
+    for (auto k = r.first; k < r.second; ++k) {
+      const int32_t i = x.at + (starts[k] - x.id0);
+      if (runs[k].users.empty()) runs[k].page0 = p->page_offsets[x.b] + i;
+      runs[k].users.push_back({x.b, i});
     }
   }
   return runs;
@@ -1078,22 +1087,28 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
     const int64_t nt = ceil_div(p->kv_lens[b], kDecTile);
     for (int k = 0; k < 2; ++k) t_alone[k] += nt * blocks_of[k][b];
   }
-  for (int k = 0; k < 2; ++k) t_shared[k] = t_alone[k];
-  for (SharedRun &r : runs) {
-    int64_t rows = 0, blocks[2] = {0, 0};
-    for (const auto &u : r.users) {
-      rows += rows_of[u.first];
-      for (int k = 0; k < 2; ++k) blocks[k] += blocks_of[k][u.first];
+  const int nb_alone = dp.row_blocks;
+  int nb_shared = nb_alone;
+  bool sharing = false;
+  auto value_runs = [&]() {
+    for (int k = 0; k < 2; ++k) t_shared[k] = t_alone[k];
+    for (SharedRun &r : runs) {
+      int64_t rows = 0, blocks[2] = {0, 0};
+      for (const auto &u : r.users) {
+        rows += rows_of[u.first];
+        for (int k = 0; k < 2; ++k) blocks[k] += blocks_of[k][u.first];
+      }
+      const int64_t nt = ceil_div((int64_t)r.npages * P, kDecTile);
+      for (int k = 0; k < 2; ++k) {
+        r.saved[k] = std::max<int64_t>(0, blocks[k] - ceil_div(rows, kDecRows * (k + 1))) * nt;
+        t_shared[k] -= r.saved[k];
+      }
     }
-    const int64_t nt = ceil_div((int64_t)r.npages * P, kDecTile);
-    for (int k = 0; k < 2; ++k) {
-      r.saved[k] = std::max<int64_t>(0, blocks[k] - ceil_div(rows, kDecRows * (k + 1))) * nt;
-      t_shared[k] -= r.saved[k];
-    }
-  }
-  int nb_shared = dp.row_blocks;
-  if (nb_shared == 1 && t_shared[1] * 10 <= t_shared[0] * 9) nb_shared = 2;
-  bool sharing = t_shared[nb_shared - 1] * 100 <= t_alone[dp.row_blocks - 1] * 85;
+    nb_shared = nb_alone;
+    if (nb_shared == 1 && t_shared[1] * 10 <= t_shared[0] * 9) nb_shared = 2;
+    sharing = t_shared[nb_shared - 1] * 100 <= t_alone[nb_alone - 1] * 85;
+  };
+  value_runs();
 
   // Segments: shared runs, and what is left of each request's pages.
   struct Seg {
@@ -1144,6 +1159,40 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
     else
       for (const auto &u : runs[s.run].users) f(u.first);
   };
+  // Partials of every request in pieces of at most per_wg tiles; the largest count.
+  std::vector<int32_t> parts(B);
+  auto count_parts = [&](int64_t per_wg) {
+    std::fill(parts.begin(), parts.end(), 0);
+    int64_t most = 0;
+    for (const Seg &s : segs) {
+      const int64_t n = ceil_div(s.tiles, per_wg);
+      readers(s, [&](int32_t b) { most = std::max<int64_t>(most, parts[b] = (int32_t)std::min<int64_t>(INT32_MAX, parts[b] + n)); });
+    }
+    return most;
+  };
+  // Workgroups of that cut, which the segments then have (kMaxDecParts pieces each at most).
+  auto set_pieces = [&](int64_t per_wg) {
+    int64_t wgs = 0;
+    for (Seg &s : segs) {
+      s.pieces = (int32_t)std::min<int64_t>(kMaxDecParts, ceil_div(s.tiles, per_wg));
+      int64_t rows = 0;
+      readers(s, [&](int32_t b) { rows += rows_of[b]; });
+      wgs += s.pieces * ceil_div(rows, kDecRows * dp.row_blocks) * Hkv;
+    }
+    return wgs;
+  };
+  cut();
+  if (sharing && count_parts(1 << 30) > kMaxDecParts) {
+    // Requests whose keys fall into more runs and stretches between them than
+    // they may have partials read them by themselves. (The others' runs become
+    // fewer by that, never more.)
+    for (SharedRun &r : runs)
+      r.users.erase(std::remove_if(r.users.begin(), r.users.end(),
+                                   [&](const std::pair<int32_t, int32_t> &u) { return parts[u.first] > kMaxDecParts; }),
+                    r.users.end());
+    value_runs();
+    cut();
+  }
   // Split planning. Without sharing: workgroups of at least 8 tiles (two per
   // wave), about as many as the compute units hold at once (two each), so the
   // whole step runs in one round of workgroups when the requests allow it.
@@ -1151,35 +1200,30 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
   // workgroups need no further cutting while they fill the compute units:
   // pieces of at most 32 tiles, 64 requests over 4 of 256 cartridges of 32 tiles
   // 136 us (143 us with one of at most 85), 50 over 3 of 16 27 us (31 us in
-  // pieces of 8).
+  // pieces of 8). Fewer workgroups than compute units: shorter pieces, as far
+  // as 8 tiles and a request's partials allow; longer runs than its partials
+  // hold in pieces of 32: longer pieces.
   const int64_t cus = device_topology().cus;
-  std::vector<int32_t> parts(B);
-  auto set_pieces = [&](int64_t per_wg) {
-    int64_t wgs = 0;
-    for (Seg &s : segs) {
-      s.pieces = (int32_t)std::min<int64_t>(kMaxDecParts, (s.tiles + per_wg - 1) / per_wg);
-      int64_t rows = 0;
-      readers(s, [&](int32_t b) { rows += rows_of[b]; });
-      wgs += s.pieces * ceil_div(rows, kDecRows * dp.row_blocks) * Hkv;
-    }
-    return wgs;
-  };
+  dp.row_blocks = sharing ? nb_shared : nb_alone;
   int64_t wgs = 0;
-  const int nb_alone = dp.row_blocks;
-  for (;;) {
-    cut();
-    dp.row_blocks = sharing ? nb_shared : nb_alone;
-    if (!sharing) {
-      wgs = set_pieces(std::max<int64_t>(8, ceil_div(t_alone[nb_alone - 1] * Hkv, 2 * cus)));
-    } else {
-      for (int64_t per_wg = 32; (wgs = set_pieces(per_wg)) < cus && per_wg > 8;) per_wg /= 2;
+  if (!sharing) {
+    wgs = set_pieces(std::max<int64_t>(8, ceil_div(t_alone[nb_alone - 1] * Hkv, 2 * cus)));
+  } else {
+    int64_t least = 8;   // the shortest pieces that a request's partials allow
+    if (count_parts(least) > kMaxDecParts) {
+      int64_t most = least;
+      for (const Seg &s : segs) most = std::max<int64_t>(most, s.tiles);
+      while (least + 1 < most) {   // (pieces of `least` are too many, of `most` are not)
+        const int64_t mid = (least + most) / 2;
+        (count_parts(mid) > kMaxDecParts ? least : most) = mid;
+      }
+      least = most;
     }
-    std::fill(parts.begin(), parts.end(), 0);
-    int32_t most = 0;
-    for (const Seg &s : segs) readers(s, [&](int32_t b) { most = std::max(most, parts[b] += s.pieces); });
-    if (most <= kMaxDecParts || !sharing) break;
-    sharing = false;   // too many pieces of one request
+    for (int64_t per_wg = std::max<int64_t>(32, least); (wgs = set_pieces(per_wg)) < cus && per_wg > least;)
+      per_wg = std::max(least, per_wg / 2);
   }
+  std::fill(parts.begin(), parts.end(), 0);
+  for (const Seg &s : segs) readers(s, [&](int32_t b) { parts[b] += s.pieces; });
   if (wgs > INT32_MAX) return fail(CAS_ERR_UNSUPPORTED, "too many workgroups");
   dp.tok_parts.resize(Tq);
   for (int b = 0; b < B; ++b) {

@@ -109,3 +109,56 @@ def test_shared_cases_share(cas, case):
     info = check(cas, q, kv, pages, P, Hkv, g, D)
     assert info.shared_runs == RUNS[name]
     assert info.row_blocks == (1 if name in ("few", "short") else 2)
+
+
+@pytest.mark.parametrize("Hkv", [1, 2, 4, 8])
+@pytest.mark.parametrize("keys", [1024, 16384, 32768, 60000, 65536, 250000])
+@pytest.mark.parametrize("n_req", [2, 8, 16])
+def test_one_run_of_any_length_is_streamed_once(cas, Hkv, keys, n_req):
+    """One-token requests over one run of pages and a few keys of their own:
+    the run is streamed once per 32 rows of its readers however long it is,
+    and no request has more than 64 partials."""
+    P, g, own = 16, 4, 50
+    run = list(range(keys // P))
+    op = -(-own // P)
+    pages = [run + [len(run) + r * op + j for j in range(op)] for r in range(n_req)]
+    kv = [len(run) * P + own] * n_req
+    info, _, _ = cas.decode_plan(problem(cas, [1] * n_req, kv, pages, P, Hkv, g, 128))
+    assert info.shared_runs == 1 and info.max_partials <= 64
+    # Once per 32 rows, the own keys per request; a piece's last tile may be partly past the run.
+    assert info.key_tiles == Hkv * (-(-n_req * g // 32) * -(-len(run) * P // TILE) + n_req * -(-own // TILE))
+    if keys <= 16384:
+        check(cas, [1] * n_req, kv, pages, P, Hkv, g, 128)
+
+
+@pytest.mark.parametrize("many", [60, 63, 64, 65, 70, 100])
+def test_a_request_over_too_many_runs_reads_alone(cas, many):
+    """15 requests over the same 4 cartridges and two over `many` others: past
+    64 partials each (the runs and its own keys) these two read their keys by
+    themselves, and the others still share."""
+    P, cp, Hkv = 16, 16, 2
+    cart = lambda c: [c * cp + j for j in range(cp)]
+    pages = [sum((cart(2 * c + 1) for c in range(4)), []) for _ in range(15)]
+    pages += [sum((cart(2 * c) for c in range(many)), []) for _ in range(2)]
+    kv = [len(pl) * P + 13 for pl in pages]
+    for r, pl in enumerate(pages):
+        pl.append(2 * cp * many + r)
+    info = check(cas, [1] * 17, kv, pages, P, Hkv, 4, 64)
+    shared = 4 * 8 * -(-60 // (16 * info.row_blocks)) + 15   # 60 rows; a tile of their own each
+    wide = many * 8 + 2 if many < 64 else 2 * (many * 8 + 1)
+    assert info.key_tiles == Hkv * (shared + wide)
+    assert info.shared_runs == (4 + many if many < 64 else 4)
+
+
+def test_a_request_over_the_whole_pool_reads_alone(cas):
+    """Eight requests in pairs over 20 cartridges each, and one whose pages are
+    the whole pool in one stretch: it holds 80 runs and reads alone, the pairs share."""
+    P, cp, Hkv = 16, 16, 2
+    pages = [[(40 * (r // 2) + 2 * c) * cp + j for c in range(20) for j in range(cp)] for r in range(8)]
+    pages.append(list(range(160 * cp)))
+    kv = [len(pl) * P + 13 for pl in pages]
+    for r, pl in enumerate(pages):
+        pl.append(160 * cp + r)
+    info = check(cas, [1] * 9, kv, pages, P, Hkv, 4, 64)
+    assert info.shared_runs == 80
+    assert info.key_tiles == Hkv * (80 * 8 + 8 + 160 * 8 + 1)
