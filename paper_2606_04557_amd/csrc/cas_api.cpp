@@ -933,86 +933,137 @@ struct DecodePlan {
   size_t off_work = 0, off_pages = 0, off_tokparts = 0, off_plse = 0, off_po = 0, bytes = 0;
 };
 
-// A run of consecutive page ids that several requests read: page_ids[page0 ..
-// page0 + npages) of its first reader, and the (request, index of the run in
-// its page list) of every reader.
-struct SharedRun {
-  int32_t page0, npages;
-  std::vector<std::pair<int32_t, int32_t>> users;
-  int64_t saved[2] = {0, 0};   // tiles of one KV head saved in blocks of 16 and of 32 rows
+// Consecutive page ids [id0, id1) from index `at` of request b's page list, and
+// the shared runs [run0, run1) that it holds, whole and in order.
+struct Stretch {
+  uint32_t id0, id1;
+  int32_t b, at;
+  int32_t run0, run1;
 };
 
-// Runs of at least min_pages that are read at least twice. The pages that every
-// query of a request sees (the first safe_pages of its list) fall into
-// stretches of consecutive ids (a cartridge's pages, usually); the ends of all
-// stretches cut the id axis into intervals, each read whole by the same
-// stretches. Lists whose stretches are short (pages scattered over the pool)
-// share nothing here, nor does a request that holds more than kMaxDecParts runs. Costs one scan of the lists and a sort of the ends: of
-// the 70 us that planning 64 requests with 16,640 pages and 65 runs takes on
-// one host core, 27 (without anything shared 6 of 24).
-std::vector<SharedRun> shared_runs(const cas_decode_problem_t *p, const std::vector<int32_t> &safe_pages,
-                                   int min_pages) {
-  struct Stretch {
-    int32_t id0, id1, b, at;   // pages [id0, id1) from index `at` of request b's list
-  };
+// A run of page ids that several requests read: npages from id0, first found at
+// page_ids[page0]. Its readers are users[user0 .. user0 + nusers).
+struct SharedRun {
+  uint32_t id0;
+  int32_t npages, page0;
+  int32_t user0, nusers;
+  int64_t saved[2];   // tiles of one KV head saved in blocks of 16 and of 32 rows
+};
+
+// Whether ids[0 .. n) are consecutive.
+inline bool consecutive(const int32_t *ids, int32_t n) {
+  uint32_t off = 0;
+  for (int32_t k = 0; k < n; ++k) off |= (uint32_t)ids[k] ^ ((uint32_t)ids[0] + (uint32_t)k);
+  return off == 0;
+}
+
+// The stretches of at least min_pages pages among the first safe_pages of every
+// request's list, in order. One of that length holds one of every min_pages
+// indices, so scattered pages cost a look at every min_pages-th of them.
+std::vector<Stretch> stretches(const cas_decode_problem_t *p, const std::vector<int32_t> &safe_pages, int min_pages) {
   std::vector<Stretch> st;
   for (int b = 0; b < p->batch; ++b) {
     const int32_t *ids = p->page_ids + p->page_offsets[b];
     const int32_t n = safe_pages[b];
-    for (int32_t i = 0; i < n;) {
-      int32_t e = i + 1;
-      for (; e + 16 <= n; e += 16) {
-        int32_t off = 0;
-        for (int k = 0; k < 16; ++k) off |= ids[e + k] ^ (ids[i] + (e - i) + k);
-        if (off) break;
-      }
-      while (e < n && ids[e] == ids[e - 1] + 1) ++e;
-      if (e - i >= min_pages) st.push_back({ids[i], ids[i] + (e - i), b, i});
-      i = e;
+    for (int32_t from = 0, j = min_pages - 1; j < n; j = from + min_pages - 1) {
+      int32_t i = j, e = j + 1;
+      if (consecutive(ids + from, min_pages)) i = from;
+      while (i > from && ids[i] - ids[i - 1] == 1) --i;
+      if (e < n && ids[e] - ids[e - 1] == 1)
+        while (e + 16 <= n && consecutive(ids + e - 1, 17)) e += 16;
+      while (e < n && ids[e] - ids[e - 1] == 1) ++e;
+      if (e - i >= min_pages) st.push_back({(uint32_t)ids[i], (uint32_t)ids[i] + (uint32_t)(e - i), b, i, 0, 0});
+      from = e;
     }
   }
+  return st;
+}
+
+// Sorts by the upper 32 bits: short lists by comparison, longer ones by 11 bits
+// at a time (2,560 ends 10 us, by comparison 110 us).
+void sort_by_id(std::vector<uint64_t> &v) {
+  if (v.size() < 96) {
+    std::sort(v.begin(), v.end());
+    return;
+  }
+  uint64_t most = 0;
+  for (uint64_t x : v) most |= x;
+  std::vector<uint64_t> w(v.size());
+  for (int sh = 32; sh < 64 && most >> sh; sh += 11) {
+    uint32_t at[2048] = {};
+    for (uint64_t x : v) ++at[x >> sh & 2047];
+    uint32_t sum = 0;
+    for (uint32_t &a : at) {
+      const uint32_t n = a;
+      a = sum;
+      sum += n;
+    }
+    for (uint64_t x : v) w[at[x >> sh & 2047]++] = x;
+    v.swap(w);
+  }
+}
+
+// Runs of at least min_pages that are read at least twice, by id. The ends of
+// all stretches cut the id axis into intervals, each read whole by the same
+// stretches. Requests usually read whole cartridges, so equal stretches are
+// counted together and only the distinct ones' ends are sorted. On one host
+// core a plan of 64 requests over 4 of 256 cartridges (16,640 pages, 65 runs)
+// takes 33 us, 11 of them to find and value the runs, over 60 of 80 cartridges
+// (61,760 pages, 80 runs) 170 us; with as many private or scattered pages 15
+// and 12 us.
+std::vector<SharedRun> shared_runs(std::vector<Stretch> &st, int min_pages) {
   std::vector<SharedRun> runs;
   if (st.size() < 2) return runs;
-  std::vector<int32_t> ends;
-  ends.reserve(2 * st.size());
-  for (const Stretch &x : st) {
-    ends.push_back(x.id0);
-    ends.push_back(x.id1);
-  }
-  std::sort(ends.begin(), ends.end());
-  ends.erase(std::unique(ends.begin(), ends.end()), ends.end());
-  auto index = [&](int32_t id) { return std::lower_bound(ends.begin(), ends.end(), id) - ends.begin(); };
-  std::vector<int32_t> readers(ends.size(), 0);   // of interval [ends[k], ends[k + 1]): summed from the differences
-  for (const Stretch &x : st) {
-    ++readers[index(x.id0)];
-    --readers[index(x.id1)];
-  }
-  std::vector<int32_t> starts;                    // first page of every run
-  for (size_t k = 0; k + 1 < ends.size(); ++k) {
-    if (k > 0) readers[k] += readers[k - 1];
-    if (readers[k] >= 2 && ends[k + 1] - ends[k] >= min_pages) {
-      starts.push_back(ends[k]);
-      runs.push_back({0, ends[k + 1] - ends[k], {}});
-    }
-  }
-  // The runs of a stretch. Requests that hold more than they may have partials read alone.
-  auto runs_of = [&](const Stretch &x) {
-    return std::make_pair(std::lower_bound(starts.begin(), starts.end(), x.id0) - starts.begin(),
-                          std::lower_bound(starts.begin(), starts.end(), x.id1) - starts.begin());
+  struct Distinct {
+    uint32_t id0, id1;
+    int32_t readers, run0, run1;
   };
-  std::vector<int64_t> held(p->batch, 0);
-  for (const Stretch &x : st) {
-    const auto r = runs_of(x);
-    held[x.b] += r.second - r.first;
-  }
-  for (const Stretch &x : st) {
-    if (held[x.b] > kMaxDecParts) continue;
-    const auto r = runs_of(x);
-    for (auto k = r.first; k < r.second; ++k) {
-      const int32_t i = x.at + (starts[k] - x.id0);
-      if (runs[k].users.empty()) runs[k].page0 = p->page_offsets[x.b] + i;
-      runs[k].users.push_back({x.b, i});
+  size_t cap = 4;
+  while (cap < 2 * st.size()) cap *= 2;
+  std::vector<int32_t> slot(cap, -1), which(st.size());
+  std::vector<Distinct> ds;
+  ds.reserve(st.size());
+  for (size_t i = 0; i < st.size(); ++i) {
+    const Stretch &x = st[i];
+    size_t h = (size_t)((x.id0 * 0x9e3779b97f4a7c15ull + x.id1 * 0xc2b2ae3d27d4eb4full) >> 32);
+    for (;; ++h) {
+      int32_t &k = slot[h & (cap - 1)];
+      if (k < 0) {
+        k = (int32_t)ds.size();
+        ds.push_back({x.id0, x.id1, 0, 0, 0});
+      }
+      if (ds[k].id0 != x.id0 || ds[k].id1 != x.id1) continue;
+      ++ds[k].readers;
+      which[i] = k;
+      break;
     }
+  }
+  // The ends in order of id, each with its place in ds.
+  std::vector<uint64_t> ends(2 * ds.size());
+  for (size_t k = 0; k < ds.size(); ++k) {
+    ends[2 * k] = (uint64_t)ds[k].id0 << 32 | 2 * k;
+    ends[2 * k + 1] = (uint64_t)ds[k].id1 << 32 | (2 * k + 1);
+  }
+  sort_by_id(ends);
+  // Readers of the interval from one id to the next, summed from the
+  // differences; run0 and run1 of an end: the runs that lie before it.
+  int32_t readers = 0;
+  for (size_t k = 0; k < ends.size();) {
+    const uint32_t id = (uint32_t)(ends[k] >> 32);
+    for (; k < ends.size() && (uint32_t)(ends[k] >> 32) == id; ++k) {
+      Distinct &d = ds[(uint32_t)ends[k] / 2];
+      const bool last = ends[k] & 1;
+      (last ? d.run1 : d.run0) = (int32_t)runs.size();
+      readers += last ? -d.readers : d.readers;
+    }
+    if (readers < 2 || k == ends.size()) continue;
+    const uint32_t n = (uint32_t)(ends[k] >> 32) - id;
+    if (n >= (uint32_t)min_pages) runs.push_back({id, (int32_t)n, -1, 0, 0, {0, 0}});
+  }
+  if (runs.empty()) return runs;
+  for (size_t i = 0; i < st.size(); ++i) {
+    st[i].run0 = ds[which[i]].run0;
+    st[i].run1 = ds[which[i]].run1;
   }
   return runs;
 }
@@ -1047,8 +1098,11 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
   }
   const int64_t Tq = p->q_offsets[B];
   if (Tq * Hq > INT32_MAX) return fail(CAS_ERR_UNSUPPORTED, "query tokens * heads above 2^31");
-  for (int32_t i = 0; i < p->page_offsets[B]; ++i)
-    if (p->page_ids[i] < 0 || p->page_ids[i] >= p->num_pages)
+  const uint32_t last_page = (uint32_t)(std::min<int64_t>(p->num_pages, (int64_t)1 << 31) - 1);
+  uint32_t most_id = 0;   // (a negative id counts as one above every valid one)
+  for (int32_t i = 0; i < p->page_offsets[B]; ++i) most_id = std::max(most_id, (uint32_t)p->page_ids[i]);
+  for (int32_t i = 0; most_id > last_page; ++i)
+    if ((uint32_t)p->page_ids[i] > last_page)
       return fail(CAS_ERR_INVALID_ARGUMENT, "page id " + std::to_string(i) + " out of range");
   dp.Tq = (int)Tq;
   dp.Hq = (int)Hq;
@@ -1070,6 +1124,7 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
   // its own costs about three tiles), the call when it streams at most 0.85 of
   // the tiles; two row blocks instead of one have to save another tenth.
   constexpr int kMinSharedTiles = 8;
+  std::vector<Stretch> st;
   std::vector<SharedRun> runs;
   if (B > 1 && Tq * g <= (1 << 14)) {   // (longer query blocks would only grow the table of rows)
     std::vector<int32_t> safe(B);
@@ -1078,95 +1133,135 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
       const int32_t n = p->q_offsets[b + 1] - p->q_offsets[b];
       safe[b] = (p->kv_lens[b] - n + 1) / P;
     }
-    runs = shared_runs(p, safe, std::max<int>(1, kMinSharedTiles * kDecTile / P));
+    const int min_pages = std::max<int>(1, kMinSharedTiles * kDecTile / P);
+    st = stretches(p, safe, min_pages);
+    runs = shared_runs(st, min_pages);
   }
   // Streamed key tiles of one KV head, every request on its own and with what
   // the shared runs save, in blocks of 16 and of 32 rows.
-  int64_t t_alone[2] = {0, 0}, t_shared[2];
+  int64_t t_alone[2] = {0, 0};
   for (int b = 0; b < B; ++b) {
     const int64_t nt = ceil_div(p->kv_lens[b], kDecTile);
     for (int k = 0; k < 2; ++k) t_alone[k] += nt * blocks_of[k][b];
   }
   const int nb_alone = dp.row_blocks;
   int nb_shared = nb_alone;
-  bool sharing = false;
+  // Whether sharing pays, with the requests that read alone left out, and the
+  // runs' readers and savings. Only runs that save anything are shared.
+  std::vector<uint8_t> alone(B, 0);
+  struct Sum {
+    int64_t rows, blocks[2];
+  };
+  std::vector<Sum> sums;
   auto value_runs = [&]() {
-    for (int k = 0; k < 2; ++k) t_shared[k] = t_alone[k];
-    for (SharedRun &r : runs) {
-      int64_t rows = 0, blocks[2] = {0, 0};
-      for (const auto &u : r.users) {
-        rows += rows_of[u.first];
-        for (int k = 0; k < 2; ++k) blocks[k] += blocks_of[k][u.first];
+    if (runs.empty()) return false;
+    sums.assign(runs.size(), Sum{0, {0, 0}});
+    for (SharedRun &r : runs) r.nusers = 0;
+    for (const Stretch &x : st) {
+      if (alone[x.b]) continue;
+      for (int32_t k = x.run0; k < x.run1; ++k) {
+        SharedRun &r = runs[k];
+        ++r.nusers;
+        if (r.page0 < 0) r.page0 = p->page_offsets[x.b] + x.at + (int32_t)(r.id0 - x.id0);
+        sums[k].rows += rows_of[x.b];
+        for (int i = 0; i < 2; ++i) sums[k].blocks[i] += blocks_of[i][x.b];
       }
-      const int64_t nt = ceil_div((int64_t)r.npages * P, kDecTile);
-      for (int k = 0; k < 2; ++k) {
-        r.saved[k] = std::max<int64_t>(0, blocks[k] - ceil_div(rows, kDecRows * (k + 1))) * nt;
-        t_shared[k] -= r.saved[k];
+    }
+    int64_t t[2] = {t_alone[0], t_alone[1]};
+    for (size_t k = 0; k < runs.size(); ++k) {
+      const int64_t nt = ceil_div((int64_t)runs[k].npages * P, kDecTile);
+      for (int i = 0; i < 2; ++i) {
+        runs[k].saved[i] = std::max<int64_t>(0, sums[k].blocks[i] - ceil_div(sums[k].rows, kDecRows * (i + 1))) * nt;
+        t[i] -= runs[k].saved[i];
       }
     }
     nb_shared = nb_alone;
-    if (nb_shared == 1 && t_shared[1] * 10 <= t_shared[0] * 9) nb_shared = 2;
-    sharing = t_shared[nb_shared - 1] * 100 <= t_alone[nb_alone - 1] * 85;
+    if (nb_shared == 1 && t[1] * 10 <= t[0] * 9) nb_shared = 2;
+    return t[nb_shared - 1] * 100 <= t_alone[nb_alone - 1] * 85;
   };
-  value_runs();
+  auto is_shared = [&](int32_t k) { return runs[k].saved[nb_shared - 1] > 0; };
+  // f(request, run or -1, first page, one past the last) for the pieces of the
+  // requests' page lists, in order: shared runs and what lies between them.
+  bool sharing = false;
+  auto pieces = [&](auto &&f) {
+    size_t i = 0;
+    for (int b = 0; b < B; ++b) {
+      const int32_t np = p->page_offsets[b + 1] - p->page_offsets[b];
+      int32_t at = 0;
+      if (sharing)
+        for (; i < st.size() && st[i].b == b; ++i) {
+          if (alone[b]) continue;
+          for (int32_t k = st[i].run0; k < st[i].run1; ++k) {
+            if (!is_shared(k)) continue;
+            const int32_t first = st[i].at + (int32_t)(runs[k].id0 - st[i].id0);
+            if (first > at) f(b, -1, at, first);
+            at = first + runs[k].npages;
+            f(b, k, first, at);
+          }
+        }
+      if (np > at) f(b, -1, at, np);
+    }
+  };
+  std::vector<int32_t> parts(B, 0);   // partials of every request
+  if (!runs.empty()) {
+    // Requests over more runs than they may have partials read their keys by
+    // themselves; so do those whose runs and stretches between them are more.
+    // (The others' runs become fewer by that, never more.)
+    for (const Stretch &x : st) parts[x.b] = (int32_t)std::min<int64_t>(kMaxDecParts + 1, (int64_t)parts[x.b] + (x.run1 - x.run0));
+    for (int b = 0; b < B; ++b) alone[b] = parts[b] > kMaxDecParts;
+    sharing = value_runs();
+    if (sharing) {
+      std::fill(parts.begin(), parts.end(), 0);
+      bool more = false;
+      pieces([&](int32_t b, int32_t, int32_t, int32_t) { ++parts[b]; });
+      for (int b = 0; b < B; ++b)
+        if (parts[b] > kMaxDecParts) more = alone[b] = 1;
+      if (more) sharing = value_runs();
+    }
+  }
 
-  // Segments: shared runs, and what is left of each request's pages.
+  // Segments: the shared runs, then what is left of each request's pages.
   struct Seg {
     int32_t page0, nkeys, full, tiles;
-    int32_t run, b;   // the run, or -1 and the only reader
-    bool own_end;     // holds the end of the reader's keys
+    int32_t user0, nusers;   // readers: users[user0 ..]
+    int32_t rows;            // of all its readers
+    bool own_end;            // holds the end of its reader's keys
     int32_t pieces;
   };
   std::vector<Seg> segs;
-  struct Range {
-    int32_t b, first, last;   // shared pages [first, last) of request b's list
-  };
-  std::vector<Range> taken;
-  auto cut = [&]() {
-    segs.clear();
-    taken.clear();
-    dp.shared = 0;
-    if (sharing)
-      for (size_t k = 0; k < runs.size(); ++k) {
-        const SharedRun &r = runs[k];
-        if (r.saved[nb_shared - 1] == 0) continue;
-        segs.push_back({r.page0, r.npages * P, r.npages * P - 1, (r.npages * P + kDecTile - 1) / kDecTile, (int32_t)k, 0, false, 0});
-        ++dp.shared;
-        for (const auto &u : r.users) taken.push_back({u.first, u.second, u.second + r.npages});
-      }
-    std::sort(taken.begin(), taken.end(), [](const Range &x, const Range &y) { return x.b != y.b ? x.b < y.b : x.first < y.first; });
-    size_t k = 0;
-    for (int b = 0; b < B; ++b) {
-      const int32_t np = p->page_offsets[b + 1] - p->page_offsets[b], L = p->kv_lens[b];
-      const int32_t n = p->q_offsets[b + 1] - p->q_offsets[b];
-      int32_t at = 0;
-      for (;;) {
-        const bool more = k < taken.size() && taken[k].b == b;
-        const int32_t to = more ? taken[k].first : np;
-        if (to > at) {
-          const bool end = to == np;
-          const int32_t nkeys = (end ? L : to * P) - at * P;
-          segs.push_back({p->page_offsets[b] + at, nkeys, end ? nkeys - n : nkeys - 1, (nkeys + kDecTile - 1) / kDecTile, -1, b, end, 0});
-        }
-        if (!more) break;
-        at = taken[k++].last;
-      }
+  std::vector<int32_t> users;
+  if (sharing) {
+    int32_t n = 0;
+    for (size_t k = 0; k < runs.size(); ++k) {
+      SharedRun &r = runs[k];
+      if (!is_shared((int32_t)k)) continue;
+      const int32_t nkeys = r.npages * P;
+      r.user0 = n;
+      n += r.nusers;
+      segs.push_back({r.page0, nkeys, nkeys - 1, (nkeys + kDecTile - 1) / kDecTile, r.user0, r.nusers, (int32_t)sums[k].rows, false, 0});
     }
-  };
-  // f(request) for every reader of a segment.
-  auto readers = [&](const Seg &s, auto &&f) {
-    if (s.run < 0) f(s.b);
-    else
-      for (const auto &u : runs[s.run].users) f(u.first);
-  };
-  // Partials of every request in pieces of at most per_wg tiles; the largest count.
-  std::vector<int32_t> parts(B);
+    users.resize(n);
+  }
+  dp.shared = (int)segs.size();
+  pieces([&](int32_t b, int32_t run, int32_t first, int32_t to) {
+    if (run >= 0) {
+      users[runs[run].user0++] = b;
+      return;
+    }
+    const int32_t np = p->page_offsets[b + 1] - p->page_offsets[b], n = p->q_offsets[b + 1] - p->q_offsets[b];
+    const bool end = to == np;
+    const int32_t nkeys = (end ? p->kv_lens[b] : to * P) - first * P;
+    segs.push_back({p->page_offsets[b] + first, nkeys, end ? nkeys - n : nkeys - 1, (nkeys + kDecTile - 1) / kDecTile,
+                    (int32_t)users.size(), 1, rows_of[b], end, 0});
+    users.push_back(b);
+  });
+  // Partials in pieces of at most per_wg tiles: the largest count of a request.
   auto count_parts = [&](int64_t per_wg) {
     std::fill(parts.begin(), parts.end(), 0);
-    int64_t most = 0;
+    int32_t most = 0;
     for (const Seg &s : segs) {
-      const int64_t n = ceil_div(s.tiles, per_wg);
-      readers(s, [&](int32_t b) { most = std::max<int64_t>(most, parts[b] = (int32_t)std::min<int64_t>(INT32_MAX, parts[b] + n)); });
+      const int32_t n = (int32_t)ceil_div(s.tiles, per_wg);
+      for (int32_t u = s.user0; u < s.user0 + s.nusers; ++u) most = std::max(most, parts[users[u]] += n);
     }
     return most;
   };
@@ -1175,24 +1270,10 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
     int64_t wgs = 0;
     for (Seg &s : segs) {
       s.pieces = (int32_t)std::min<int64_t>(kMaxDecParts, ceil_div(s.tiles, per_wg));
-      int64_t rows = 0;
-      readers(s, [&](int32_t b) { rows += rows_of[b]; });
-      wgs += s.pieces * ceil_div(rows, kDecRows * dp.row_blocks) * Hkv;
+      wgs += s.pieces * ceil_div(s.rows, kDecRows * dp.row_blocks) * Hkv;
     }
     return wgs;
   };
-  cut();
-  if (sharing && count_parts(1 << 30) > kMaxDecParts) {
-    // Requests whose keys fall into more runs and stretches between them than
-    // they may have partials read them by themselves. (The others' runs become
-    // fewer by that, never more.)
-    for (SharedRun &r : runs)
-      r.users.erase(std::remove_if(r.users.begin(), r.users.end(),
-                                   [&](const std::pair<int32_t, int32_t> &u) { return parts[u.first] > kMaxDecParts; }),
-                    r.users.end());
-    value_runs();
-    cut();
-  }
   // Split planning. Without sharing: workgroups of at least 8 tiles (two per
   // wave), about as many as the compute units hold at once (two each), so the
   // whole step runs in one round of workgroups when the requests allow it.
@@ -1223,8 +1304,12 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
       per_wg = std::max(least, per_wg / 2);
   }
   std::fill(parts.begin(), parts.end(), 0);
-  for (const Seg &s : segs) readers(s, [&](int32_t b) { parts[b] += s.pieces; });
-  if (wgs > INT32_MAX) return fail(CAS_ERR_UNSUPPORTED, "too many workgroups");
+  int64_t nrows = 0;
+  for (const Seg &s : segs) {
+    nrows += s.rows;
+    for (int32_t u = s.user0; u < s.user0 + s.nusers; ++u) parts[users[u]] += s.pieces;
+  }
+  if (wgs > INT32_MAX || nrows > INT32_MAX) return fail(CAS_ERR_UNSUPPORTED, "too many workgroups");
   dp.tok_parts.resize(Tq);
   for (int b = 0; b < B; ++b) {
     dp.max_parts = std::max(dp.max_parts, parts[b]);
@@ -1232,32 +1317,25 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
   }
   // Rows and workgroups. The workgroups go longest range first, ties in the
   // order of segment, KV head, row block, piece: the first walk counts the
-  // lengths, the second puts each workgroup in its place.
+  // lengths (a segment's pieces have two at most), the second puts each
+  // workgroup in its place.
   const int rows_per_wg = kDecRows * dp.row_blocks;
-  struct Span {
-    int32_t t0, t1;
-  };
-  auto span = [](const Seg &s, int32_t i) {
-    return Span{(int32_t)((int64_t)s.tiles * i / s.pieces), (int32_t)((int64_t)s.tiles * (i + 1) / s.pieces)};
-  };
-  std::vector<int32_t> next_part(B, 0), row0(segs.size() + 1, 0);
+  std::vector<int32_t> next_part(B, 0);
   std::map<int32_t, int64_t, std::greater<int32_t>> at;   // length -> workgroups, then the next one's place
-  for (size_t k = 0; k < segs.size(); ++k) {
-    const Seg &s = segs[k];
-    readers(s, [&](int32_t b) {
-      const int32_t q0 = p->q_offsets[b], n = p->q_offsets[b + 1] - q0;
+  dp.rows.resize((size_t)nrows);
+  DevDecodeRow *row = dp.rows.data();
+  for (const Seg &s : segs) {
+    for (int32_t u = s.user0; u < s.user0 + s.nusers; ++u) {
+      const int32_t b = users[u], q0 = p->q_offsets[b], n = p->q_offsets[b + 1] - q0;
       const int32_t part = parts[b] > 1 ? next_part[b] : -1;
       for (int32_t i = 0; i < n; ++i)
-        for (int32_t h = 0; h < g; ++h)
-          dp.rows.push_back({(q0 + i) * (int32_t)Hq + h, s.own_end ? s.full + i : s.nkeys - 1, part});
+        for (int32_t h = 0; h < g; ++h) *row++ = {(q0 + i) * (int32_t)Hq + h, s.own_end ? s.full + i : s.nkeys - 1, part};
       next_part[b] += s.pieces;
-    });
-    row0[k + 1] = (int32_t)dp.rows.size();
-    const int64_t wgs_of_piece = ceil_div(row0[k + 1] - row0[k], rows_per_wg) * Hkv;
-    for (int32_t i = 0; i < s.pieces; ++i) {
-      const Span t = span(s, i);
-      at[t.t1 - t.t0] += wgs_of_piece;
     }
+    const int64_t wgs_of_piece = ceil_div(s.rows, rows_per_wg) * Hkv;
+    const int32_t longer = s.tiles % s.pieces;
+    at[s.tiles / s.pieces] += (s.pieces - longer) * wgs_of_piece;
+    if (longer) at[s.tiles / s.pieces + 1] += longer * wgs_of_piece;
   }
   int64_t place = 0;
   for (auto &x : at) {
@@ -1266,21 +1344,27 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
     place += n;
   }
   dp.work.resize((size_t)wgs);
-  std::vector<Span> spans;
-  std::vector<int64_t *> places;
-  for (size_t k = 0; k < segs.size(); ++k) {
-    const Seg &s = segs[k];
-    spans.resize(s.pieces);
-    places.resize(s.pieces);
-    for (int32_t i = 0; i < s.pieces; ++i) {
-      spans[i] = span(s, i);
-      places[i] = &at[spans[i].t1 - spans[i].t0];
+  struct Piece {
+    int32_t t0, t1;
+    int64_t *place;
+  };
+  std::vector<Piece> cut;
+  int32_t row0 = 0;
+  for (const Seg &s : segs) {
+    const int32_t len = s.tiles / s.pieces;
+    int64_t *const places[2] = {&at[len], s.tiles % s.pieces ? &at[len + 1] : nullptr};
+    cut.resize(s.pieces);
+    for (int32_t i = 0, t0 = 0; i < s.pieces; ++i) {
+      const int32_t t1 = (int32_t)((int64_t)s.tiles * (i + 1) / s.pieces);
+      cut[i] = {t0, t1, places[t1 - t0 - len]};
+      t0 = t1;
     }
     for (int kvh = 0; kvh < Hkv; ++kvh)
-      for (int32_t r = row0[k]; r < row0[k + 1]; r += rows_per_wg)
+      for (int32_t r = 0; r < s.rows; r += rows_per_wg)
         for (int32_t i = 0; i < s.pieces; ++i)
-          dp.work[(*places[i])++] = {s.page0, s.nkeys, s.full, kvh, spans[i].t0, spans[i].t1, r,
-                                     std::min(rows_per_wg, row0[k + 1] - r), i};
+          dp.work[(*cut[i].place)++] = {s.page0, s.nkeys, s.full, kvh, cut[i].t0, cut[i].t1, row0 + r,
+                                        std::min(rows_per_wg, s.rows - r), i};
+    row0 += s.rows;
   }
   size_t off = align_up(dp.rows.size() * sizeof(DevDecodeRow), 256);
   dp.off_work = off;
@@ -1289,7 +1373,6 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
   off = align_up(off + (size_t)p->page_offsets[B] * sizeof(int32_t), 256);
   dp.off_tokparts = off;
   off = align_up(off + (size_t)Tq * sizeof(int32_t), 256);
-  const size_t table_end = off;
   if (dp.max_parts > 1) {
     const size_t plane = (size_t)Tq * Hq;
     dp.off_plse = off;
@@ -1298,7 +1381,6 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
     off = align_up(off + (size_t)dp.max_parts * plane * p->head_dim * 4, 256);
   }
   dp.bytes = off;
-  (void)table_end;
   return CAS_OK;
 }
 

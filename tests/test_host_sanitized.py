@@ -33,7 +33,7 @@ def test_host_code_under_asan_and_ubsan(tmp_path):
     env["ASAN_OPTIONS"] = f"detect_leaks=0:abort_on_error=1:log_path={log}"
     env["UBSAN_OPTIONS"] = f"print_stacktrace=1:log_path={log}"
     r = subprocess.run([sys.executable, "-m", "pytest", "-q", "-x", "-p", "no:cacheprovider",
-                        "tests/test_host_lib.py", "tests/test_pool_policy.py"],
+                        "tests/test_host_lib.py", "tests/test_pool_policy.py", "tests/test_decode_plan.py"],
                        cwd=ROOT, env=env, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True,
                        timeout=600)
     reports = "".join(open(f).read() for f in glob.glob(log + "*"))
