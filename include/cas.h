@@ -446,6 +446,10 @@ cas_status_t cas_pool_read_moments(cas_pool_t *pool, int32_t cart, float *dst);
 const char *cas_status_string(cas_status_t s);
 /* Message of the last failed call on this thread ("" if none). */
 const char *cas_last_error_message(void);
+/* Workspace bytes that the last call on this thread which returned
+ * CAS_ERR_WORKSPACE needs (0 before any): what the size query for that call
+ * would return. */
+size_t cas_last_workspace_needed(void);
 /* CAS_ABI_VERSION of the built library. */
 int32_t cas_abi_version(void);
 

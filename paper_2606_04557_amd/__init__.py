@@ -19,7 +19,7 @@ __all__ = ["Segment", "Problem", "CasError", "load", "prefix_attn_fwd", "prefix_
            "prefix_attn_bwd",
            "workspace_size", "plan_info", "set_tuning", "get_tuning", "cartridge_stage",
            "timing_enable", "timing_reset", "timing_read", "AdamCartridge", "adam_lr_scale",
-           "cartridge_adam", "DecodeProblem", "paged_decode_fwd", "plan_rotation", "CartridgePool"]
+           "cartridge_adam", "DecodeProblem", "paged_decode_fwd", "decode_plan", "plan_rotation", "CartridgePool"]
 
 
 class CasError(RuntimeError):
@@ -173,16 +173,17 @@ def _workspace(nbytes: int, device):
 
 
 def _with_workspace(call, size, workspace, device) -> None:
-    """call(ptr, bytes) with the caller's workspace, or, without one or where
-    the library finds it too small (before it enqueues anything), with a new
-    one of size() bytes. The library's own check stands in for asking for the
-    size first, which plans the whole problem a second time."""
-    if workspace is not None:
-        status = call(workspace.data_ptr(), workspace.numel())
-        if status != _lib.CAS_ERR_WORKSPACE:
-            return _check(status)
-    ws = _workspace(size(), device)
-    _check(call(ws.data_ptr(), ws.numel()))
+    """call(ptr, bytes) with the caller's workspace, or, without one, with a
+    new one of size() bytes. The library's own check stands in for asking for
+    the size first, which plans the whole problem a second time; where it finds
+    the workspace too small (before it enqueues anything) it has the size that
+    the call needs."""
+    ws = workspace if workspace is not None else _workspace(size(), device)
+    status = call(ws.data_ptr(), ws.numel())
+    if status == _lib.CAS_ERR_WORKSPACE:
+        ws = _workspace(load().cas_last_workspace_needed(), device)
+        status = call(ws.data_ptr(), ws.numel())
+    _check(status)
 
 
 def prefix_attn_fwd(q, k_self, v_self, rows: Sequence[Sequence[Segment]], num_kv_heads: int,
@@ -330,16 +331,7 @@ class DecodeProblem:
         self._kv = (ctypes.c_int32 * max(B, 1))(*[int(x) for x in kv_lens])
         self._po = (ctypes.c_int32 * (B + 1))(*po)
         self._ids = (ctypes.c_int32 * max(len(ids), 1))(*ids)
-        # Workspace bytes to offer a call that brings none: the tables and about
-        # as many partials of every row as the longest request is cut into
-        # (pieces of 8 to 16 tiles of 32 keys), or what the library last asked
-        # for. A guess: the library checks it, and its size is asked for if it
-        # does not do (0: ask at once). Asking plans the call a second time.
-        tiles = [-(-int(x) // 32) for x in kv_lens]
-        per_wg = min(16, max(8, sum(tiles) * num_kv_heads // 512))
-        parts = min(64, max(tiles, default=0) // per_wg + 6)
-        guess = (1 << 18) + 4 * len(ids) + parts * self.Tq * num_kv_heads * group_size * (4 * head_dim + 4)
-        self.ws_bytes = guess if guess <= 64 << 20 else 0
+        self.ws_bytes = 0   # workspace bytes of a call, once the library has been asked
         I = ctypes.POINTER(ctypes.c_int32)
         self.c = _lib.DecodeProblem(B, num_kv_heads, group_size, head_dim, float(softmax_scale), page_size,
                                     int(num_pages), ctypes.cast(self._qo, I), ctypes.cast(self._kv, I),
@@ -367,13 +359,12 @@ def paged_decode_fwd(q, k_pages, v_pages, q_counts: Sequence[int], kv_lens: Sequ
     st = _stream_handle(q.device, stream)
 
     def size():
-        n = ctypes.c_size_t(0)
-        _check(load().cas_paged_decode_workspace_size(ctypes.byref(prob.c), ctypes.byref(n)))
-        prob.ws_bytes = n.value
-        return n.value
+        if not prob.ws_bytes:
+            n = ctypes.c_size_t(0)
+            _check(load().cas_paged_decode_workspace_size(ctypes.byref(prob.c), ctypes.byref(n)))
+            prob.ws_bytes = n.value
+        return prob.ws_bytes
 
-    if workspace is None and prob.ws_bytes:
-        workspace = _workspace(prob.ws_bytes, q.device)
     _with_workspace(lambda ptr, n: load().cas_paged_decode_fwd(*args, ptr, n, st), size, workspace, q.device)
     return o, lse
 

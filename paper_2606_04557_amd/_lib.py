@@ -23,7 +23,7 @@ CAS_DTYPE_FP32 = 1
 # Every function include/cas.h declares.
 EXPORTS = [
     "cas_prefix_attn_workspace_size", "cas_prefix_attn_fwd", "cas_prefix_attn_bwd",
-    "cas_cartridge_stage", "cas_status_string", "cas_last_error_message", "cas_abi_version",
+    "cas_cartridge_stage", "cas_status_string", "cas_last_error_message", "cas_abi_version", "cas_last_workspace_needed",
     "cas_set_tuning", "cas_get_tuning", "cas_plan_info", "cas_timing_enable",
     "cas_timing_reset", "cas_timing_read", "cas_adam_lr_scale", "cas_cartridge_adam_workspace_size",
     "cas_cartridge_adam", "cas_paged_decode_workspace_size", "cas_paged_decode_fwd",

@@ -25,6 +25,7 @@ using namespace cas;
 namespace {
 
 thread_local std::string g_err;
+thread_local size_t g_ws_needed = 0;
 
 cas_status_t fail(cas_status_t s, const std::string &msg) {
   g_err = msg;
@@ -906,6 +907,7 @@ cas_status_t hip_fail(const char *what, hipError_t e) {
 }
 
 cas_status_t check_workspace(void *ws, size_t have, size_t need) {
+  if (have < need || (need > 0 && !ws)) g_ws_needed = need;
   if (need > 0 && !ws) return fail(CAS_ERR_WORKSPACE, "workspace is NULL");
   if (have < need)
     return fail(CAS_ERR_WORKSPACE, "workspace too small: need " + std::to_string(need) + " bytes, have " +
@@ -1550,6 +1552,8 @@ const char *cas_status_string(cas_status_t s) {
 }
 
 const char *cas_last_error_message(void) { return g_err.c_str(); }
+
+size_t cas_last_workspace_needed(void) { return g_ws_needed; }
 
 float cas_adam_lr_scale(int32_t step, int32_t warmup_steps, int32_t warmup_buckets) {
   return lr_scale(step, warmup_steps, warmup_buckets);

@@ -202,3 +202,49 @@ def test_plan_time(cas, name, bound):
     ratio = plan_us(cas, pages) / plan_us(cas, private)
     print(f"{name}: {ratio:.2f}")
     assert ratio <= bound
+
+
+@pytest.mark.parametrize("n,given", [(4, None), (12, None), (60, None), (60, 1 << 20), (4, 0)])
+def test_call_plans_at_most_twice(cas, monkeypatch, n, given):
+    """Without a workspace, or with one that is too small, a decode call plans
+    its problem once for the size and once to run, whatever it shares, and is
+    offered no more than it needs; a problem that is kept is planned once per
+    call from then on."""
+    import ctypes
+
+    import torch
+    from paper_2606_04557_amd import _lib
+    real, plans, offered = cas.load(), [], []
+
+    class Lib:
+        def __getattr__(self, name):
+            return getattr(real, name)
+
+        def cas_paged_decode_workspace_size(self, prob, out):
+            plans.append("size")
+            return real.cas_paged_decode_workspace_size(prob, out)
+
+        def cas_paged_decode_fwd(self, prob, q, k, v, o, lse, ws, nbytes, stream):
+            # The library's refusal of a small workspace, which needs no device; nothing is run.
+            plans.append("fwd")
+            need = ctypes.c_size_t(0)
+            assert real.cas_paged_decode_workspace_size(prob, ctypes.byref(need)) == 0
+            if nbytes < need.value:
+                return real.cas_paged_decode_fwd(prob, q, k, v, o, lse, ws, nbytes, stream)
+            offered.append((nbytes, need.value))
+            return _lib.CAS_OK
+
+    monkeypatch.setattr(cas, "load", lambda: Lib())
+    monkeypatch.setattr(cas, "_stream_handle", lambda device, stream: None)
+    r = random.Random(9)
+    pages = [[c * 16 + j for c in r.sample(range(80), n) for j in range(16)] + [1280 + b] for b in range(64)]
+    q = torch.zeros(64, 4, 64, dtype=torch.bfloat16)
+    pool = torch.zeros(1344, 16, 2, 64, dtype=torch.bfloat16)
+    kv = [len(pl) * 16 - 3 for pl in pages]
+    prob = problem(cas, [1] * 64, kv, pages)
+    ws = torch.empty(given, dtype=torch.uint8) if given is not None else None
+    for first in (True, False):
+        cas.paged_decode_fwd(q, pool, pool.clone(), [1] * 64, kv, pages, 2, 2, 0.125, problem=prob, workspace=ws)
+        assert len(plans) == (2 if first or given is not None else 1), plans
+        assert offered[-1][0] == offered[-1][1]
+        plans.clear()
