@@ -329,8 +329,12 @@ typedef struct {
 } cas_decode_problem_t;
 
 /* Workspace bytes of a cas_paged_decode_fwd call (launch tables and the
- * split partials), written to *bytes; like the prefix-attention query it
- * depends on the compute-unit count of the current device. */
+ * partials), written to *bytes; like the prefix-attention query it depends on
+ * the compute-unit count of the current device. Page runs that requests share
+ * are streamed once, which takes a partial per request and run: with them the
+ * size is larger. A workspace of that size also serves any other page ids with
+ * the same counts and lengths: where it is too small for what they share, the
+ * call streams every request's keys by themselves. */
 cas_status_t cas_paged_decode_workspace_size(const cas_decode_problem_t *p, size_t *bytes);
 
 /*

@@ -346,7 +346,9 @@ def paged_decode_fwd(q, k_pages, v_pages, q_counts: Sequence[int], kv_lens: Sequ
     packed by request) over its kv_lens[b] keys held in the pages page_lists[b]
     of the pools k_pages, v_pages ([num_pages, page_size, Hkv, d] bf16).
     Returns O [Tq, Hq, d] and LSE [Hq, Tq] (fp32). A DecodeProblem built once
-    from the same tables may be passed as ``problem`` to skip rebuilding them."""
+    from the same tables may be passed as ``problem`` to skip rebuilding them.
+    A workspace that holds the call only without the partials of shared page
+    runs is used as it is, and then nothing is shared."""
     import torch
     num_pages, page_size, Hkv, D = k_pages.shape
     prob = problem if problem is not None else DecodeProblem(q_counts, kv_lens, page_lists, num_pages, page_size,

@@ -933,6 +933,27 @@ struct DecodePlan {
   // those rows take one pass over the keys.
   int row_blocks = 1;
   size_t off_work = 0, off_pages = 0, off_tokparts = 0, off_plse = 0, off_po = 0, bytes = 0;
+  size_t alone_bytes = 0;   // of the plan that shares nothing, which the page ids do not change
+
+  // Places nrows rows, nwork workgroups and `parts` partials of every row in the workspace.
+  void lay_out(const cas_decode_problem_t *p, int64_t nrows, int64_t nwork, int parts) {
+    size_t off = align_up((size_t)nrows * sizeof(DevDecodeRow), 256);
+    off_work = off;
+    off = align_up(off + (size_t)nwork * sizeof(DevDecodeWork), 256);
+    off_pages = off;
+    off = align_up(off + (size_t)p->page_offsets[p->batch] * sizeof(int32_t), 256);
+    off_tokparts = off;
+    off = align_up(off + (size_t)Tq * sizeof(int32_t), 256);
+    off_plse = off_po = 0;
+    if (parts > 1) {
+      const size_t plane = (size_t)Tq * Hq;
+      off_plse = off;
+      off = align_up(off + (size_t)parts * plane * 4, 256);
+      off_po = off;
+      off = align_up(off + (size_t)parts * plane * p->head_dim * 4, 256);
+    }
+    bytes = off;
+  }
 };
 
 // Consecutive page ids [id0, id1) from index `at` of request b's page list, and
@@ -1070,7 +1091,8 @@ std::vector<SharedRun> shared_runs(std::vector<Stretch> &st, int min_pages) {
   return runs;
 }
 
-cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
+// `share` false: every request streams its keys by itself.
+cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp, bool share = true) {
   if (!p) return fail(CAS_ERR_INVALID_ARGUMENT, "problem is NULL");
   if (p->batch < 1 || p->num_kv_heads < 1 || p->group_size < 1)
     return fail(CAS_ERR_INVALID_ARGUMENT, "batch, num_kv_heads and group_size must be >= 1");
@@ -1128,7 +1150,7 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
   constexpr int kMinSharedTiles = 8;
   std::vector<Stretch> st;
   std::vector<SharedRun> runs;
-  if (B > 1 && Tq * g <= (1 << 14)) {   // (longer query blocks would only grow the table of rows)
+  if (share && B > 1 && Tq * g <= (1 << 14)) {   // (longer query blocks would only grow the table of rows)
     std::vector<int32_t> safe(B);
     for (int b = 0; b < B; ++b) {
       // The first query of a request sees keys 0 .. kv_len - n.
@@ -1287,11 +1309,21 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
   // as 8 tiles and a request's partials allow; longer runs than its partials
   // hold in pieces of 32: longer pieces.
   const int64_t cus = device_topology().cus;
+  const int64_t per_wg_alone = std::max<int64_t>(8, ceil_div(t_alone[nb_alone - 1] * Hkv, 2 * cus));
   dp.row_blocks = sharing ? nb_shared : nb_alone;
   int64_t wgs = 0;
   if (!sharing) {
-    wgs = set_pieces(std::max<int64_t>(8, ceil_div(t_alone[nb_alone - 1] * Hkv, 2 * cus)));
+    wgs = set_pieces(per_wg_alone);
   } else {
+    // What the same requests need when they share nothing.
+    int64_t alone_wgs = 0, most = 1;
+    for (int b = 0; b < B; ++b) {
+      const int64_t n = std::min<int64_t>(kMaxDecParts, ceil_div(ceil_div(p->kv_lens[b], kDecTile), per_wg_alone));
+      alone_wgs += n * blocks_of[nb_alone - 1][b] * Hkv;
+      most = std::max(most, n);
+    }
+    dp.lay_out(p, Tq * g, alone_wgs, (int)most);
+    dp.alone_bytes = dp.bytes;
     int64_t least = 8;   // the shortest pieces that a request's partials allow
     if (count_parts(least) > kMaxDecParts) {
       int64_t most = least;
@@ -1368,21 +1400,8 @@ cas_status_t build_decode(const cas_decode_problem_t *p, DecodePlan &dp) {
                                         std::min(rows_per_wg, s.rows - r), i};
     row0 += s.rows;
   }
-  size_t off = align_up(dp.rows.size() * sizeof(DevDecodeRow), 256);
-  dp.off_work = off;
-  off = align_up(off + dp.work.size() * sizeof(DevDecodeWork), 256);
-  dp.off_pages = off;
-  off = align_up(off + (size_t)p->page_offsets[B] * sizeof(int32_t), 256);
-  dp.off_tokparts = off;
-  off = align_up(off + (size_t)Tq * sizeof(int32_t), 256);
-  if (dp.max_parts > 1) {
-    const size_t plane = (size_t)Tq * Hq;
-    dp.off_plse = off;
-    off = align_up(off + (size_t)dp.max_parts * plane * 4, 256);
-    dp.off_po = off;
-    off = align_up(off + (size_t)dp.max_parts * plane * p->head_dim * 4, 256);
-  }
-  dp.bytes = off;
+  dp.lay_out(p, nrows, wgs, dp.max_parts);
+  if (!sharing) dp.alone_bytes = dp.bytes;
   return CAS_OK;
 }
 
@@ -1564,7 +1583,7 @@ cas_status_t cas_paged_decode_workspace_size(const cas_decode_problem_t *p, size
   DecodePlan dp;
   cas_status_t s = build_decode(p, dp);
   if (s != CAS_OK) return s;
-  *bytes = dp.bytes;
+  *bytes = std::max(dp.bytes, dp.alone_bytes);
   return CAS_OK;
 }
 
@@ -1607,7 +1626,12 @@ cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, 
   if (lse) iv.push_back({(uintptr_t)lse, (uintptr_t)lse + (uintptr_t)dp.Tq * dp.Hq * 4, true, 2, "lse"});
   std::string msg;
   if (!overlap_free(iv, msg)) return fail(CAS_ERR_INVALID_ARGUMENT, msg);
-  s = check_workspace(workspace, ws_bytes, dp.bytes);
+  if (workspace && ws_bytes < dp.bytes && ws_bytes >= dp.alone_bytes) {
+    dp = DecodePlan{};
+    s = build_decode(p, dp, false);
+    if (s != CAS_OK) return s;
+  }
+  s = check_workspace(workspace, ws_bytes, ws_bytes < dp.bytes ? std::max(dp.bytes, dp.alone_bytes) : dp.bytes);
   if (s != CAS_OK) return s;
   hipStream_t stream = (hipStream_t)hip_stream;
   char *ws = (char *)workspace;

@@ -204,7 +204,7 @@ def test_plan_time(cas, name, bound):
     assert ratio <= bound
 
 
-@pytest.mark.parametrize("n,given", [(4, None), (12, None), (60, None), (60, 1 << 20), (4, 0)])
+@pytest.mark.parametrize("n,given", [(4, None), (12, None), (60, None), (60, 1 << 16), (4, 0)])
 def test_call_plans_at_most_twice(cas, monkeypatch, n, given):
     """Without a workspace, or with one that is too small, a decode call plans
     its problem once for the size and once to run, whatever it shares, and is
@@ -248,3 +248,42 @@ def test_call_plans_at_most_twice(cas, monkeypatch, n, given):
         assert len(plans) == (2 if first or given is not None else 1), plans
         assert offered[-1][0] == offered[-1][1]
         plans.clear()
+
+
+def fwd_status(cas, prob, nbytes):
+    """What a call with a workspace of nbytes at an odd address says: too small, or
+    (large enough, and refused for the address before any device is touched) misaligned."""
+    import ctypes
+    A = 1 << 44
+    return cas.load().cas_paged_decode_fwd(ctypes.byref(prob.c), A, 2 * A, 3 * A, 4 * A, None, 5 * A + 4, nbytes, None)
+
+
+@pytest.mark.parametrize("seed", range(40))
+def test_workspace_serves_other_pages_of_the_same_lengths(cas, seed):
+    """A workspace of the size asked for with one set of page ids is accepted
+    with any other of the same counts and lengths, shared or not, and a byte
+    less than the smaller of the two plans is not."""
+    import ctypes
+    from paper_2606_04557_amd import _lib
+    r = random.Random(700 + seed)
+    q, kv, pages, P, Hkv, g, D = draw(r)
+    n = sum(len(pl) for pl in pages)
+    ids, private = list(range(n)), []
+    for pl in pages:
+        private.append(ids[: len(pl)])
+        del ids[: len(pl)]
+    r.shuffle(pages[0])
+    same = [list(range(len(pl))) for pl in pages]
+    sizes, probs = [], []
+    for pls in (pages, private, same):
+        probs.append(problem(cas, q, kv, pls, P, Hkv, g, D))
+        out = ctypes.c_size_t(0)
+        assert cas.load().cas_paged_decode_workspace_size(ctypes.byref(probs[-1].c), ctypes.byref(out)) == _lib.CAS_OK
+        sizes.append(out.value)
+    assert sizes[1] <= min(sizes)
+    for prob in probs:
+        for s in sizes:
+            assert fwd_status(cas, prob, s) == _lib.CAS_ERR_ALIGNMENT
+        plan = cas.decode_plan(prob)[0].ws_bytes
+        assert fwd_status(cas, prob, min(plan, sizes[1]) - 1) == _lib.CAS_ERR_WORKSPACE
+        assert cas.load().cas_last_workspace_needed() == sizes[probs.index(prob)]

@@ -39,7 +39,7 @@ def _pool(seed, n_carts, cart_pages, P, Hkv, D, reqs, own_extra=0):
     return kp, vp, kv_lens, q_counts, pages
 
 
-def _run(kp, vp, kv_lens, q_counts, pages, Hkv, g, D, seed, scale=None):
+def _run(kp, vp, kv_lens, q_counts, pages, Hkv, g, D, seed, scale=None, workspace=None):
     import torch
     import paper_2606_04557_amd as cas
     Tq, Hq = sum(q_counts), Hkv * g
@@ -49,7 +49,7 @@ def _run(kp, vp, kv_lens, q_counts, pages, Hkv, g, D, seed, scale=None):
     dq = torch.from_numpy(q).to(torch.bfloat16).cuda()
     dk = torch.from_numpy(kp).to(torch.bfloat16).cuda()
     dv = torch.from_numpy(vp).to(torch.bfloat16).cuda()
-    o, lse = cas.paged_decode_fwd(dq, dk, dv, q_counts, kv_lens, pages, Hkv, g, scale)
+    o, lse = cas.paged_decode_fwd(dq, dk, dv, q_counts, kv_lens, pages, Hkv, g, scale, workspace=workspace)
     torch.cuda.synchronize()
     O, LSE = oracle.paged_decode_forward(q, kp, vp, q_counts, kv_lens, pages, scale, g)
     e_o = rel_err(host(o), O)
@@ -163,6 +163,25 @@ def test_decode_shared_runs(case):
     Hkv, g, D = c["Hkv"], c["g"], c["D"]
     kp, vp, kl, qc, pages = _shared_problem(1400, **c)
     _run(kp, vp, kl, qc, pages, Hkv, g, D, 1401)
+
+
+def test_decode_shared_runs_in_a_workspace_without_room_for_them():
+    """A workspace that holds only the plan that shares nothing is used for that plan."""
+    import ctypes
+    import torch
+    import paper_2606_04557_amd as cas
+    c = dict(SHARED[1])
+    c.pop("name")
+    Hkv, g, D, P = c["Hkv"], c["g"], c["D"], c["P"]
+    kp, vp, kl, qc, pages = _shared_problem(1450, **c)
+    ends = np.cumsum([0] + [len(pl) for pl in pages])
+    private = cas.DecodeProblem(qc, kl, [list(range(a, b)) for a, b in zip(ends, ends[1:])], int(ends[-1]), P, Hkv, g, D, 0.1)
+    n = ctypes.c_size_t(0)
+    cas._check(cas.load().cas_paged_decode_workspace_size(ctypes.byref(private.c), ctypes.byref(n)))
+    assert n.value < cas.decode_plan(cas.DecodeProblem(qc, kl, pages, kp.shape[0], P, Hkv, g, D, 0.1))[0].ws_bytes
+    ws = torch.full((n.value + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    _run(kp, vp, kl, qc, pages, Hkv, g, D, 1451, workspace=ws[:n.value])
+    assert bool((ws[n.value:] == 0x5a).all())
 
 
 @pytest.mark.parametrize("n_req", [1, 6])
