@@ -561,7 +561,8 @@ void build_dkdv_order(Plan &pl, bool with_self) {
   struct E {
     int64_t nblk;
     int32_t owner, pos, kvh;   // pos: tile within its cartridge or the row's self keys
-    DevWg wg() const { return {owner, pos, kvh}; }
+    int32_t cost() const { return (int32_t)std::min<int64_t>(nblk, 1 << 20) + kDkdvFixedCost; }
+    DevWg wg() const { return {owner, pos, kvh, cost()}; }
   };
   std::vector<E> v;
   const int key_tile = pl.dt == kBF16 ? kDkdvKeyTile : kDkdvKeyTileFp32;
@@ -603,7 +604,7 @@ void build_dkdv_order(Plan &pl, bool with_self) {
     }
     return;
   }
-  // bf16: one persistent workgroup per compute unit works through lists of
+  // bf16: the workgroups, one per compute unit at a time, work through lists of
   // entries, longest first. XCD-affine where the KV heads divide evenly:
   // workgroup i runs on XCD i % X (round-robin dispatch) and starts on list
   // i % X, the entries of KV heads h with h % X == i % X, so the query blocks
@@ -613,7 +614,9 @@ void build_dkdv_order(Plan &pl, bool with_self) {
   // list and then from those with work left: XCDs run at different speeds
   // (up to 4 % apart on one chip), so a fixed share per XCD ends with the
   // slowest, and a new workgroup per entry leaves its compute unit idle for
-  // 3-6 us between two of them.
+  // 3-6 us between two of them. After kDkdvStay it ends all the same: with its
+  // registers and LDS hardly another kernel fits beside it, so the compute unit
+  // is free for other streams' work only between two workgroups.
   const int L = X > 1 && pl.Hkv % X == 0 ? X : 1;
   std::vector<std::vector<E>> q(L);
   for (const E &e : v) q[e.kvh % L].push_back(e);
@@ -621,11 +624,23 @@ void build_dkdv_order(Plan &pl, bool with_self) {
   const int64_t wgs = std::min<int64_t>(cnt, std::max(1, pl.cus / L));   // workgroups of one list
   pl.dkdv_lists = L;
   pl.dkdv_list_len = (int)cnt;
-  pl.dkdv_list_head = (int)wgs;
   size_t at = 0;
   for (const std::vector<E> &l : q)
     for (const E &e : l) pl.order[at++] = e.wg();
-  pl.dkdv_grid = L * wgs;
+  if (cnt <= wgs) {   // every entry has a compute unit of its own
+    pl.dkdv_list_head = (int)cnt;
+    pl.dkdv_grid = L * cnt;
+    return;
+  }
+  // Entries that fill a stay by themselves need no draw where they come first;
+  // the shortest two rounds, or an eighth of the list, are drawn all the same.
+  // Workgroups: one for each of those entries, and as many as the others' costs
+  // fill stays (each but the last ends at kDkdvStay or beyond), so that nothing
+  // is left; one more round for XCDs that run out of their own list first.
+  int64_t full = 0, rest = 0;
+  for (const E &e : q[0]) (e.cost() >= kDkdvStay ? full : rest) += e.cost() >= kDkdvStay ? 1 : e.cost();
+  pl.dkdv_list_head = (int)std::max(wgs, std::min(full, cnt - std::max(2 * wgs, cnt / 8)));
+  pl.dkdv_grid = L * (std::min(cnt, full + rest / kDkdvStay + 1) + wgs);
 }
 
 // Turns the self-tile offsets of the tile table into pointers.

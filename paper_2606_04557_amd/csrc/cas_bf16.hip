@@ -1022,12 +1022,15 @@ __global__ __launch_bounds__(256) void bwd_prologue_bf16_kernel(PreParams p) {
 // ahead. Copies for blocks past the end use an empty buffer resource (they
 // write zeros that nothing reads).
 //
-// The workgroups are persistent: one per compute unit, each working through
-// entries (key tile, KV head) that it draws when it has finished one. Against
-// one workgroup per entry this saves the dispatch between two entries of a
-// compute unit: 858 -> 836 us on 8,192 packed tokens (8 entries of ~100 us per
-// compute unit), 2,142 -> 2,085 us on 64 ragged cartridges x 512 queries (34
-// of ~60 us), 578 -> 567 us on 4 x 1,024 cartridges x 1,024 queries.
+// A workgroup works through entries (key tile, KV head), drawing the next when
+// it has finished one, until it has stayed for kDkdvStay query blocks (about
+// 0.2 ms). Against one workgroup per entry this saves the dispatch between
+// two entries of a compute unit. Kernel times of three builds in turn, one
+// workgroup per entry, stays, workgroups that stay to the end: 16 x 2,048
+// cartridges x 2,048 queries 3,688, 3,621 and 3,632 us, 4 x 1,024 x 1,024 597,
+// 590 and 587 us, 64 x 2,176 x 512 2,115, 2,076 and 2,070 us. A 1,024^3 matrix
+// product on another stream, started in the first of these, takes 0.24, 0.21 and
+// 2.2 ms: it finds room only where a workgroup ends.
 //
 // P needs no mask for keys beyond the tile (their dK / dV columns are never
 // stored) or for packed rows beyond the batch row's last (Q, dO, Q^T, dO^T,
@@ -1056,6 +1059,7 @@ void dkdv_bf16_kernel(DkdvParams) {
   // compiler from telling the direct-to-LDS copies' targets from the LDS
   // reads, and it would then wait for every outstanding copy before each read.
   __shared__ __attribute__((aligned(1024))) char smem[CLAIM + 16];
+  int *const slot = reinterpret_cast<int *>(smem + CLAIM);   // the next entry; costs of the entries so far (thread 0's)
   char *const qr0 = smem, *const qr1 = smem + RB, *const ot0 = smem + 2 * RB, *const ot1 = smem + 3 * RB;
   char *const or0 = smem + 4 * RB, *const or1 = smem + 5 * RB, *const qt0 = smem + 6 * RB,
               *const qt1 = smem + 7 * RB;
@@ -1068,7 +1072,18 @@ void dkdv_bf16_kernel(DkdvParams) {
   int entry;
   {
     const DkdvParams p = load_kernarg<DkdvParams>();
-    entry = (int)blockIdx.x % p.lists * p.list_len + (int)blockIdx.x / p.lists;
+    const int list = (int)blockIdx.x % p.lists, j = (int)blockIdx.x / p.lists;
+    entry = list * p.list_len + j;
+    if (threadIdx.x == 0) slot[1] = 0;
+    if (j >= p.list_head) {
+      if (threadIdx.x == 0) {
+        const int claimed = __hip_atomic_fetch_add(p.claim + list, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        *slot = dkdv_claimed_entry(p, list, claimed);
+      }
+      lds_barrier();
+      entry = __builtin_amdgcn_readfirstlane(*slot);
+      if (entry < 0) return;
+    }
   }
   for (;;) {
   // Per entry, the lane index and the parameters are read anew: values kept
@@ -1082,6 +1097,7 @@ void dkdv_bf16_kernel(DkdvParams) {
   const bool pwave = wave < 4;
   int claimed = 0;                             // thread 0's draw from its list for the entry after this one
   const DevWg wg = load_const(p.order, entry);
+  if (tid == 0) slot[1] += wg.cost;
   const int kvh = __builtin_amdgcn_readfirstlane(wg.kvh), key0 = __builtin_amdgcn_readfirstlane(wg.tile) * KTB;
   const int g = p.g, Hkv = p.Hkv, Hq = Hkv * g;
   const float c = p.scale_log2;
@@ -1617,7 +1633,7 @@ void dkdv_bf16_kernel(DkdvParams) {
     // The next entry's draw travels while the gradients are stored.
     {
       const DkdvParams pe = load_kernarg<DkdvParams>();
-      if (tid == 0 && pe.list_len > pe.list_head)
+      if (tid == 0 && pe.list_len > pe.list_head && slot[1] < kDkdvStay)
         claimed = __hip_atomic_fetch_add(pe.claim + (int)blockIdx.x % pe.lists, 1, __ATOMIC_RELAXED,
                                          __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -1659,8 +1675,7 @@ void dkdv_bf16_kernel(DkdvParams) {
   if (pe.list_len == pe.list_head) return;   // every list was handed out at the start
   // After the barrier every wave has read its staged rows back, and the next
   // entry's copies may overwrite the arena.
-  int *const slot = reinterpret_cast<int *>(smem + CLAIM);
-  if (tid == 0) *slot = dkdv_claimed_entry(pe, (int)blockIdx.x % pe.lists, claimed);
+  if (tid == 0) *slot = slot[1] < kDkdvStay ? dkdv_claimed_entry(pe, (int)blockIdx.x % pe.lists, claimed) : -1;
   lds_barrier();
   entry = __builtin_amdgcn_readfirstlane(*slot);
   if (entry < 0) return;

@@ -83,7 +83,14 @@ struct DevWg {
   int32_t owner;
   int32_t tile;
   int32_t kvh;
+  int32_t cost;   // bf16: query blocks, and kDkdvFixedCost
 };
+
+// bf16 dK/dV: a workgroup draws further entries until the costs of those that
+// it has done reach kDkdvStay (in 64-row query blocks of about 1.7 us; setting
+// up and storing an entry takes as long as kDkdvFixedCost of them).
+constexpr int kDkdvStay = 128;
+constexpr int kDkdvFixedCost = 4;
 
 // One workgroup of the bf16 forward or dQ kernel: 256-row query block qblk
 // of batch row b at KV head kvh, key-axis split `split`.
@@ -184,8 +191,9 @@ struct DkdvParams {
   const DevWg *order;       // fp32: workgroup i takes entry i
   // bf16: `lists` lists (one per XCD, or one) of list_len entries, one after
   // the other in `order`. Workgroup i works on list i % lists: it starts with
-  // entry i / lists (< list_head) and claims entries from list_head on at run
-  // time, first of its own list, then of any list that has some left.
+  // entry i / lists where that is below list_head, and claims entries from
+  // list_head on at run time, first of its own list, then of any list that has
+  // some left, until it has stayed long enough (kDkdvStay) or none is left.
   int32_t *claim;           // [lists] entries claimed so far (zero at launch)
   int32_t lists, list_len, list_head;
   int32_t B, Hkv, g;

@@ -117,3 +117,43 @@ def test_dkdv_entry_lists(Hkv, n_carts):
                        q_lens=[40, 9, 130], cart_lens=[129 + 3 * i for i in range(n_carts)],
                        rows=[list(range(n_carts)), [0, n_carts - 1], list(range(0, n_carts, 3))], seed=777, cart_std=0.5)
     _check_full(GpuCase(wl), f"lists {Hkv} {n_carts}")
+
+
+def test_dkdv_leaves_compute_units_to_other_streams():
+    """A matrix product on another stream, started while a dK/dV of 3.6 ms
+    runs, finishes long before it: the workgroups, which leave no room for
+    another kernel on their compute units, end after a stay of about 0.2 ms.
+    (Measured 0.19-0.25 ms; 2.1-2.4 ms where they stayed to the end.)"""
+    import time
+
+    import torch
+    import paper_2606_04557_amd as cas
+    B, S, Hkv, g, D, n, L = 2, 2048, 8, 4, 128, 16, 2048
+    t = lambda *shape: torch.randn(*shape, device="cuda", dtype=torch.bfloat16)
+    q, ks, vs, do = t(B, S, Hkv * g, D), t(B, S, Hkv, D), t(B, S, Hkv, D), t(B, S, Hkv * g, D)
+    rows = [[cas.Segment(*(t(L, Hkv, D) for _ in range(4))) for _ in range(n)] for _ in range(B)]
+    scale = D ** -0.5
+    o, lse = cas.prefix_attn_fwd(q, ks, vs, rows, Hkv, g, scale)
+    ws = torch.empty(cas.workspace_size(cas.Problem.from_tensors(q, rows, Hkv, g, scale), True), dtype=torch.uint8, device="cuda")
+    grads = [torch.empty_like(x) for x in (q, ks, vs)]
+    bwd = lambda: cas.prefix_attn_bwd(q, ks, vs, rows, Hkv, g, scale, o, lse, do, dq=grads[0], dk_self=grads[1],
+                                      dv_self=grads[2], workspace=ws)
+    a, out = t(1024, 1024), t(1024, 1024)
+    side = torch.cuda.Stream()
+    bwd()
+    with torch.cuda.stream(side):
+        torch.mm(a, a, out=out)
+    torch.cuda.synchronize()
+    took = []
+    for _ in range(7):
+        e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        bwd()
+        time.sleep(0.0015)   # the prologue is over
+        with torch.cuda.stream(side):
+            e[0].record()
+            torch.mm(a, a, out=out)
+            e[1].record()
+        torch.cuda.synchronize()
+        took.append(e[0].elapsed_time(e[1]))
+    print("matmul beside dK/dV, ms:", [round(x, 3) for x in took])
+    assert sorted(took)[3] < 1.0
