@@ -324,13 +324,13 @@ void decode_bf16_kernel(DecodeParams p) {
           store4(p.part_o + (my_part[rb] * p.plane + R) * D + ch, o[0] * inv, o[1] * inv, o[2] * inv, o[3] * inv);
       }
       if (wave == 0 && bq == 0) {
-        const float lse = (M + log2f(L)) * kLn2;
+        // A NaN sum stays NaN (and in the merge, so that it gives what one pass would).
+        const float lse = L == 0.0f ? -INFINITY : (M + log2f(L)) * kLn2;
         if (my_part[rb] < 0) {
           const int t = my_R[rb] / Hq, h = my_R[rb] - t * Hq;
-          if (p.lse != nullptr) p.lse[(int64_t)h * p.Tq + t] = L > 0.0f ? lse : -INFINITY;
+          if (p.lse != nullptr) p.lse[(int64_t)h * p.Tq + t] = lse;
         } else {
-          // A NaN sum stays NaN, so that the merge gives what one pass would.
-          p.part_lse[my_part[rb] * p.plane + R] = L == 0.0f ? -INFINITY : lse;
+          p.part_lse[my_part[rb] * p.plane + R] = lse;
         }
       }
     }
@@ -382,10 +382,10 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(DecodeParams p) {
     }
   }
   if (gr != 0 || ns <= 1) return;   // (a request with one partial wrote its output itself)
-  // (As for one partial: a row without weight is zero with LSE -inf, NaN stays in O.)
+  // (As for one partial: a row without weight is zero with LSE -inf, NaN stays in O and LSE.)
   const float inv = w_sum > 0.0f ? 1.0f / w_sum : 0.0f;
   store4((__bf16 *)p.o + R * D + c4 * 4, acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
-  if (c4 == 0 && p.lse != nullptr) p.lse[(R - (int64_t)t * Hq) * p.Tq + t] = w_sum > 0.0f ? mx + logf(w_sum) : -INFINITY;
+  if (c4 == 0 && p.lse != nullptr) p.lse[(R - (int64_t)t * Hq) * p.Tq + t] = w_sum == 0.0f ? -INFINITY : mx + logf(w_sum);
 }
 
 }  // namespace

@@ -184,27 +184,32 @@ def test_decode_shared_runs_in_a_workspace_without_room_for_them():
     assert bool((ws[n.value:] == 0x5a).all())
 
 
-@pytest.mark.parametrize("n_req", [1, 6])
+@pytest.mark.parametrize("n_req", [1, 2, 6])
 def test_decode_nan_key_stays(n_req):
     """A key that is not a number makes every row that reads it NaN, whether the
-    row's keys take one pass, several pieces (one request of 2,100 keys) or a
-    run shared with other requests, and leaves the other requests alone."""
+    row's keys take one pass (two requests of 148 keys), several pieces (one of
+    2,612) or a run shared with other requests, in O and in LSE, and leaves the other
+    requests alone."""
     import torch
     import paper_2606_04557_amd as cas
     own = 2100 if n_req == 1 else 20
-    reqs = [([0, 1] if n_req > 1 and r % 2 else [0], own, 1) for r in range(n_req)] + [([], 700, 1)]
-    kp, vp, kl, qc, pages = _pool(1500 + n_req, 2, 32, 16, 2, 128, reqs)
+    reqs = [([0, 1] if n_req > 2 and r % 2 else [0], own, 1) for r in range(n_req)] + [([], 700, 1)]
+    kp, vp, kl, qc, pages = _pool(1500 + n_req, 2, 8 if n_req == 2 else 32, 16, 2, 128, reqs)
+    plan = cas.decode_plan(cas.DecodeProblem(qc, kl, pages, kp.shape[0], 16, 2, 4, 128, 0.1))
+    assert (plan[0].shared_runs > 0) == (n_req == 6) and any(r[2] < 0 for r in plan[1]) == (n_req == 2)
     o, lse = _run(kp, vp, kl, qc, pages, 2, 4, 128, 1501)
-    good = o.clone()
+    good, good_lse = o.clone(), lse.clone()
     kp = kp.copy()
     kp[5, 3, 1, 7] = np.nan          # cartridge 0, KV head 1
     q = rng.bf16_bits_to_f32(rng.f64_to_bf16_bits(rng.normal(rng.stream_key(1501, 3), sum(qc) * 8 * 128, 1.0)))
     q = torch.from_numpy(q.reshape(sum(qc), 8, 128)).to(torch.bfloat16).cuda()
-    o, _ = cas.paged_decode_fwd(q, torch.from_numpy(kp).to(torch.bfloat16).cuda(), torch.from_numpy(vp).to(torch.bfloat16).cuda(),
+    o, lse = cas.paged_decode_fwd(q, torch.from_numpy(kp).to(torch.bfloat16).cuda(), torch.from_numpy(vp).to(torch.bfloat16).cuda(),
                                 qc, kl, pages, 2, 4, float(np.float32(1.0 / np.sqrt(128))))
     torch.cuda.synchronize()
     assert bool(torch.isnan(o[:-1, 4:]).all())
     assert torch.equal(o[:-1, :4], good[:-1, :4]) and torch.equal(o[-1], good[-1])
+    assert bool(torch.isnan(lse[4:, :-1]).all())
+    assert torch.equal(lse[:4, :-1], good_lse[:4, :-1]) and torch.equal(lse[:, -1], good_lse[:, -1])
 
 
 def test_decode_retrieval_mix_full_size():
