@@ -109,7 +109,7 @@ struct Plan {
   int fwd_splits = 1, dq_splits = 1;
   int xcds = 8;                   // XCDs of the device (workgroup order)
   int cus = 256;                  // compute units of the device
-  int nqblk_fwd = 0, nqblk_dq = 0;
+  int nqblk = 0;   // row blocks of the longest row (forward and dQ)
   bool want_self_grad = false;
   // workspace layout
   size_t off_segs = 0, off_rows = 0, off_tiles = 0, off_items = 0, off_carts = 0, off_uses = 0, off_order = 0,
@@ -406,16 +406,15 @@ cas_status_t build_plan(const cas_problem_t *p, bool bwd, Plan &pl, int fwd_spli
     }
     return auto_splits(c, base, ceil_div(sum_tiles, std::max<int64_t>(1, base)), max_tiles, pl.T * pl.Hq * D * 4, topo.cus);
   };
-  const int rpw_fwd = bf16 ? kBf16RowsPerWg : kFwdRowsPerWg, rpw_dq = bf16 ? kBf16RowsPerWg : kDqRowsPerWg;
-  const SplitCost &sc = bf16 ? kBf16Splits : kFp32Splits;
-  const int fwd_auto = plan_splits(sc, rpw_fwd), dq_auto = rpw_dq == rpw_fwd ? fwd_auto : plan_splits(sc, rpw_dq);
-  pl.fwd_splits = tu.fwd_splits > 0 ? std::min(tu.fwd_splits, kMaxSplits) : fwd_auto;
+  // Forward and dQ have workgroups of the same rows, and so one plan.
+  static_assert(kFwdRowsPerWg == kDqRowsPerWg, "one split plan for both passes");
+  const int rpw = bf16 ? kBf16RowsPerWg : kFwdRowsPerWg;
+  const int auto_n = plan_splits(bf16 ? kBf16Splits : kFp32Splits, rpw);
+  pl.fwd_splits = tu.fwd_splits > 0 ? std::min(tu.fwd_splits, kMaxSplits) : auto_n;
   if (fwd_split_cap > 0) pl.fwd_splits = std::min(pl.fwd_splits, fwd_split_cap);
-  pl.dq_splits = tu.dq_splits > 0 ? std::min(tu.dq_splits, kMaxSplits) : dq_auto;
-  pl.nqblk_fwd = (int)ceil_div(pl.nrows_max, rpw_fwd);
-  pl.nqblk_dq = (int)ceil_div(pl.nrows_max, rpw_dq);
-  if ((int64_t)pl.B * Hkv * pl.nqblk_fwd * pl.fwd_splits > INT32_MAX ||
-      (int64_t)pl.B * Hkv * pl.nqblk_dq * pl.dq_splits > INT32_MAX)
+  pl.dq_splits = tu.dq_splits > 0 ? std::min(tu.dq_splits, kMaxSplits) : auto_n;
+  pl.nqblk = (int)ceil_div(pl.nrows_max, rpw);
+  if ((int64_t)pl.B * Hkv * pl.nqblk * std::max(pl.fwd_splits, pl.dq_splits) > INT32_MAX)
     return fail(CAS_ERR_UNSUPPORTED, "grid too large");
   if (bf16) build_items(pl, bwd ? pl.dq_splits : pl.fwd_splits);
 
@@ -1538,7 +1537,7 @@ cas_status_t prefix_attn_fwd_run(const cas_problem_t *p, const void *q, const vo
   fp.Hkv = pl.Hkv;
   fp.g = pl.g;
   fp.nrows_max = pl.nrows_max;
-  fp.nqblk = pl.nqblk_fwd;
+  fp.nqblk = pl.nqblk;
   fp.splits = pl.fwd_splits;
   fp.lse_hs = pl.packed ? (int32_t)pl.T : pl.Sq;
   fp.n_items = (int32_t)pl.items.size();
@@ -1758,7 +1757,7 @@ cas_status_t cas_plan_info(const cas_problem_t *p, cas_plan_info_t *out) {
   if (s != CAS_OK) return s;
   out->fwd_splits = pf.fwd_splits;
   out->dq_splits = pb.dq_splits;
-  out->fwd_workgroups = pf.dt == kBF16 ? (int32_t)pf.items.size() : pf.nqblk_fwd * pf.Hkv * pf.B * pf.fwd_splits;
+  out->fwd_workgroups = pf.dt == kBF16 ? (int32_t)pf.items.size() : pf.nqblk * pf.Hkv * pf.B * pf.fwd_splits;
   out->dkdv_workgroups = (int32_t)pb.order_cap;
   out->unique_segments = (int32_t)pb.carts.size();
   out->total_key_tiles = (int32_t)(pb.order_cap / pb.Hkv);
@@ -1859,7 +1858,7 @@ cas_status_t cas_prefix_attn_bwd(const cas_problem_t *p, const void *q, const vo
     dp.Hkv = pl.Hkv;
     dp.g = pl.g;
     dp.nrows_max = pl.nrows_max;
-    dp.nqblk = pl.nqblk_dq;
+    dp.nqblk = pl.nqblk;
     dp.splits = pl.dq_splits;
     dp.n_items = (int32_t)pl.items.size();
     dp.scale_log2 = scale_log2;
