@@ -402,10 +402,10 @@ hipError_t launch_decode_bf16(const DecodeParams &p, int D, int n_work, int row_
   return hipGetLastError();
 }
 
-// Groups per row: each should take at least two of the row's partials (max_parts
-// is the call's largest count). With fewer the extra workgroups cost more
-// than the shorter walk saves: 4,096 rows of 5 splits take 6.7 us with eight
-// groups, 4.9 us with one walking them all.
+// Groups per row: four and eight only where each takes at least two of the
+// partials of the call's longest row (max_parts). With fewer the extra
+// workgroups cost more than the shorter walk saves: 4,096 rows of 5 splits take
+// 6.7 us with eight groups, 4.8 us with two, 4.9 us with one walking them all.
 template <int D>
 static void launch_decode_merge_t(const DecodeParams &p, int max_parts, hipStream_t s) {
   auto grid = [&](int gr) { const int64_t rpw = 256 / (D / 4 * gr); return dim3((unsigned)((p.plane + rpw - 1) / rpw)); };

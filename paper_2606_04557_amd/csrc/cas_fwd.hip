@@ -13,14 +13,14 @@
 // Segment tiles stop at segment ends, so a ragged tail is the only masked
 // prefix tile; self tiles are masked only where they cross the diagonal.
 // With splits > 1 each workgroup takes a contiguous share of the key tiles
-// and writes a normalised partial O and its LSE, merged afterwards.
+// and writes its O as accumulated, with the row's maximum and sum, merged
+// afterwards (the bf16 kernels: normalised, with its LSE).
 #include <algorithm>
 
 #include "cas_device.h"
 
 namespace cas {
 
-//
 // The next tile's rows are loaded while the current tile is worked on. Bound by
 // the matrix products of one wave per SIMD (64 cycles each): 32 rows per wave
 // with the loads ahead take 5.8 us a tile of 64 channels and 9.4 of 128, where
