@@ -368,6 +368,22 @@ cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, 
                                   size_t ws_bytes, void *hip_stream);
 
 /*
+ * The same in two steps, so that a step's planning is done once for its size
+ * and all its calls (the attention layers of a model share one set of tables):
+ * create validates and plans for the current device and writes the workspace
+ * bytes to *ws_bytes; run is cas_paged_decode_fwd of the planned problem, from
+ * any thread and on any stream. The problem's host arrays have to stay as they
+ * are until the plan is destroyed; runs already enqueued do not need it.
+ */
+typedef struct cas_decode_plan cas_decode_plan_t;
+
+cas_status_t cas_paged_decode_plan_create(const cas_decode_problem_t *p, cas_decode_plan_t **plan, size_t *ws_bytes);
+cas_status_t cas_paged_decode_run(const cas_decode_plan_t *plan, const void *q, const void *k_pages,
+                                  const void *v_pages, void *o, float *lse, void *workspace,
+                                  size_t ws_bytes, void *hip_stream);
+cas_status_t cas_paged_decode_plan_destroy(cas_decode_plan_t *plan);
+
+/*
  * Budget manager (paper: paragraphs "Budget Manager" and "Pool rotation";
  * hyperparameter table: budget B = 20, rotation interval R = 10, swap
  * fraction phi = 0.5, least-trained cartridges first, Adam moments of

@@ -309,9 +309,26 @@ def cartridge_adam(carts: Sequence[AdamCartridge], lr: float, beta1: float = 0.9
                                      ws.numel(), _stream_handle(dev, stream)))
 
 
+class _DecodePlan:
+    """A launch plan (cas_decode_plan_t), with the tables that it refers to."""
+
+    def __init__(self, problem: DecodeProblem):
+        lib, handle, n = load(), ctypes.c_void_p(), ctypes.c_size_t(0)
+        _check(lib.cas_paged_decode_plan_create(ctypes.byref(problem.c), ctypes.byref(handle), ctypes.byref(n)))
+        self.handle, self.ws_bytes = handle, n.value
+        self._tables = (problem._qo, problem._kv, problem._po, problem._ids)
+        self._destroy = lib.cas_paged_decode_plan_destroy
+
+    def __del__(self):
+        if hasattr(self, "_destroy"):
+            self._destroy(self.handle)
+
+
 class DecodeProblem:
     """Host tables of a paged decode call (cas_decode_problem_t): per request its
-    query count, key count and page list (pages of [page_size, Hkv, d])."""
+    query count, key count and page list (pages of [page_size, Hkv, d]). The
+    first call on them plans its launches, for every further one too: the
+    tables are not to be changed afterwards."""
 
     def __init__(self, q_counts: Sequence[int], kv_lens: Sequence[int], page_lists: Sequence[Sequence[int]],
                  num_pages: int, page_size: int, num_kv_heads: int, group_size: int, head_dim: int,
@@ -331,11 +348,18 @@ class DecodeProblem:
         self._kv = (ctypes.c_int32 * max(B, 1))(*[int(x) for x in kv_lens])
         self._po = (ctypes.c_int32 * (B + 1))(*po)
         self._ids = (ctypes.c_int32 * max(len(ids), 1))(*ids)
-        self.ws_bytes = 0   # workspace bytes of a call, once the library has been asked
+        self._plan = None
         I = ctypes.POINTER(ctypes.c_int32)
         self.c = _lib.DecodeProblem(B, num_kv_heads, group_size, head_dim, float(softmax_scale), page_size,
                                     int(num_pages), ctypes.cast(self._qo, I), ctypes.cast(self._kv, I),
                                     ctypes.cast(self._po, I), ctypes.cast(self._ids, I))
+
+    def plan(self) -> _DecodePlan:
+        # (Threads that plan at the same time each have a plan; one of them is kept.)
+        plan = self._plan
+        if plan is None:
+            plan = self._plan = _DecodePlan(self)
+        return plan
 
 
 def paged_decode_fwd(q, k_pages, v_pages, q_counts: Sequence[int], kv_lens: Sequence[int],
@@ -346,9 +370,8 @@ def paged_decode_fwd(q, k_pages, v_pages, q_counts: Sequence[int], kv_lens: Sequ
     packed by request) over its kv_lens[b] keys held in the pages page_lists[b]
     of the pools k_pages, v_pages ([num_pages, page_size, Hkv, d] bf16).
     Returns O [Tq, Hq, d] and LSE [Hq, Tq] (fp32). A DecodeProblem built once
-    from the same tables may be passed as ``problem`` to skip rebuilding them.
-    A workspace that holds the call only without the partials of shared page
-    runs is used as it is, and then nothing is shared."""
+    from the same tables may be passed as ``problem`` to skip rebuilding and
+    planning them."""
     import torch
     num_pages, page_size, Hkv, D = k_pages.shape
     prob = problem if problem is not None else DecodeProblem(q_counts, kv_lens, page_lists, num_pages, page_size,
@@ -357,17 +380,10 @@ def paged_decode_fwd(q, k_pages, v_pages, q_counts: Sequence[int], kv_lens: Sequ
         o = torch.empty_like(q)
     if lse is None and need_lse:
         lse = torch.empty((q.shape[1], q.shape[0]), dtype=torch.float32, device=q.device)
-    args = (ctypes.byref(prob.c), q.data_ptr(), k_pages.data_ptr(), v_pages.data_ptr(), o.data_ptr(), _ptr(lse))
-    st = _stream_handle(q.device, stream)
-
-    def size():
-        if not prob.ws_bytes:
-            n = ctypes.c_size_t(0)
-            _check(load().cas_paged_decode_workspace_size(ctypes.byref(prob.c), ctypes.byref(n)))
-            prob.ws_bytes = n.value
-        return prob.ws_bytes
-
-    _with_workspace(lambda ptr, n: load().cas_paged_decode_fwd(*args, ptr, n, st), size, workspace, q.device)
+    plan = prob.plan()
+    ws = workspace if workspace is not None and workspace.numel() >= plan.ws_bytes else _workspace(plan.ws_bytes, q.device)
+    _check(load().cas_paged_decode_run(plan.handle, q.data_ptr(), k_pages.data_ptr(), v_pages.data_ptr(), o.data_ptr(),
+                                       _ptr(lse), ws.data_ptr(), ws.numel(), _stream_handle(q.device, stream)))
     return o, lse
 
 

@@ -1621,30 +1621,28 @@ cas_status_t cas_paged_decode_plan_info(const cas_decode_problem_t *p, cas_decod
   return CAS_OK;
 }
 
-cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, const void *k_pages,
-                                  const void *v_pages, void *o, float *lse, void *workspace,
-                                  size_t ws_bytes, void *hip_stream) {
-  DecodePlan dp;
-  cas_status_t s = build_decode(p, dp);
-  if (s != CAS_OK) return s;
+static cas_status_t run_decode(const cas_decode_problem_t *p, const DecodePlan &plan, const void *q, const void *k_pages,
+                               const void *v_pages, void *o, float *lse, void *workspace, size_t ws_bytes,
+                               void *hip_stream) {
   if (!q || !k_pages || !v_pages || !o) return fail(CAS_ERR_INVALID_ARGUMENT, "q, k_pages, v_pages and o must be non-NULL");
   if (!aligned16(q) || !aligned16(k_pages) || !aligned16(v_pages) || !aligned16(o) || ((uintptr_t)lse & 3u))
     return fail(CAS_ERR_ALIGNMENT, "tensors must be 16-byte aligned (lse 4-byte)");
-  const uintptr_t qbytes = (uintptr_t)dp.Tq * dp.Hq * p->head_dim * 2;
+  const uintptr_t qbytes = (uintptr_t)plan.Tq * plan.Hq * p->head_dim * 2;
   const uintptr_t pool = (uintptr_t)p->num_pages * p->page_size * p->num_kv_heads * p->head_dim * 2;
   std::vector<Interval> iv;
   iv.push_back({(uintptr_t)q, (uintptr_t)q + qbytes, false, 0, "q"});
   iv.push_back({(uintptr_t)k_pages, (uintptr_t)k_pages + pool, false, 0, "k_pages"});
   iv.push_back({(uintptr_t)v_pages, (uintptr_t)v_pages + pool, false, 0, "v_pages"});
   iv.push_back({(uintptr_t)o, (uintptr_t)o + qbytes, true, 1, "o"});
-  if (lse) iv.push_back({(uintptr_t)lse, (uintptr_t)lse + (uintptr_t)dp.Tq * dp.Hq * 4, true, 2, "lse"});
+  if (lse) iv.push_back({(uintptr_t)lse, (uintptr_t)lse + (uintptr_t)plan.Tq * plan.Hq * 4, true, 2, "lse"});
   std::string msg;
   if (!overlap_free(iv, msg)) return fail(CAS_ERR_INVALID_ARGUMENT, msg);
-  if (workspace && ws_bytes < dp.bytes && ws_bytes >= dp.alone_bytes) {
-    dp = DecodePlan{};
-    s = build_decode(p, dp, false);
-    if (s != CAS_OK) return s;
-  }
+  // A workspace for the same lengths that share nothing: neither do these.
+  DecodePlan unshared;
+  const bool room = ws_bytes >= plan.bytes || ws_bytes < plan.alone_bytes || !workspace;
+  cas_status_t s = room ? CAS_OK : build_decode(p, unshared, false);
+  if (s != CAS_OK) return s;
+  const DecodePlan &dp = room ? plan : unshared;
   s = check_workspace(workspace, ws_bytes, ws_bytes < dp.bytes ? std::max(dp.bytes, dp.alone_bytes) : dp.bytes);
   if (s != CAS_OK) return s;
   hipStream_t stream = (hipStream_t)hip_stream;
@@ -1681,6 +1679,44 @@ cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, 
     e = timed("decode_merge", stream, [&] { return launch_decode_merge_bf16(kp, p->head_dim, dp.max_parts, stream); });
     if (e != hipSuccess) return hip_fail("decode_merge launch", e);
   }
+  return CAS_OK;
+}
+
+cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, const void *k_pages,
+                                  const void *v_pages, void *o, float *lse, void *workspace,
+                                  size_t ws_bytes, void *hip_stream) {
+  DecodePlan dp;
+  cas_status_t s = build_decode(p, dp);
+  if (s != CAS_OK) return s;
+  return run_decode(p, dp, q, k_pages, v_pages, o, lse, workspace, ws_bytes, hip_stream);
+}
+
+struct cas_decode_plan {
+  cas_decode_problem_t p;
+  DecodePlan dp;
+};
+
+cas_status_t cas_paged_decode_plan_create(const cas_decode_problem_t *p, cas_decode_plan_t **plan, size_t *ws_bytes) {
+  if (!plan || !ws_bytes) return fail(CAS_ERR_INVALID_ARGUMENT, "plan or ws_bytes is NULL");
+  *plan = nullptr;
+  auto pl = std::make_unique<cas_decode_plan>();
+  cas_status_t s = build_decode(p, pl->dp);
+  if (s != CAS_OK) return s;
+  pl->p = *p;
+  *ws_bytes = std::max(pl->dp.bytes, pl->dp.alone_bytes);
+  *plan = pl.release();
+  return CAS_OK;
+}
+
+cas_status_t cas_paged_decode_run(const cas_decode_plan_t *plan, const void *q, const void *k_pages,
+                                  const void *v_pages, void *o, float *lse, void *workspace,
+                                  size_t ws_bytes, void *hip_stream) {
+  if (!plan) return fail(CAS_ERR_INVALID_ARGUMENT, "plan is NULL");
+  return run_decode(&plan->p, plan->dp, q, k_pages, v_pages, o, lse, workspace, ws_bytes, hip_stream);
+}
+
+cas_status_t cas_paged_decode_plan_destroy(cas_decode_plan_t *plan) {
+  delete plan;
   return CAS_OK;
 }
 

@@ -205,33 +205,26 @@ def test_plan_time(cas, name, bound):
 
 
 @pytest.mark.parametrize("n,given", [(4, None), (12, None), (60, None), (60, 1 << 16), (4, 0)])
-def test_call_plans_at_most_twice(cas, monkeypatch, n, given):
+def test_a_problem_is_planned_once(cas, monkeypatch, n, given):
     """Without a workspace, or with one that is too small, a decode call plans
-    its problem once for the size and once to run, whatever it shares, and is
-    offered no more than it needs; a problem that is kept is planned once per
-    call from then on."""
-    import ctypes
-
+    its problem once, whatever it shares, and offers what it needs and no more;
+    further calls on the same DecodeProblem plan nothing."""
     import torch
     from paper_2606_04557_amd import _lib
     real, plans, offered = cas.load(), [], []
 
     class Lib:
         def __getattr__(self, name):
+            assert name in ("cas_paged_decode_plan_destroy", "cas_last_error_message", "cas_status_string"), name
             return getattr(real, name)
 
-        def cas_paged_decode_workspace_size(self, prob, out):
-            plans.append("size")
-            return real.cas_paged_decode_workspace_size(prob, out)
+        def cas_paged_decode_plan_create(self, prob, handle, nbytes):
+            status = real.cas_paged_decode_plan_create(prob, handle, nbytes)
+            plans.append(nbytes._obj.value)
+            return status
 
-        def cas_paged_decode_fwd(self, prob, q, k, v, o, lse, ws, nbytes, stream):
-            # The library's refusal of a small workspace, which needs no device; nothing is run.
-            plans.append("fwd")
-            need = ctypes.c_size_t(0)
-            assert real.cas_paged_decode_workspace_size(prob, ctypes.byref(need)) == 0
-            if nbytes < need.value:
-                return real.cas_paged_decode_fwd(prob, q, k, v, o, lse, ws, nbytes, stream)
-            offered.append((nbytes, need.value))
+        def cas_paged_decode_run(self, handle, q, k, v, o, lse, ws, nbytes, stream):
+            offered.append(nbytes)
             return _lib.CAS_OK
 
     monkeypatch.setattr(cas, "load", lambda: Lib())
@@ -241,21 +234,26 @@ def test_call_plans_at_most_twice(cas, monkeypatch, n, given):
     q = torch.zeros(64, 4, 64, dtype=torch.bfloat16)
     pool = torch.zeros(1344, 16, 2, 64, dtype=torch.bfloat16)
     kv = [len(pl) * 16 - 3 for pl in pages]
-    prob = problem(cas, [1] * 64, kv, pages)
     ws = torch.empty(given, dtype=torch.uint8) if given is not None else None
-    for first in (True, False):
-        cas.paged_decode_fwd(q, pool, pool.clone(), [1] * 64, kv, pages, 2, 2, 0.125, problem=prob, workspace=ws)
-        assert len(plans) == (2 if first or given is not None else 1), plans
-        assert offered[-1][0] == offered[-1][1]
-        plans.clear()
+    call = lambda prob: cas.paged_decode_fwd(q, pool, pool.clone(), [1] * 64, kv, pages, 2, 2, 0.125, problem=prob, workspace=ws)
+    prob = problem(cas, [1] * 64, kv, pages)
+    for _ in range(3):
+        call(prob)
+        assert len(plans) == 1 and offered[-1] == plans[0]
+    call(None)
+    assert len(plans) == 2 and offered[-1] == plans[1]
 
 
 def fwd_status(cas, prob, nbytes):
-    """What a call with a workspace of nbytes at an odd address says: too small, or
-    (large enough, and refused for the address before any device is touched) misaligned."""
+    """What a call with a workspace of nbytes at an odd address says, planned
+    before or not: too small, or (large enough, and refused for the address
+    before any device is touched) misaligned."""
     import ctypes
     A = 1 << 44
-    return cas.load().cas_paged_decode_fwd(ctypes.byref(prob.c), A, 2 * A, 3 * A, 4 * A, None, 5 * A + 4, nbytes, None)
+    args = A, 2 * A, 3 * A, 4 * A, None, 5 * A + 4, nbytes, None
+    status = cas.load().cas_paged_decode_fwd(ctypes.byref(prob.c), *args)
+    assert cas.load().cas_paged_decode_run(prob.plan().handle, *args) == status
+    return status
 
 
 @pytest.mark.parametrize("seed", range(40))
@@ -287,3 +285,23 @@ def test_workspace_serves_other_pages_of_the_same_lengths(cas, seed):
         plan = cas.decode_plan(prob)[0].ws_bytes
         assert fwd_status(cas, prob, min(plan, sizes[1]) - 1) == _lib.CAS_ERR_WORKSPACE
         assert cas.load().cas_last_workspace_needed() == sizes[probs.index(prob)]
+
+
+def test_plan_handle_validation(cas):
+    import ctypes
+    from paper_2606_04557_amd import _lib
+    lib, h, n = cas.load(), ctypes.c_void_p(), ctypes.c_size_t(0)
+    bad = problem(cas, [1], [17], [[0]])     # 17 keys need two pages of 16
+    assert lib.cas_paged_decode_plan_create(ctypes.byref(bad.c), ctypes.byref(h), ctypes.byref(n)) == _lib.CAS_ERR_INVALID_ARGUMENT
+    assert not h.value and lib.cas_paged_decode_plan_destroy(None) == _lib.CAS_OK
+    with pytest.raises(cas.CasError):
+        bad.plan()
+    A = 1 << 44
+    assert lib.cas_paged_decode_run(None, A, A, A, A, None, A, 1 << 20, None) == _lib.CAS_ERR_INVALID_ARGUMENT
+    good = problem(cas, [1], [17], [[0, 1]])
+    run = lambda *a: lib.cas_paged_decode_run(good.plan().handle, *a)
+    assert run(None, A, 2 * A, 3 * A, None, 4 * A, 1 << 20, None) == _lib.CAS_ERR_INVALID_ARGUMENT
+    assert run(A, 2 * A, 3 * A, A, None, 4 * A, 1 << 20, None) == _lib.CAS_ERR_INVALID_ARGUMENT      # o over q
+    assert run(A + 8, 2 * A, 3 * A, 4 * A, None, 5 * A, 1 << 20, None) == _lib.CAS_ERR_ALIGNMENT
+    assert run(A, 2 * A, 3 * A, 4 * A, None, None, 0, None) == _lib.CAS_ERR_WORKSPACE
+    assert lib.cas_last_workspace_needed() == good.plan().ws_bytes
