@@ -151,9 +151,9 @@ Topology device_topology() {
 // Key-axis splits of the forward or dQ pass, for base_wgs workgroups unsplit
 // that walk avg_tiles key tiles on average and max_tiles at most, one
 // workgroup per compute unit at a time (bf16). Costs are in key tiles (about
-// 1.2-1.7 us each): a workgroup costs kWgTiles on top of the tiles it walks
+// 1.2-1.7 us each): a workgroup costs wg_tiles on top of the tiles it walks
 // (dispatch, first loads, pipeline fill and drain, epilogue: 11-13 us), a
-// split pass kMergeTiles for the merge's launch plus the partials' bytes.
+// split pass merge_tiles for the merge's launch plus the partials' bytes.
 //
 // Rounds of workgroups decide. Forward and merge, each timed with its launch:
 // 32 workgroups' 139 tiles take 53 us in 8 splits, one round, and 67 us in 16,
@@ -161,7 +161,7 @@ Topology device_topology() {
 // workgroups' 18 tiles 32 us unsplit, 26 us in 4 to 10 splits; 152 workgroups'
 // 17 tiles 31 us unsplit, 44 us in 2 splits.
 //
-// Where one round would leave splits of kLongTiles or more, one and two
+// Where one round would leave splits of long_tiles or more, one and two
 // rounds measure alike (64 workgroups of 2,056 tiles, forward and dQ: 2,287 us
 // in 4 splits, 2,320 us in 8); such calls keep two workgroups per compute
 // unit. With more workgroups than compute units, two splits at most are tried

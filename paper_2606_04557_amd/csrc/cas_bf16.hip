@@ -1028,8 +1028,8 @@ __global__ __launch_bounds__(256) void bwd_prologue_bf16_kernel(PreParams p) {
 // two entries of a compute unit. Kernel times of three builds in turn, one
 // workgroup per entry, stays, workgroups that stay to the end: 16 x 2,048
 // cartridges x 2,048 queries 3,688, 3,621 and 3,632 us, 4 x 1,024 x 1,024 597,
-// 590 and 587 us, 64 x 2,176 x 512 2,115, 2,076 and 2,070 us. A 1,024^3 matrix
-// product on another stream, started in the first of these, takes 0.24, 0.21 and
+// 590 and 587 us, 64 x 2,176 x 512 2,115, 2,076 and 2,070 us, 8,192 packed tokens
+// 838, 840 and 835 us. A 1,024^3 matrix product on another stream, started in the first of these, takes 0.24, 0.21 and
 // 2.2 ms: it finds room only where a workgroup ends.
 //
 // P needs no mask for keys beyond the tile (their dK / dV columns are never
