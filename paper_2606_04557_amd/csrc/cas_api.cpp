@@ -102,7 +102,7 @@ struct Plan {
   std::vector<int32_t> uses;
   std::vector<DevWg> order;       // dK/dV workgroups, longest first
   int64_t dkdv_grid = 0;          // dK/dV workgroups launched
-  int dkdv_lists = 1, dkdv_list_len = 0, dkdv_list_head = 0;   // bf16 (see DkdvParams)
+  int dkdv_lists = 1, dkdv_list_len = 0, dkdv_list_head = 0, dkdv_bounded = 0;   // bf16 (see DkdvParams)
   int64_t order_cap = 0;          // 128-key tiles x KV heads, with every self tile
   int64_t order_alloc = 0;        // order entries with every self tile
   int64_t max_prefix = 0;
@@ -626,20 +626,25 @@ void build_dkdv_order(Plan &pl, bool with_self) {
   size_t at = 0;
   for (const std::vector<E> &l : q)
     for (const E &e : l) pl.order[at++] = e.wg();
-  if (cnt <= wgs) {   // every entry has a compute unit of its own
-    pl.dkdv_list_head = (int)cnt;
-    pl.dkdv_grid = L * cnt;
-    return;
+  // As many workgroups as stays that the list's costs fill, taken in order, and
+  // at least one round. The last round stays until nothing is left, which takes
+  // every entry whatever the stays came to, and needs no workgroup to find out
+  // that there is none. Entries that fill a stay by themselves need no draw
+  // where they come first; the shortest two rounds, or an eighth of the list,
+  // are drawn all the same.
+  int64_t full = 0, stays = 0, cost = 0;
+  for (const E &e : q[0]) {
+    if (e.cost() >= kDkdvStay) ++full;
+    cost += e.cost();
+    if (cost >= kDkdvStay) {
+      ++stays;
+      cost = 0;
+    }
   }
-  // Entries that fill a stay by themselves need no draw where they come first;
-  // the shortest two rounds, or an eighth of the list, are drawn all the same.
-  // Workgroups: one for each of those entries, and as many as the others' costs
-  // fill stays (each but the last ends at kDkdvStay or beyond), so that nothing
-  // is left; one more round for XCDs that run out of their own list first.
-  int64_t full = 0, rest = 0;
-  for (const E &e : q[0]) (e.cost() >= kDkdvStay ? full : rest) += e.cost() >= kDkdvStay ? 1 : e.cost();
+  const int64_t n = std::max(wgs, stays);
   pl.dkdv_list_head = (int)std::max(wgs, std::min(full, cnt - std::max(2 * wgs, cnt / 8)));
-  pl.dkdv_grid = L * (std::min(cnt, full + rest / kDkdvStay + 1) + wgs);
+  pl.dkdv_bounded = (int)(n - wgs);
+  pl.dkdv_grid = L * n;
 }
 
 // Turns the self-tile offsets of the tile table into pointers.
@@ -1934,6 +1939,7 @@ cas_status_t cas_prefix_attn_bwd(const cas_problem_t *p, const void *q, const vo
     kp.lists = pl.dkdv_lists;
     kp.list_len = pl.dkdv_list_len;
     kp.list_head = pl.dkdv_list_head;
+    kp.bounded = pl.dkdv_bounded;
     kp.B = pl.B;
     kp.Hkv = pl.Hkv;
     kp.g = pl.g;

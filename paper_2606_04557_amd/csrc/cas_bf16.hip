@@ -1025,12 +1025,13 @@ __global__ __launch_bounds__(256) void bwd_prologue_bf16_kernel(PreParams p) {
 // A workgroup works through entries (key tile, KV head), drawing the next when
 // it has finished one, until it has stayed for kDkdvStay query blocks (about
 // 0.2 ms). Against one workgroup per entry this saves the dispatch between
-// two entries of a compute unit. Kernel times of three builds in turn, one
-// workgroup per entry, stays, workgroups that stay to the end: 16 x 2,048
-// cartridges x 2,048 queries 3,688, 3,621 and 3,632 us, 4 x 1,024 x 1,024 597,
-// 590 and 587 us, 64 x 2,176 x 512 2,115, 2,076 and 2,070 us, 8,192 packed tokens
-// 838, 840 and 835 us. A 1,024^3 matrix product on another stream, started in the first of these, takes 0.24, 0.21 and
-// 2.2 ms: it finds room only where a workgroup ends.
+// two entries of a compute unit; the last round of workgroups stays until
+// nothing is left. Kernel times of three builds in turn (one workgroup per
+// entry, stays, every workgroup to the end): 16 x 2,048 cartridges x 2,048
+// queries 3,774, 3,718 and 3,722 us, 4 x 1,024 x 1,024 569, 561 and 563 us,
+// ragged 64 x 2,176 x 512 2,081, 2,060 and 2,056 us, 8,192 packed tokens 843, 837
+// and 837 us. A 1,024^3 matrix product on another stream, started in the first of
+// these, takes 0.26, 0.21 and 2.2 ms: it finds room only where a workgroup ends.
 //
 // P needs no mask for keys beyond the tile (their dK / dV columns are never
 // stored) or for packed rows beyond the batch row's last (Q, dO, Q^T, dO^T,
@@ -1059,7 +1060,7 @@ void dkdv_bf16_kernel(DkdvParams) {
   // compiler from telling the direct-to-LDS copies' targets from the LDS
   // reads, and it would then wait for every outstanding copy before each read.
   __shared__ __attribute__((aligned(1024))) char smem[CLAIM + 16];
-  int *const slot = reinterpret_cast<int *>(smem + CLAIM);   // the next entry; costs of the entries so far (thread 0's)
+  int *const slot = reinterpret_cast<int *>(smem + CLAIM);   // the next entry; costs of the entries so far, or -1 to stay (thread 0's)
   char *const qr0 = smem, *const qr1 = smem + RB, *const ot0 = smem + 2 * RB, *const ot1 = smem + 3 * RB;
   char *const or0 = smem + 4 * RB, *const or1 = smem + 5 * RB, *const qt0 = smem + 6 * RB,
               *const qt1 = smem + 7 * RB;
@@ -1074,7 +1075,7 @@ void dkdv_bf16_kernel(DkdvParams) {
     const DkdvParams p = load_kernarg<DkdvParams>();
     const int list = (int)blockIdx.x % p.lists, j = (int)blockIdx.x / p.lists;
     entry = list * p.list_len + j;
-    if (threadIdx.x == 0) slot[1] = 0;
+    if (threadIdx.x == 0) slot[1] = j < p.bounded ? 0 : -1;
     if (j >= p.list_head) {
       if (threadIdx.x == 0) {
         const int claimed = __hip_atomic_fetch_add(p.claim + list, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1097,7 +1098,7 @@ void dkdv_bf16_kernel(DkdvParams) {
   const bool pwave = wave < 4;
   int claimed = 0;                             // thread 0's draw from its list for the entry after this one
   const DevWg wg = load_const(p.order, entry);
-  if (tid == 0) slot[1] += wg.cost;
+  if (tid == 0 && slot[1] >= 0) slot[1] += wg.cost;
   const int kvh = __builtin_amdgcn_readfirstlane(wg.kvh), key0 = __builtin_amdgcn_readfirstlane(wg.tile) * KTB;
   const int g = p.g, Hkv = p.Hkv, Hq = Hkv * g;
   const float c = p.scale_log2;

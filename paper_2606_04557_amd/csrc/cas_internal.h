@@ -193,9 +193,10 @@ struct DkdvParams {
   // the other in `order`. Workgroup i works on list i % lists: it starts with
   // entry i / lists where that is below list_head, and claims entries from
   // list_head on at run time, first of its own list, then of any list that has
-  // some left, until it has stayed long enough (kDkdvStay) or none is left.
+  // some left: until it has stayed long enough (kDkdvStay) where i / lists is
+  // below bounded, or else until none is left.
   int32_t *claim;           // [lists] entries claimed so far (zero at launch)
-  int32_t lists, list_len, list_head;
+  int32_t lists, list_len, list_head, bounded;
   int32_t B, Hkv, g;
   float scale_log2;
   float scale;
