@@ -115,6 +115,12 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
         return _lib
     if not os.path.exists(path):
         raise RuntimeError(f"libcas is not built ({path} missing): run paper_2606_04557_amd.build")
+    # torch brings its own HIP runtime: loaded before it, libcas would bind to the
+    # system's, and the process would have two, of which the second sees no device.
+    try:
+        import torch  # noqa: F401
+    except ImportError:
+        pass          # (planning and validation do without)
     lib = ctypes.CDLL(path)
     vp, i32, sz = ctypes.c_void_p, ctypes.c_int32, ctypes.c_size_t
     P = ctypes.POINTER

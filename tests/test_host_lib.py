@@ -470,3 +470,14 @@ def test_binding_segment_table(layout):
         odd = wide[..., ::2]
         with pytest.raises(ValueError):
             cas.Problem.from_tensors(q, [[cas.Segment(odd, odd)], []], 2, 2, 0.1)
+
+
+def test_one_hip_runtime_in_the_process():
+    """libcas loaded before torch shares torch's HIP runtime: with a second one
+    in the process its calls would find no device."""
+    import subprocess
+    import sys
+    code = ("import paper_2606_04557_amd as cas; cas.load(); import torch\n"
+            "print(len({l.split()[-1] for l in open('/proc/self/maps') if 'libamdhip64' in l}))")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, stdout=subprocess.PIPE, text=True, check=True)
+    assert r.stdout.split() == ["1"]
