@@ -46,7 +46,9 @@ COMMON_FLAGS = [
 
 # The bf16 kernels produce no NaN of their own (masked scores are -inf, never
 # NaN), so max/min need not quiet signalling NaNs: without this every fmaxf
-# on an MFMA result costs an extra canonicalising instruction.
+# on an MFMA result costs an extra canonicalising instruction. A NaN among the
+# inputs still reaches every output that depends on it: it travels through the
+# arithmetic, and where one decides anything the bits are compared.
 #
 # The optimizer step rounds once per operation in a documented order, so no
 # multiply-add contraction there.

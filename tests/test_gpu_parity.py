@@ -180,11 +180,13 @@ def test_fp32_splits_lose_no_precision(D, splits):
 
 @pytest.mark.parametrize("dtype", ["bf16", "fp32"])
 @pytest.mark.parametrize("splits", [1, 3, 9])
-def test_nan_key_stays(dtype, splits):
+@pytest.mark.parametrize("D", [64, 128])
+def test_nan_key_stays(dtype, splits, D):
     """A key that is not a number makes O and LSE of the rows that read it NaN,
-    however the key axis is split; other rows and KV heads are untouched."""
+    however the key axis is split; other rows and KV heads are untouched. (The
+    bf16 kernels, one per head_dim, are compiled as if no comparison met a NaN.)"""
     import paper_2606_04557_amd as cas
-    wl = casgen.custom("nan", dtype, batch=2, q_len=40, num_q_heads=4, num_kv_heads=2, head_dim=64, cart_lens=[300, 200],
+    wl = casgen.custom("nan", dtype, batch=2, q_len=40, num_q_heads=4, num_kv_heads=2, head_dim=D, cart_lens=[300, 200],
                        rows=[[0, 1], [0]], seed=240, cart_std=0.5)
     T = casgen.make_tensors(wl)
     try:
