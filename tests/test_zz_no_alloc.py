@@ -20,7 +20,7 @@ def test_noalloc_forward_matches_workspace_forward():
     import paper_2606_04557_amd as cas
     torch.cuda.synchronize()
     # B = 1 and 256 queries give 32 forward workgroups, so the planner splits
-    # the 40K-token ragged prefix 16 ways: 67 MB of partials, more than the
+    # the 37K-token ragged prefix 8 ways: 34 MB of partials, more than the
     # 16 MiB scratch, which then holds 3 splits.
     lens = [1500 + 37 * i for i in range(20)]
     big = casgen.custom("noalloc_big", "bf16", batch=1, q_len=256, num_q_heads=32, num_kv_heads=8,
