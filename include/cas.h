@@ -372,8 +372,8 @@ cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, 
  * and all its calls (the attention layers of a model share one set of tables):
  * create validates and plans for the current device and writes the workspace
  * bytes to *ws_bytes; run is cas_paged_decode_fwd of the planned problem, from
- * any thread and on any stream. The problem's host arrays have to stay as they
- * are until the plan is destroyed; runs already enqueued do not need it.
+ * any thread and on any stream. The plan has copies of the problem's tables; runs
+ * already enqueued do not need it.
  */
 typedef struct cas_decode_plan cas_decode_plan_t;
 

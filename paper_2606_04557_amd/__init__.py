@@ -310,13 +310,12 @@ def cartridge_adam(carts: Sequence[AdamCartridge], lr: float, beta1: float = 0.9
 
 
 class _DecodePlan:
-    """A launch plan (cas_decode_plan_t), with the tables that it refers to."""
+    """A launch plan (cas_decode_plan_t)."""
 
     def __init__(self, problem: DecodeProblem):
         lib, handle, n = load(), ctypes.c_void_p(), ctypes.c_size_t(0)
         _check(lib.cas_paged_decode_plan_create(ctypes.byref(problem.c), ctypes.byref(handle), ctypes.byref(n)))
         self.handle, self.ws_bytes = handle, n.value
-        self._tables = (problem._qo, problem._kv, problem._po, problem._ids)
         self._destroy = lib.cas_paged_decode_plan_destroy
 
     def __del__(self):

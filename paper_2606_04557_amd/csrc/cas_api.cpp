@@ -1697,7 +1697,8 @@ cas_status_t cas_paged_decode_fwd(const cas_decode_problem_t *p, const void *q, 
 }
 
 struct cas_decode_plan {
-  cas_decode_problem_t p;
+  cas_decode_problem_t p;         // its tables are the copies below
+  std::vector<int32_t> tables;    // q_offsets, kv_lens, page_offsets, page_ids as they were validated
   DecodePlan dp;
 };
 
@@ -1707,7 +1708,18 @@ cas_status_t cas_paged_decode_plan_create(const cas_decode_problem_t *p, cas_dec
   auto pl = std::make_unique<cas_decode_plan>();
   cas_status_t s = build_decode(p, pl->dp);
   if (s != CAS_OK) return s;
+  const size_t B = (size_t)p->batch, ids = (size_t)p->page_offsets[B];
+  pl->tables.reserve(3 * B + 2 + ids);
+  auto copy = [&](const int32_t *src, size_t n) {
+    const int32_t *at = pl->tables.data() + pl->tables.size();
+    pl->tables.insert(pl->tables.end(), src, src + n);
+    return at;
+  };
   pl->p = *p;
+  pl->p.q_offsets = copy(p->q_offsets, B + 1);
+  pl->p.kv_lens = copy(p->kv_lens, B);
+  pl->p.page_offsets = copy(p->page_offsets, B + 1);
+  pl->p.page_ids = copy(p->page_ids, ids);
   *ws_bytes = std::max(pl->dp.bytes, pl->dp.alone_bytes);
   *plan = pl.release();
   return CAS_OK;

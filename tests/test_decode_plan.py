@@ -305,3 +305,24 @@ def test_plan_handle_validation(cas):
     assert run(A + 8, 2 * A, 3 * A, 4 * A, None, 5 * A, 1 << 20, None) == _lib.CAS_ERR_ALIGNMENT
     assert run(A, 2 * A, 3 * A, 4 * A, None, None, 0, None) == _lib.CAS_ERR_WORKSPACE
     assert lib.cas_last_workspace_needed() == good.plan().ws_bytes
+
+
+def test_plan_keeps_its_own_tables(cas):
+    """A plan does not look at the caller's tables again: freed or changed, they
+    neither take a run out of the pool nor change what it needs."""
+    import ctypes
+    from paper_2606_04557_amd import _lib
+    r = random.Random(5)
+    pages = [[c * 16 + j for c in r.sample(range(80), 20) for j in range(16)] for _ in range(64)]
+    prob = problem(cas, [1] * 64, [len(pl) * 16 - 3 for pl in pages], pages)
+    lib, h, n = cas.load(), ctypes.c_void_p(), ctypes.c_size_t(0)
+    info = cas.decode_plan(prob)[0]
+    assert info.shared_runs > 0 and lib.cas_paged_decode_plan_create(ctypes.byref(prob.c), ctypes.byref(h), ctypes.byref(n)) == 0
+    for a in (prob._qo, prob._kv, prob._po, prob._ids):
+        for i in range(len(a)):
+            a[i] = -7
+    A = 1 << 44
+    run = lambda nbytes: lib.cas_paged_decode_run(h, A, 2 * A, 3 * A, 4 * A, None, 5 * A + 4, nbytes, None)
+    # (Large enough and refused for its address; the smaller one is for the plan that shares nothing, made by the run.)
+    assert run(n.value) == run(info.ws_bytes - 1) == _lib.CAS_ERR_ALIGNMENT
+    assert lib.cas_paged_decode_plan_destroy(h) == _lib.CAS_OK
