@@ -382,6 +382,8 @@ cas_status_t cas_paged_decode_run(const cas_decode_plan_t *plan, const void *q, 
                                   const void *v_pages, void *o, float *lse, void *workspace,
                                   size_t ws_bytes, void *hip_stream);
 cas_status_t cas_paged_decode_plan_destroy(cas_decode_plan_t *plan);
+/* Whether plan is one of problem p as its values and tables are now (1) or not (0). */
+int32_t cas_paged_decode_plan_matches(const cas_decode_plan_t *plan, const cas_decode_problem_t *p);
 
 /*
  * Budget manager (paper: paragraphs "Budget Manager" and "Pool rotation";

@@ -326,8 +326,8 @@ class _DecodePlan:
 class DecodeProblem:
     """Host tables of a paged decode call (cas_decode_problem_t): per request its
     query count, key count and page list (pages of [page_size, Hkv, d]). The
-    first call on them plans its launches, for every further one too: the
-    tables are not to be changed afterwards."""
+    first call on them plans its launches, for every further one too while they
+    stay as they are."""
 
     def __init__(self, q_counts: Sequence[int], kv_lens: Sequence[int], page_lists: Sequence[Sequence[int]],
                  num_pages: int, page_size: int, num_kv_heads: int, group_size: int, head_dim: int,
@@ -356,7 +356,7 @@ class DecodeProblem:
     def plan(self) -> _DecodePlan:
         # (Threads that plan at the same time each have a plan; one of them is kept.)
         plan = self._plan
-        if plan is None:
+        if plan is None or not load().cas_paged_decode_plan_matches(plan.handle, ctypes.byref(self.c)):
             plan = self._plan = _DecodePlan(self)
         return plan
 

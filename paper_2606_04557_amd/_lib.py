@@ -28,7 +28,7 @@ EXPORTS = [
     "cas_timing_reset", "cas_timing_read", "cas_adam_lr_scale", "cas_cartridge_adam_workspace_size",
     "cas_cartridge_adam", "cas_paged_decode_workspace_size", "cas_paged_decode_fwd",
     "cas_paged_decode_plan_info", "cas_paged_decode_plan_create", "cas_paged_decode_run", "cas_paged_decode_plan_destroy",
-    "cas_pool_plan_rotation", "cas_pool_create", "cas_pool_destroy", "cas_pool_host_cartridge",
+    "cas_paged_decode_plan_matches", "cas_pool_plan_rotation", "cas_pool_create", "cas_pool_destroy", "cas_pool_host_cartridge",
     "cas_pool_load", "cas_pool_active", "cas_pool_end_step", "cas_pool_flush",
     "cas_prefix_attn_fwd_noalloc", "cas_pool_read_moments",
 ]
@@ -146,6 +146,8 @@ def load(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.cas_paged_decode_plan_create.argtypes = [P(DecodeProblem), P(vp), P(sz)]
     lib.cas_paged_decode_run.argtypes = [vp, vp, vp, vp, vp, vp, vp, sz, vp]
     lib.cas_paged_decode_plan_destroy.argtypes = [vp]
+    lib.cas_paged_decode_plan_matches.argtypes = [vp, P(DecodeProblem)]
+    lib.cas_paged_decode_plan_matches.restype = i32
     u8p = P(ctypes.c_uint8)
     lib.cas_pool_plan_rotation.argtypes = [P(i32), u8p, i32, i32, ctypes.c_float, P(i32), P(i32), P(i32)]
     lib.cas_pool_create.argtypes = [P(PoolConfig), P(vp)]

@@ -1732,6 +1732,18 @@ cas_status_t cas_paged_decode_run(const cas_decode_plan_t *plan, const void *q, 
   return run_decode(&plan->p, plan->dp, q, k_pages, v_pages, o, lse, workspace, ws_bytes, hip_stream);
 }
 
+int32_t cas_paged_decode_plan_matches(const cas_decode_plan_t *plan, const cas_decode_problem_t *p) {
+  if (!plan || !p || !p->q_offsets || !p->kv_lens || !p->page_offsets || !p->page_ids) return 0;
+  const cas_decode_problem_t &o = plan->p;
+  if (p->batch != o.batch || p->num_kv_heads != o.num_kv_heads || p->group_size != o.group_size || p->head_dim != o.head_dim ||
+      p->softmax_scale != o.softmax_scale || p->page_size != o.page_size || p->num_pages != o.num_pages)
+    return 0;
+  auto same = [](const int32_t *a, const int32_t *b, size_t n) { return std::memcmp(a, b, n * sizeof(int32_t)) == 0; };
+  const size_t B = (size_t)o.batch;
+  return same(p->q_offsets, o.q_offsets, B + 1) && same(p->kv_lens, o.kv_lens, B) &&
+         same(p->page_offsets, o.page_offsets, B + 1) && same(p->page_ids, o.page_ids, (size_t)o.page_offsets[B]);
+}
+
 cas_status_t cas_paged_decode_plan_destroy(cas_decode_plan_t *plan) {
   delete plan;
   return CAS_OK;

@@ -215,7 +215,8 @@ def test_a_problem_is_planned_once(cas, monkeypatch, n, given):
 
     class Lib:
         def __getattr__(self, name):
-            assert name in ("cas_paged_decode_plan_destroy", "cas_last_error_message", "cas_status_string"), name
+            assert name in ("cas_paged_decode_plan_destroy", "cas_paged_decode_plan_matches", "cas_last_error_message",
+                            "cas_status_string"), name
             return getattr(real, name)
 
         def cas_paged_decode_plan_create(self, prob, handle, nbytes):
@@ -326,3 +327,23 @@ def test_plan_keeps_its_own_tables(cas):
     # (Large enough and refused for its address; the smaller one is for the plan that shares nothing, made by the run.)
     assert run(n.value) == run(info.ws_bytes - 1) == _lib.CAS_ERR_ALIGNMENT
     assert lib.cas_paged_decode_plan_destroy(h) == _lib.CAS_OK
+
+
+def test_a_changed_problem_is_planned_again(cas):
+    """A DecodeProblem whose tables or values change after its first call is
+    planned anew (and validated: a page id past the pool is refused)."""
+    prob = problem(cas, [1, 1], [40, 33], [[0, 1, 2], [3, 4, 5]])
+    for table, i, to in (("_kv", 0, 41), ("_ids", 5, 2), ("_po", 0, 0), ("_qo", 1, 1)):
+        plan = prob.plan()
+        assert prob.plan() is plan
+        a = getattr(prob, table)
+        changed, a[i] = a[i] != to, to
+        assert (prob.plan() is not plan) == changed
+    for name, to in (("softmax_scale", 0.25), ("num_pages", 7), ("batch", 1), ("group_size", 1), ("num_kv_heads", 1),
+                     ("head_dim", 128)):
+        plan = prob.plan()
+        setattr(prob.c, name, to)
+        assert prob.plan() is not plan and prob.plan() is prob.plan()
+    prob._ids[0] = 7
+    with pytest.raises(cas.CasError):
+        prob.plan()
